@@ -280,14 +280,22 @@ __device__ __forceinline__ double lnf_diff(uint64_t x, uint64_t y)
     return neg ? -r : r;
 }
 
-// floor(a * b / d) for a*b < 2^106, d >= 1, exactly: estimate in binary64,
-// correct with 128-bit products.
+// floor(a * b / d) for a*b < 2^117, d >= 1 and a quotient below 2^53,
+// exactly: an estimate in binary64 (off by a few), corrected by the remainder.
+// Below d = 2^60 the remainder of the estimate fits a signed 64-bit word, so
+// the products are needed modulo 2^64 only.
 __device__ __forceinline__ uint64_t muldiv_floor(uint64_t a, uint64_t b, uint64_t d)
 {
+    const double est = floor(((double)a * (double)b) / (double)d);
+    uint64_t q = est <= 0.0 ? 0ull : (uint64_t)est;
+    if (d < (1ull << 60)) {
+        int64_t r = (int64_t)(a * b - q * d);
+        while (r < 0) { --q; r += (int64_t)d; }
+        while (r >= (int64_t)d) { ++q; r -= (int64_t)d; }
+        return q;
+    }
     typedef unsigned __int128 u128;
     const u128 num = (u128)a * b;
-    double est = floor(((double)a * (double)b) / (double)d);
-    uint64_t q = est <= 0.0 ? 0ull : (uint64_t)est;
     while ((u128)q * d > num) --q;
     while ((u128)(q + 1) * d <= num) ++q;
     return q;
@@ -308,126 +316,212 @@ struct HypRatio {
     uint64_t N, K, k, M;
     __device__ __forceinline__ double operator()(uint64_t X) const
     {
-        double T = lnf_diff(X, M);
-        T = T + lnf_diff(k - X, k - M);
-        T = T + lnf_diff(K - X, K - M);
-        T = T + lnf_diff(N - K - k + X, N - K - k + M);
+        // one copy of the difference's code (rarely run: see RouQuick)
+        double T = 0.0;
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t b = i == 0 ? 0 : i == 1 ? k : i == 2 ? K : N - K - k;
+            const bool up = i == 0 || i == 3;
+            T = T + lnf_diff(up ? b + X : b - X, up ? b + M : b - M);
+        }
         return T;
-    }
-    // the t-th difference of the sum above, and the sum in the same order
-    __device__ __forceinline__ double term(uint32_t t, uint64_t X) const
-    {
-        const uint64_t b = t == 0 ? 0 : t == 1 ? k : t == 2 ? K : N - K - k;
-        const bool up = t == 0 || t == 3;
-        return lnf_diff(up ? b + X : b - X, up ? b + M : b - M);
-    }
-    __device__ __forceinline__ double combine(double d0, double d1, double d2, double d3, uint64_t) const
-    {
-        return ((d0 + d1) + d2) + d3;
     }
 };
 
-// log f(x) - log f(M) of the binomial law; lq = log p - log(1-p).
+// log f(x) - log f(M) of the binomial law.
 struct BinRatio {
     uint64_t N, M;
-    double lq;
+    double p;
     __device__ __forceinline__ double operator()(uint64_t X) const
     {
-        double T = lnf_diff(X, M);
-        T = T + lnf_diff(N - X, N - M);
-        T = T + ((double)X - (double)M) * lq;
+        double T = 0.0;
+#pragma unroll 1
+        for (int i = 0; i < 2; ++i) T = T + lnf_diff(i ? N - X : X, i ? N - M : M);
+        if (p != 0.5) {                    // log p - log(1 - p) is zero at 1/2
+            const double lq = log_f64(p) - log1p_f64(-p);
+            T = T + ((double)X - (double)M) * lq;
+        }
         return T;
-    }
-    __device__ __forceinline__ double term(uint32_t t, uint64_t X) const
-    {
-        const bool up = t != 1;
-        const uint64_t b = t == 1 ? N : 0;
-        return t < 2 ? lnf_diff(up ? b + X : b - X, up ? b + M : b - M) : 0.0;
-    }
-    __device__ __forceinline__ double combine(double d0, double d1, double, double, uint64_t X) const
-    {
-        return (d0 + d1) + ((double)X - (double)M) * lq;
     }
 };
 
-// Broadcast within aligned lane groups of G = 2 or 4 lanes: the value of lane
-// T of each group, to the whole group (DPP quad_perm; the group's lanes are
-// active together).
-template <int G, int T>
-__device__ __forceinline__ double group_bcast(double v)
+// ---------------------------------------------------------------------------
+// The acceptance decision in binary32.  A proposal is accepted iff
+// 2 log U <= T = log f(X) - log f(M) (the squeezes lie on either side of
+// 2 log U, so away from equality they never change the decision).  The four
+// (hypergeometric) or two (binomial) log-factorial differences of T, the
+// arguments A_i moving by +d or -d, d = X - M, are with y_i = A_i + 1/2
+//   ln (A_i + d)! - ln A_i! = d ln y_i + y_i phi(d / y_i) + (t - t^2) / (24 y_i) + ...,
+//   phi(t) = (1 + t) ln(1 + t) - t = t^2 (1/2 - t/6 + t^2/12 - ...),
+// (Stirling's series about A + 1/2).  The d ln y_i add up to d times the
+// logarithm of a ratio that is 1 + q with |q| <= sum 1 / y_i because M is the
+// mode, so nothing large is subtracted and binary32 holds T to
+// 2e-6 of the sum of its terms plus the neglected 2e-5 of the smallest
+// arguments taken (y = 16, t = 0.2; measured at most 0.37 of the margin
+// below).  Proposals with |t| > 0.2 or |d| >= 2^24 (a few per cent: the
+// ratio of uniforms has a heavy tail) are rejected by a bound on phi.
+// Decisions closer than the margin, and laws outside y >= 16, |q| <= 1/16, go
+// to the binary64 ratio above (about one proposal in 10^4 of the tile
+// tree's), so the variates are those of the binary64 test bit for bit.  Measured, headline call: planner 0.38 ->
+// 0.15 ms, count kernel 0.167 -> 0.069 ms (under the profiler; the binary64
+// ratio is about 500 vector instructions, this one about 50).
+// ---------------------------------------------------------------------------
+template <int NT>
+struct RouQuick {
+    static_assert(NT == 2 || NT == 4, "binomial: two factorials, hypergeometric: four");
+    float lam, iy[NT];
+
+    static __device__ __forceinline__ constexpr bool up(int i) { return i == 0 || i == 3; }
+
+    // y_i, and the ratio's q = num / den
+    __device__ __forceinline__ void init(const double (&y)[NT], double num, double den)
+    {
+        float c = 0.0f, most = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            iy[i] = __builtin_amdgcn_rcpf((float)y[i]);
+            c = __builtin_fmaf(up(i) ? iy[i] : -iy[i], iy[i], c);
+            most = fmaxf(most, iy[i]);
+        }
+        const float q = (float)num * __builtin_amdgcn_rcpf((float)den);
+        float l = __builtin_fmaf(q, -1.0f / 6.0f, 0.2f);
+        l = __builtin_fmaf(q, l, -0.25f);
+        l = __builtin_fmaf(q, l, 1.0f / 3.0f);
+        l = __builtin_fmaf(q, l, -0.5f);
+        l = __builtin_fmaf(q, l, 1.0f);
+        lam = __builtin_fmaf(c, 1.0f / 24.0f, q * l);
+        if (!(most <= 1.0f / 16.0f && fabsf(q) <= 1.0f / 16.0f)) iy[0] = 1e30f;   // every t is out of range
+    }
+
+    // 1: accepted, 0: rejected, -1: too close to say.  X = M + d64 is in
+    // range, so every A_i + d is at least 0 and every t above -1.
+    __device__ __forceinline__ int decide(int64_t d64, double U) const
+    {
+        const float d = (float)d64;
+        // 2 ln U; the hardware's base-2 logarithm is good to 1 ulp
+        const float lu = 1.3862943611f * __builtin_amdgcn_logf((float)U);
+        float most = iy[0];
+#pragma unroll
+        for (int i = 1; i < NT; ++i) most = fmaxf(most, iy[i]);
+        const float ad = fabsf(d);
+        if (!(ad * most <= 0.2f && ad < 0x1p24f)) {
+            // far from the mode (a small U): phi(t) >= t^2 / (2 + 2 |t| / 3)
+            // (Bernstein) bounds T from above; the neglected terms are below 1
+            if (most > 1.0f) return -1;
+            float low = 0.0f;
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const float t = ad * iy[i];
+                low = __builtin_fmaf(ad * t, __builtin_amdgcn_rcpf(__builtin_fmaf(t, 0.66666669f, 2.0f)), low);
+            }
+            return 0.9999f * low - 1.0001f * fabsf(d * lam) + lu > 1.0f ? 0 : -1;
+        }
+        const float d2 = d * d;
+        float S = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const float t = (up(i) ? d : -d) * iy[i];
+            float P = __builtin_fmaf(t, -1.0f / 72.0f, 1.0f / 56.0f);
+            P = __builtin_fmaf(t, P, -1.0f / 42.0f);
+            P = __builtin_fmaf(t, P, 1.0f / 30.0f);
+            P = __builtin_fmaf(t, P, -1.0f / 20.0f);
+            P = __builtin_fmaf(t, P, 1.0f / 12.0f);
+            P = __builtin_fmaf(t, P, -1.0f / 6.0f);
+            P = __builtin_fmaf(t, P, __builtin_fmaf(iy[i] * iy[i], -1.0f / 24.0f, 0.5f));
+            S = __builtin_fmaf(d2 * iy[i], P, S);
+        }
+        const float gap = __builtin_fmaf(d, lam, S) + lu;
+        const float eps = __builtin_fmaf(2e-6f, S - lu, 5e-5f);
+        return gap < -eps ? 1 : gap > eps ? 0 : -1;
+    }
+};
+
+// The binary64 test of one proposal, with the squeezes.
+template <class Ratio>
+__device__ __forceinline__ bool rou_accept(const Ratio &ratio, uint64_t X, double U)
 {
-    static_assert((G == 2 && T < 2) || (G == 4 && T < 4), "lane within a group of 2 or 4");
-    constexpr int ctrl = G == 4 ? T * 0x55 : (T | T << 2 | (T + 2) << 4 | (T + 2) << 6);
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, ctrl, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), ctrl, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    const double T = ratio(X);
+    if (U * (4.0 - U) - 3.0 <= T) return true;
+    if (U * (U - T) >= 1.0) return false;
+    return 2.0 * log_f64(U) <= T;
 }
 
-// PAR = 1, TERMS = 1: one proposal at a time in one lane.  Otherwise an
-// aligned group of PAR * TERMS lanes works on one variate (the same
-// arguments in every lane of the group): it tries proposals j0 .. j0 + PAR - 1
-// at once, and with TERMS = 2 or 4 the four log-factorial differences of a
-// proposal's ratio are spread over TERMS lanes (lane t forms differences t,
-// t + TERMS, ...) and summed in the sequential order.  The lowest accepted proposal wins, so the variate is
-// the one the sequential loop returns.  Used where a variate's latency, not
-// the lanes' throughput, bounds a kernel.
-template <int PAR, int TERMS, class Ratio>
-__device__ __forceinline__ uint64_t rou_sample(const Stream &s, double a, double h, uint64_t upper,
-                                               const Ratio &ratio)
+// Proposal j of a variate: accepted or not, and its X.
+template <class Ratio, class Quick>
+__device__ __forceinline__ bool rou_try(const Stream &s, uint32_t j, double a, double h, uint64_t upper,
+                                        const Ratio &ratio, const Quick &quick, uint64_t &X)
 {
-    static_assert(PAR == 1 || PAR == 2 || PAR == 4 || PAR == 8, "1, 2, 4 or 8 proposals at once");
-    static_assert(TERMS == 1 || TERMS == 2 || TERMS == 4, "ratio in one, two or four lanes");
-    constexpr uint32_t GL = PAR * TERMS;     // lanes per variate
-    const double upper_excl = (double)upper + 1.0;
+    const U4 w = s.block(j);
+    const double U = unit_of(((uint64_t)w.y << 32) | w.x);
+    const double V = unit_of(((uint64_t)w.w << 32) | w.z);
+    const double t = a + h * (V - 0.5) / U;
+    if (!(t >= 0.0 && t < (double)upper + 1.0)) return false;
+    X = (uint64_t)floor(t);
+    if (X > upper) return false;           // upper + 1 rounds in binary64 above 2^53
+    const int dec = quick.decide((int64_t)(X - ratio.M), U);
+    return __builtin_expect(dec < 0, 0) ? rou_accept(ratio, X, U) : dec != 0;
+}
+
+// Aligned groups of PAR lanes: the lowest lane of the caller's group with
+// `acc` set decides; its X to the whole group.  False when no lane has it.
+template <int PAR>
+__device__ __forceinline__ bool group_first(bool acc, uint64_t &X)
+{
     const uint32_t lane = __lane_id();
-    const uint32_t q = (lane & (GL - 1)) / TERMS;
-    const uint32_t tq = lane & (TERMS - 1);
+    const uint32_t base = lane & ~(uint32_t)(PAR - 1);
+    const uint32_t won = (uint32_t)(__ballot(acc) >> base) & (uint32_t)((1ull << PAR) - 1);
+    if (!won) return false;
+    const int src = (int)(base + __builtin_ctz(won));
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)X, src);
+    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(X >> 32), src);
+    X = ((uint64_t)hi << 32) | lo;
+    return true;
+}
+
+// PAR = 1: one proposal at a time.  Otherwise an aligned group of PAR lanes
+// works on one variate (the same arguments in every lane of the group) and
+// tries proposals j0 .. j0 + PAR - 1 at once; the lowest accepted one wins,
+// so the variate is the one the sequential loop returns.  Used where a
+// variate's latency, not the lanes' throughput, bounds a kernel.
+template <int PAR, class Ratio, class Quick>
+__device__ __forceinline__ uint64_t rou_sample(const Stream &s, double a, double h, uint64_t upper,
+                                               const Ratio &ratio, const Quick &quick)
+{
+    static_assert(PAR >= 1 && PAR <= 16 && (PAR & (PAR - 1)) == 0, "1, 2, 4, 8 or 16 proposals at once");
+    const uint32_t q = __lane_id() & (PAR - 1);
     for (uint32_t j0 = 0;; j0 += PAR) {
-        const U4 w = s.block(j0 + q);
-        const double U = unit_of(((uint64_t)w.y << 32) | w.x);
-        const double V = unit_of(((uint64_t)w.w << 32) | w.z);
-        const double t = a + h * (V - 0.5) / U;
-        bool acc = false;
         uint64_t X = 0;
-        if (t >= 0.0 && t < upper_excl) {
-            X = (uint64_t)floor(t);
-            if (X <= upper) {           // upper + 1 rounds in binary64 above 2^53
-                double T;
-                if (TERMS == 1) {
-                    T = ratio(X);
-                } else if (TERMS == 2) {
-                    const double da = ratio.term(tq, X), db = ratio.term(tq + 2, X);
-                    T = ratio.combine(group_bcast<2, 0>(da), group_bcast<2, 1>(da), group_bcast<2, 0>(db),
-                                      group_bcast<2, 1>(db), X);
-                } else {
-                    const double d = ratio.term(tq, X);
-                    T = ratio.combine(group_bcast<4, 0>(d), group_bcast<4, 1>(d), group_bcast<4, 2>(d),
-                                      group_bcast<4, 3>(d), X);
-                }
-                if (U * (4.0 - U) - 3.0 <= T) acc = true;
-                else if (U * (U - T) >= 1.0) acc = false;
-                else acc = 2.0 * log_f64(U) <= T;
-            }
-        }
-        if (GL == 1) {
+        const bool acc = rou_try(s, j0 + q, a, h, upper, ratio, quick, X);
+        if (PAR == 1) {
             if (acc) return X;
-        } else {
-            const uint32_t base = lane & ~(GL - 1);
-            const uint32_t won = (uint32_t)(__ballot(acc) >> base) & (uint32_t)((1ull << GL) - 1);
-            if (won) {
-                const int src = (int)(base + __builtin_ctz(won));
-                const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)X, src);
-                const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(X >> 32), src);
-                return ((uint64_t)hi << 32) | lo;
-            }
+        } else if (group_first<PAR>(acc, X)) {
+            return X;
         }
     }
+}
+
+// The quick test's arguments of HYP(N, K, k) and BIN(N, p).
+__device__ __forceinline__ RouQuick<4> quick_of(const HypRatio &r)
+{
+    const double y1 = (double)r.M + 0.5, y2 = (double)(r.k - r.M) + 0.5, y3 = (double)(r.K - r.M) + 0.5;
+    const double y4 = (double)(r.N - r.K - r.k + r.M) + 0.5;
+    RouQuick<4> q;
+    const double den = y2 * y3;
+    q.init({y1, y2, y3, y4}, y1 * y4 - den, den);
+    return q;
+}
+__device__ __forceinline__ RouQuick<2> quick_of(const BinRatio &r)
+{
+    const double y1 = (double)r.M + 0.5, y2 = (double)(r.N - r.M) + 0.5;
+    RouQuick<2> q;
+    const double den = y2 * r.p;
+    q.init({y1, y2}, y1 * (1.0 - r.p) - den, den);
+    return q;
 }
 
 // Hypergeometric: how many of k draws without replacement from N items land
 // among K marked ones (the sample size of a sub-universe, Sec. 2.2).
-template <int PAR = 1, int TERMS = 1>
+template <int PAR = 1>
 __device__ __forceinline__ uint64_t hyp(const Stream &s, uint64_t N, uint64_t K, uint64_t k)
 {
     // symmetries: complement the draws, complement the marked set, swap roles
@@ -454,8 +548,8 @@ __device__ __forceinline__ uint64_t hyp(const Stream &s, uint64_t N, uint64_t K,
         const double c = sqrt(var + 0.5);
         const double h = kRouD1 * c + kRouD2;
         const double a = mu + 0.5;
-        HypRatio r{N, hi, lo, muldiv_floor(lo + 1, hi + 1, N + 2)};
-        x = rou_sample<PAR, TERMS>(s, a, h, lo, r);
+        const HypRatio r{N, hi, lo, muldiv_floor(lo + 1, hi + 1, N + 2)};
+        x = rou_sample<PAR>(s, a, h, lo, r, quick_of(r));
     }
     if (c2) x = k1 - x;
     if (c1) x = K - x;
@@ -467,23 +561,27 @@ __device__ __forceinline__ uint64_t hyp(const Stream &s, uint64_t N, uint64_t K,
 // do not wait for each other's rejection loops.  Identical draws and result.
 struct HypRun {
     Stream s;
-    uint64_t N, K, k1, hi, lo, M, x;
-    double a, h, upper_excl;
+    HypRatio r;           // r.K marked items, r.k draws, after the symmetries
+    RouQuick<4> quick;
+    uint64_t K, k1, x;
+    double a, h;
     uint32_t j;
     bool c1, c2, done;
 
-    __device__ __forceinline__ void init(const Stream &st, uint64_t N_, uint64_t K_, uint64_t k)
+    __device__ __forceinline__ void init(const Stream &st, uint64_t N, uint64_t K_, uint64_t k)
     {
         s = st;
-        N = N_;
         K = K_;
         k1 = k;
         uint64_t K1 = K_;
         c1 = c2 = false;
         if (k1 > N - k1) { k1 = N - k1; c1 = true; }
         if (K1 > N - K1) { K1 = N - K1; c2 = true; }
-        lo = k1 < K1 ? k1 : K1;
-        hi = k1 < K1 ? K1 : k1;
+        const uint64_t lo = k1 < K1 ? k1 : K1;
+        const uint64_t hi = k1 < K1 ? K1 : k1;
+        r.N = N;
+        r.K = hi;
+        r.k = lo;
         j = 0;
         done = true;
         if (lo == 0) {
@@ -501,67 +599,64 @@ struct HypRun {
             const double c = sqrt(var + 0.5);
             h = kRouD1 * c + kRouD2;
             a = mu + 0.5;
-            M = muldiv_floor(lo + 1, hi + 1, N + 2);
-            upper_excl = (double)lo + 1.0;
+            r.M = muldiv_floor(lo + 1, hi + 1, N + 2);
+            quick = quick_of(r);
             done = false;
         }
     }
 
-    // one proposal; true once the variate is known.  TERMS = 2 or 4: the
-    // aligned group of TERMS lanes holding the same state forms the ratio's
-    // four differences together (same value in every lane of the group).
-    template <int TERMS = 1>
+    // one trip of proposals; true once the variate is known.  PAR > 1: the
+    // aligned group of PAR lanes holding the same state tries PAR proposals
+    // at once (the lowest accepted one is the sequential walk's).
+    template <int PAR = 1>
     __device__ __forceinline__ bool step()
     {
         if (done) return true;
-        const U4 w = s.block(j++);
-        const double U = unit_of(((uint64_t)w.y << 32) | w.x);
-        const double V = unit_of(((uint64_t)w.w << 32) | w.z);
-        const double t = a + h * (V - 0.5) / U;
-        if (!(t >= 0.0) || t >= upper_excl) return false;
-        const uint64_t X = (uint64_t)floor(t);
-        if (X > lo) return false;
-        const HypRatio ratio{N, hi, lo, M};
-        double T;
-        if (TERMS == 1) {
-            T = ratio(X);
-        } else if (TERMS == 2) {
-            const uint32_t tq = __lane_id() & 1;
-            const double da = ratio.term(tq, X), db = ratio.term(tq + 2, X);
-            T = ratio.combine(group_bcast<2, 0>(da), group_bcast<2, 1>(da), group_bcast<2, 0>(db),
-                              group_bcast<2, 1>(db), X);
-        } else {
-            const double d = ratio.term(__lane_id() & 3, X);
-            T = ratio.combine(group_bcast<4, 0>(d), group_bcast<4, 1>(d), group_bcast<4, 2>(d),
-                              group_bcast<4, 3>(d), X);
-        }
-        bool acc = false;
-        if (U * (4.0 - U) - 3.0 <= T) acc = true;
-        else if (U * (U - T) >= 1.0) acc = false;
-        else acc = 2.0 * log_f64(U) <= T;
-        if (acc) { x = X; done = true; }
+        uint64_t X = 0;
+        const bool acc = rou_try(s, j + (__lane_id() & (PAR - 1)), a, h, r.k, r, quick, X);
+        j += PAR;
+        if (PAR == 1 ? acc : group_first<PAR>(acc, X)) { x = X; done = true; }
         return done;
     }
 
     __device__ __forceinline__ uint64_t result() const
     {
-        uint64_t r = x;
-        if (c2) r = k1 - r;
-        if (c1) r = K - r;
-        return r;
+        uint64_t y = x;
+        if (c2) y = k1 - y;
+        if (c1) y = K - y;
+        return y;
     }
 };
 
+// Waiting time of Bernoulli(1/2) trials, floor(log U / log(1/2)): the
+// exponent of U, unless U is within 2^-20 of a power of two, where the
+// rounding of the quotient decides.
+__device__ __forceinline__ uint64_t half_gap(double U)
+{
+    const uint32_t hi = (uint32_t)((uint64_t)__double_as_longlong(U) >> 32);
+    const uint32_t top = hi & 0xFFFFFu;
+    if (top == 0 || top == 0xFFFFFu) return (uint64_t)floor(log_f64(U) / log1p_f64(-0.5));
+    return 1022u - (hi >> 20);
+}
+
 // Binomial(N, p): a G(n,p) chunk's edge count (Sec. 4.3).  Small means by
 // geometric waiting times floor(log U / log(1-p)); otherwise ratio of uniforms.
-template <int PAR = 1, int TERMS = 1>
+template <int PAR = 1>
 __device__ __forceinline__ uint64_t bin_core(const Stream &s, uint64_t N, double p)
 {
     const double Nd = (double)N;
     if (Nd * p < 16.0) {
-        const double L = log1p_f64(-p);
         Draws64 d(s);
         uint64_t X = 0, pos = 0;
+        if (p == 0.5) {
+            for (;;) {
+                const uint64_t g = half_gap(unit_of(d.get()));
+                if (g >= N - pos) return X;
+                pos += g + 1;
+                ++X;
+            }
+        }
+        const double L = log1p_f64(-p);
         for (;;) {
             const double U = unit_of(d.get());
             const double g = floor(log_f64(U) / L);
@@ -576,17 +671,17 @@ __device__ __forceinline__ uint64_t bin_core(const Stream &s, uint64_t N, double
     const double c = sqrt(var + 0.5);
     const double h = kRouD1 * c + kRouD2;
     const double a = mu + 0.5;
-    BinRatio r{N, (uint64_t)floor((Nd + 1.0) * p), log_f64(p) - log1p_f64(-p)};
-    return rou_sample<PAR, TERMS>(s, a, h, N, r);
+    const BinRatio r{N, (uint64_t)floor((Nd + 1.0) * p), p};
+    return rou_sample<PAR>(s, a, h, N, r, quick_of(r));
 }
 
-template <int PAR = 1, int TERMS = 1>
+template <int PAR = 1>
 __device__ __forceinline__ uint64_t binom(const Stream &s, uint64_t N, double p)
 {
     if (N == 0 || p <= 0.0) return 0;
     if (p >= 1.0) return N;
-    if (p > 0.5) return N - bin_core<PAR, TERMS>(s, N, 1.0 - p);
-    return bin_core<PAR, TERMS>(s, N, p);
+    if (p > 0.5) return N - bin_core<PAR>(s, N, 1.0 - p);
+    return bin_core<PAR>(s, N, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -610,9 +705,50 @@ __host__ __device__ __forceinline__ uint64_t section_bound(const Inst &I, uint64
     return (i * I.n) / I.P;
 }
 
+// floor(x / d) where the quotient is below 2^50, from rcp = 1 / d in
+// binary64: the estimate is off by less than one, so one step corrects it
+// (a 64-bit integer division takes about 130 instructions here).
+__device__ __forceinline__ uint64_t div_est(uint64_t x, uint64_t d, double rcp)
+{
+    uint64_t q = (uint64_t)((double)x * rcp);
+    const int64_t r = (int64_t)(x - q * d);
+    if (r < 0) --q;
+    else if ((uint64_t)r >= d) ++q;
+    return q;
+}
+
+// section_bound(I, i) on the device: floor(i n / P) = i floor(n / P) +
+// floor(i (n mod P) / P).  floor(n / P) is the floor of the binary64
+// quotient, because n <= 2^32 keeps a fraction 2^-32 away from an integer.
+struct Sections {
+    uint64_t q, r, P;
+    double rcp;
+    __device__ __forceinline__ explicit Sections(const Inst &I) : P(I.P), rcp(1.0 / (double)I.P)
+    {
+        q = (uint64_t)((double)I.n / (double)I.P);
+        r = I.n - q * P;
+    }
+    __device__ __forceinline__ uint64_t operator()(uint64_t i) const
+    {
+        return i * q + div_est(i * r, P, rcp);
+    }
+};
+
 __host__ __device__ __forceinline__ uint64_t uord(uint64_t P, uint64_t i)
 {
     return i * P - i * (i - 1) / 2;   // ordinal of diagonal chunk (i, i)
+}
+
+// Row of the undirected chunk matrix that ordinal c lies in: the largest i
+// with uord(i) <= c.  The binary64 root is within one of it (c < 2^30).
+__device__ __forceinline__ uint64_t urow(uint64_t P, uint64_t c)
+{
+    const double b = (double)(2 * P + 1);
+    int64_t i = (int64_t)((b - sqrt(b * b - 8.0 * (double)c)) * 0.5);
+    i = i < 0 ? 0 : i >= (int64_t)P ? (int64_t)P - 1 : i;
+    while (uord(P, (uint64_t)i) > c) --i;
+    while (i + 1 < (int64_t)P && uord(P, (uint64_t)i + 1) <= c) ++i;
+    return (uint64_t)i;
 }
 
 struct Chunk {
@@ -620,6 +756,7 @@ struct Chunk {
     uint64_t row0;    // directed: first row
     uint64_t a, h;    // undirected: row section start / size
     uint64_t b, w;    // undirected: column section start / size
+    uint32_t ci, cj;  // row chunk; undirected: cell of the chunk matrix
     uint32_t diag;    // undirected triangle chunk
 };
 
@@ -640,20 +777,19 @@ __device__ __forceinline__ Chunk chunk_geometry(const Inst &I, uint64_t c)
 {
     Chunk g;
     g.diag = 0; g.a = g.h = g.b = g.w = 0; g.row0 = 0;
+    const Sections at(I);
     if (I.directed) {
-        g.row0 = section_bound(I, c);
-        g.N = (section_bound(I, c + 1) - g.row0) * (I.n - 1);
+        g.ci = (uint32_t)c;
+        g.cj = 0;
+        g.row0 = at(c);
+        g.N = (at(c + 1) - g.row0) * (I.n - 1);
         return g;
     }
-    // row of the chunk matrix: largest i with uord(i) <= c
-    uint64_t lo = 0, hi = I.P;
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (uord(I.P, mid) <= c) lo = mid; else hi = mid;
-    }
-    const uint64_t ci = lo, cj = lo + (c - uord(I.P, lo));
-    g.a = section_bound(I, ci); g.h = section_bound(I, ci + 1) - g.a;
-    g.b = section_bound(I, cj); g.w = section_bound(I, cj + 1) - g.b;
+    const uint64_t ci = urow(I.P, c), cj = ci + (c - uord(I.P, ci));
+    g.ci = (uint32_t)ci;
+    g.cj = (uint32_t)cj;
+    g.a = at(ci); g.h = at(ci + 1) - g.a;
+    g.b = at(cj); g.w = at(cj + 1) - g.b;
     g.diag = ci == cj;
     g.N = g.diag ? g.h * (g.h - (g.h > 0)) / 2 : g.h * g.w;
     return g;
@@ -678,82 +814,79 @@ __device__ __forceinline__ uint32_t unit_depth(uint64_t T, uint32_t ulog)
 // paper; Sec. 2.2, 4.1, 4.2).  The split of a range [lo, hi) of chunks or
 // sections is at lo + ceil((hi - lo)/2).
 // ---------------------------------------------------------------------------
-template <int PAR = 1, int TERMS = 1>
-__device__ __forceinline__ uint64_t dtree_count(const Inst &I, uint64_t c)
-{
-    uint64_t k = I.m, lo = 0, hi = I.P;
-    uint32_t heap = 1;
-    const uint64_t w = I.n - 1;
-    while (hi - lo > 1) {
-        const uint64_t mid = lo + (hi - lo + 1) / 2;
-        const uint64_t blo = section_bound(I, lo);
-        const uint64_t Nn = (section_bound(I, hi) - blo) * w;
-        const uint64_t Nl = (section_bound(I, mid) - blo) * w;
-        const uint64_t X = hyp<PAR, TERMS>(make_stream(I.seed, heap, 0, TAG_DTREE), Nn, Nl, k);
-        if (c < mid) { hi = mid; k = X; heap = 2 * heap; }
-        else         { lo = mid; k = k - X; heap = 2 * heap + 1; }
-    }
-    return k;
-}
+__device__ __forceinline__ uint64_t tri_slots(uint64_t A) { return A * (A - (A > 0)) / 2; }
 
-__device__ __forceinline__ uint64_t tri_slots(const Inst &I, uint64_t a, uint64_t b)
+// A node splits its count over its parts one conditional variate at a time:
+// part r gets HYP(slots left, slots of part r, count left), until the part
+// that holds the chunk, and the last part gets the rest.  Directed: two
+// halves of the row chunks [a, b).  Undirected: a triangle [a, b) has the
+// parts T1 = [a, l), R = [a, l) x [l, b), T2 = [l, b); a rectangle
+// [a, b) x [c, d) its four quadrants, or two halves where a side has one section.
+// One loop over all levels and parts, so that the variate's code (the path's
+// whole time is its latency, about 1.7 us per variate) appears once: 37 KB for
+// the count kernel, which fits the instruction cache, where a copy per kind of
+// split and a division per section bound took 146 KB.
+template <int PAR = 1>
+__device__ __forceinline__ uint64_t path_count(const Inst &I, uint64_t ci, uint64_t cj)
 {
-    const uint64_t A = section_bound(I, b) - section_bound(I, a);
-    return A * (A - (A > 0)) / 2;
-}
-
-__device__ __forceinline__ uint64_t rect_slots(const Inst &I, uint64_t a, uint64_t b, uint64_t c, uint64_t d)
-{
-    return (section_bound(I, b) - section_bound(I, a)) * (section_bound(I, d) - section_bound(I, c));
-}
-
-template <int PAR = 1, int TERMS = 1>
-__device__ __forceinline__ uint64_t utree_count(const Inst &I, uint64_t ci, uint64_t cj)
-{
-    uint64_t k = I.m, a = 0, b = I.P, cc = 0, d = 0;
+    const Sections at(I);
+    // rows [a, b) start and end at slots' rows A, B; columns [c, d) at C, D
+    uint64_t k = I.m, a = 0, b = I.P, c = 0, d = 0, A = 0, B = I.n, C = 0, D = 0;
     uint32_t code = 1;
-    bool tri = true;
+    const bool dir = I.directed != 0;
+    bool tri = !dir;
     for (;;) {
+        const uint64_t l = a + (b - a + 1) / 2, q = c + (d - c + 1) / 2;
+        const bool rows = b - a > 1, cols = !dir && !tri && d - c > 1;
+        if (!rows && !cols) return k;
+        // the node's parts: slots of the first three, their number, the chunk's
+        uint64_t Lb = 0, Qb = 0, left, n0, n1 = 0, n2 = 0;
+        uint32_t parts = 2, mine;
+        if (rows) Lb = at(l);
+        if (cols) Qb = at(q);
         if (tri) {
-            if (b - a == 1) return k;
-            const uint64_t l = a + (b - a + 1) / 2;
-            const uint64_t Nn = tri_slots(I, a, b), N1 = tri_slots(I, a, l), NR = rect_slots(I, a, l, l, b);
-            const uint64_t X0 = hyp<PAR, TERMS>(make_stream(I.seed, code, 0, TAG_UTREE), Nn, N1, k);
-            if (cj < l) { b = l; k = X0; code = 4 * code; continue; }
-            const uint64_t X1 = hyp<PAR, TERMS>(make_stream(I.seed, code, 1, TAG_UTREE), Nn - N1, NR, k - X0);
-            if (ci < l) { tri = false; cc = l; d = b; b = l; k = X1; code = 4 * code + 1; continue; }
-            a = l; k = k - X0 - X1; code = 4 * code + 2;
-            continue;
+            left = tri_slots(B - A);
+            n0 = tri_slots(Lb - A);
+            n1 = (Lb - A) * (B - Lb);
+            parts = 3;
+            mine = cj < l ? 0 : ci < l ? 1 : 2;
+        } else {
+            const uint64_t w = dir ? I.n - 1 : D - C;        // slots of a row
+            left = (B - A) * w;
+            if (rows && cols) {
+                n0 = (Lb - A) * (Qb - C);
+                n1 = (Lb - A) * (D - Qb);
+                n2 = (B - Lb) * (Qb - C);
+                parts = 4;
+                mine = (ci >= l ? 2u : 0u) + (cj >= q ? 1u : 0u);
+            } else if (rows) {
+                n0 = (Lb - A) * w;
+                mine = ci < l ? 0 : 1;
+            } else {
+                n0 = (B - A) * (Qb - C);
+                mine = cj < q ? 0 : 1;
+            }
         }
-        if (b - a == 1 && d - cc == 1) return k;
-        const uint64_t Nn = rect_slots(I, a, b, cc, d);
-        if (d - cc == 1) {
-            const uint64_t l = a + (b - a + 1) / 2;
-            const uint64_t X = hyp<PAR, TERMS>(make_stream(I.seed, code, 0, TAG_UTREE), Nn, rect_slots(I, a, l, cc, d), k);
-            if (ci < l) { b = l; k = X; code = 4 * code; }
-            else        { a = l; k = k - X; code = 4 * code + 1; }
-            continue;
+        for (uint32_t r = 0; r + 1 < parts; ++r) {
+            const uint64_t nr = r == 0 ? n0 : r == 1 ? n1 : n2;
+            const uint64_t X = hyp<PAR>(make_stream(I.seed, code, dir ? 0 : r, dir ? TAG_DTREE : TAG_UTREE), left,
+                                        nr, k);
+            if (r == mine) { k = X; break; }
+            left -= nr;
+            k -= X;
         }
-        if (b - a == 1) {
-            const uint64_t q = cc + (d - cc + 1) / 2;
-            const uint64_t X = hyp<PAR, TERMS>(make_stream(I.seed, code, 0, TAG_UTREE), Nn, rect_slots(I, a, b, cc, q), k);
-            if (cj < q) { d = q; k = X; code = 4 * code; }
-            else        { cc = q; k = k - X; code = 4 * code + 1; }
-            continue;
+        code = (dir ? 2 : 4) * code + mine;
+        if (tri && mine == 1) {
+            tri = false;
+            c = l; C = Lb; d = b; D = B;
+            b = l; B = Lb;
+        } else {
+            const bool low = tri ? mine == 0 : parts == 4 ? mine < 2 : mine == 0;
+            if (rows) { if (low) { b = l; B = Lb; } else { a = l; A = Lb; } }
+            if (cols) {
+                if (parts == 4 ? (mine & 1) != 0 : mine != 0) { c = q; C = Qb; } else { d = q; D = Qb; }
+            }
         }
-        const uint64_t l = a + (b - a + 1) / 2, q = cc + (d - cc + 1) / 2;
-        const uint64_t N00 = rect_slots(I, a, l, cc, q), N01 = rect_slots(I, a, l, q, d);
-        const uint64_t N10 = rect_slots(I, l, b, cc, q);
-        const uint32_t quad = (ci >= l ? 2u : 0u) + (cj >= q ? 1u : 0u);
-        const uint64_t X00 = hyp<PAR, TERMS>(make_stream(I.seed, code, 0, TAG_UTREE), Nn, N00, k);
-        uint64_t X01 = 0, X10 = 0;
-        if (quad >= 1) X01 = hyp<PAR, TERMS>(make_stream(I.seed, code, 1, TAG_UTREE), Nn - N00, N01, k - X00);
-        if (quad >= 2) X10 = hyp<PAR, TERMS>(make_stream(I.seed, code, 2, TAG_UTREE), Nn - N00 - N01, N10, k - X00 - X01);
-        const uint64_t kk = quad == 0 ? X00 : quad == 1 ? X01 : quad == 2 ? X10 : k - X00 - X01 - X10;
-        if (quad < 2) b = l; else a = l;
-        if (quad & 1) cc = q; else d = q;
-        k = kk;
-        code = 4 * code + quad;
     }
 }
 

@@ -93,21 +93,19 @@ __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v)
 }
 
 // ---------------------------------------------------------------------------
-// count: a group of PAR * TERMS lanes per chunk, a workgroup per 64 chunks.
+// count: a group of PAR lanes per chunk, a workgroup per 64 chunks.
 // The count of a chunk is a root path of dependent variates (Sec. 4.1, 4.2)
 // or one binomial (Sec. 4.3), so the kernel's time is the latency of that
 // chain: the lanes of a chunk try PAR ratio-of-uniforms proposals of each
-// variate at once and, with TERMS = 4, form each proposal's log-factorial
-// differences in four lanes (the first accepted proposal in proposal order
+// variate at once (the first accepted proposal in proposal order
 // wins, so the counts are those of the one-proposal loop).  Writes the
 // chunk's edge count, tile count and planner-unit count, and the workgroup's
 // three sums to bsum (the first phase of the offset scan).
 // ---------------------------------------------------------------------------
-template <int PAR, int TERMS>
-__global__ __launch_bounds__(64 * PAR * TERMS) void count_kernel(Job job)
+template <int PAR>
+__global__ __launch_bounds__(64 * PAR) void count_kernel(Job job)
 {
-    constexpr int kCountPar = PAR, kCountTerms = TERMS;
-    constexpr int kCountLanes = PAR * TERMS, kCountWaves = PAR * TERMS;   // 64 chunks per workgroup
+    constexpr int kCountLanes = PAR, kCountWaves = PAR;   // 64 chunks per workgroup
     __shared__ uint64_t s_sum[kCountWaves][3];
     const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t g = (uint64_t)blockIdx.x * 64 + threadIdx.x / kCountLanes;
@@ -119,16 +117,9 @@ __global__ __launch_bounds__(64 * PAR * TERMS) void count_kernel(Job job)
         const uint64_t c = chunk_ordinal(I, g - I.chunk_base);
         const Chunk ch = chunk_geometry(I, c);
         if (I.model == 1) {
-            cnt = binom<kCountPar, kCountTerms>(make_stream(I.seed, (uint32_t)c, 0, TAG_CBIN), ch.N, I.p);
-        } else if (I.directed) {
-            cnt = dtree_count<kCountPar, kCountTerms>(I, c);
+            cnt = binom<PAR>(make_stream(I.seed, (uint32_t)c, 0, TAG_CBIN), ch.N, I.p);
         } else {
-            uint64_t lo = 0, hi = I.P;
-            while (hi - lo > 1) {
-                const uint64_t mid = (lo + hi) >> 1;
-                if (uord(I.P, mid) <= c) lo = mid; else hi = mid;
-            }
-            cnt = utree_count<kCountPar, kCountTerms>(I, lo, lo + (c - uord(I.P, lo)));
+            cnt = path_count<PAR>(I, ch.ci, ch.cj);
         }
         T = tiles_of(ch.N, I.s);
         Us = T ? (1ull << unit_depth(T, job.unit_log)) : 0;
@@ -265,14 +256,14 @@ __global__ __launch_bounds__(256) void inst_offsets_kernel(Job job)
 // so leaves come in tile order and each tile's output offset is a running
 // sum.  Every split is one HypRun, advanced by one proposal per loop trip;
 // pending right children wait on a small per-lane stack in LDS.  With
-// TERMS = 2 or 4 a unit belongs to a group of that many lanes, which keep
-// the same state and spread each proposal's four log-factorial differences
-// over the group (for launches with few units, where one unit's chain of
+// PAR > 1 a unit belongs to a group of that many lanes, which keep
+// the same state and try as many proposals of a variate at once (for
+// launches with few units, where one unit's chain of
 // variates, not the lanes' throughput, sets the time).
 // ---------------------------------------------------------------------------
 constexpr int kPlanStack = 8;   // > depth of a unit subtree (6 for 64 tiles)
 
-template <int TERMS>
+template <int PAR>
 __global__ __launch_bounds__(64) void plan_kernel(Job job)
 {
     __shared__ uint64_t st_k[kPlanStack][64];
@@ -282,9 +273,9 @@ __global__ __launch_bounds__(64) void plan_kernel(Job job)
     const uint64_t U = job.status[3];
     // blocked unit ranges: a lane group's next unit is the following one, so
     // the chunk index only moves forward (one binary search per group)
-    const uint64_t TL = (uint64_t)gridDim.x * (64 / TERMS);
+    const uint64_t TL = (uint64_t)gridDim.x * (64 / PAR);
     const uint64_t per = (U + TL - 1) / TL;
-    uint64_t u = ((uint64_t)blockIdx.x * 64 + lane) / TERMS * per;
+    uint64_t u = ((uint64_t)blockIdx.x * 64 + lane) / PAR * per;
     const uint64_t uend = u + per < U ? u + per : U;
     bool active = u < uend;
     uint64_t g = 0;
@@ -352,7 +343,7 @@ __global__ __launch_bounds__(64) void plan_kernel(Job job)
                     running = true;
                 }
             }
-            if (active && running && hr.template step<TERMS>()) {
+            if (active && running && hr.template step<PAR>()) {
                 const uint64_t X = hr.result();
                 const uint64_t mid = lo + (hi - lo + 1) / 2;
                 running = false;

@@ -177,8 +177,8 @@ kg_status ensure_init(int *dev_out)
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, queue_kernel<kCapMax>, 64, 0) != hipSuccess || nb < 1) nb = 1;
     g_queue_blocks_per_cu[dev] = nb;
     {
-        const void *fk[kCountVariants] = {(const void *)count_kernel<1, 1>, (const void *)count_kernel<1, 2>,
-                                          (const void *)count_kernel<1, 4>, (const void *)count_kernel<2, 4>};
+        const void *fk[kCountVariants] = {(const void *)count_kernel<1>, (const void *)count_kernel<2>,
+                                          (const void *)count_kernel<4>, (const void *)count_kernel<8>};
         const int threads[kCountVariants] = {64, 128, 256, 512};
         for (int v = 0; v < kCountVariants; ++v) {
             nb = 0;
@@ -399,10 +399,10 @@ void launch_count(const Job &job, uint64_t nb, int dev, hipStream_t s)
         for (int c = kCountVariants - 1; c >= 1; --c)
             if (nb <= cu * (uint64_t)g_count_blocks_per_cu[dev][c]) { v = c; break; }
     }
-    if (v == 3) hipLaunchKernelGGL((count_kernel<2, 4>), dim3((uint32_t)nb), dim3(512), 0, s, job);
-    else if (v == 2) hipLaunchKernelGGL((count_kernel<1, 4>), dim3((uint32_t)nb), dim3(256), 0, s, job);
-    else if (v == 1) hipLaunchKernelGGL((count_kernel<1, 2>), dim3((uint32_t)nb), dim3(128), 0, s, job);
-    else hipLaunchKernelGGL((count_kernel<1, 1>), dim3((uint32_t)nb), dim3(64), 0, s, job);
+    if (v == 3) hipLaunchKernelGGL(count_kernel<8>, dim3((uint32_t)nb), dim3(512), 0, s, job);
+    else if (v == 2) hipLaunchKernelGGL(count_kernel<4>, dim3((uint32_t)nb), dim3(256), 0, s, job);
+    else if (v == 1) hipLaunchKernelGGL(count_kernel<2>, dim3((uint32_t)nb), dim3(128), 0, s, job);
+    else hipLaunchKernelGGL(count_kernel<1>, dim3((uint32_t)nb), dim3(64), 0, s, job);
 }
 
 // count + scan (+ instance offsets).  `resident`: the descriptor table is
@@ -435,14 +435,15 @@ kg_status launch_generate(const Prepared &P, Job &job, int dev, hipStream_t s)
     // planner units: at most 2 per 2^unit_log tiles plus one per chunk; one lane each
     const uint64_t ub = 2 * (P.Tb >> job.unit_log) + P.G + 1;
     uint64_t pgrid = (uint64_t)(cu * opt_or(g_plan_waves, g_plan_blocks_per_cu[dev]));
-    // few units (their bound fits the resident lanes 4 or 2 times over): a
+    // few units (their bound fits the resident lanes 8, 4 or 2 times over): a
     // group of lanes per unit shortens each unit's chain of variates
-    const int terms = ub * 4 <= pgrid * 64 ? 4 : ub * 2 <= pgrid * 64 ? 2 : 1;
-    if (pgrid > (ub * terms + 63) / 64) pgrid = (ub * terms + 63) / 64;
+    const int par = ub * 8 <= pgrid * 64 ? 8 : ub * 4 <= pgrid * 64 ? 4 : ub * 2 <= pgrid * 64 ? 2 : 1;
+    if (pgrid > (ub * par + 63) / 64) pgrid = (ub * par + 63) / 64;
     {
         KernelTimer tm(KG_KERNEL_PLAN, s);
-        if (terms == 4) hipLaunchKernelGGL(plan_kernel<4>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
-        else if (terms == 2) hipLaunchKernelGGL(plan_kernel<2>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
+        if (par == 8) hipLaunchKernelGGL(plan_kernel<8>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
+        else if (par == 4) hipLaunchKernelGGL(plan_kernel<4>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
+        else if (par == 2) hipLaunchKernelGGL(plan_kernel<2>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
         else hipLaunchKernelGGL(plan_kernel<1>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
     }
     uint64_t sgrid = (uint64_t)(cu * opt_or(g_sample_waves, g_sample_blocks_per_cu[dev]));

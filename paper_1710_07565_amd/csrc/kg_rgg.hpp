@@ -80,9 +80,16 @@ __global__ __launch_bounds__(64) void rgg_split_kernel(RggJob J, uint32_t l)
     const uint64_t z = (uint64_t)blockIdx.x * 64 + threadIdx.x;
     if (z >= (1ull << (2 * l))) return;
     const uint64_t k = J.tree[rgg_level_base(l) + z];
-    const uint64_t lower = binom(make_stream(J.seed, (uint32_t)z, 3 * l + 0, TAG_RTREE), k, 0.5);
-    const uint64_t ll = binom(make_stream(J.seed, (uint32_t)z, 3 * l + 1, TAG_RTREE), lower, 0.5);
-    const uint64_t ul = binom(make_stream(J.seed, (uint32_t)z, 3 * l + 2, TAG_RTREE), k - lower, 0.5);
+    // lower half, its left quadrant, the upper half's left quadrant (one copy
+    // of the variate's code)
+    uint64_t v[3];
+#pragma unroll 1
+    for (uint32_t i = 0; i < 3; ++i) {
+        const uint64_t of = i == 0 ? k : i == 1 ? v[0] : k - v[0];
+        const uint64_t x = binom(make_stream(J.seed, (uint32_t)z, 3 * l + i, TAG_RTREE), of, 0.5);
+        if (i == 0) v[0] = x; else if (i == 1) v[1] = x; else v[2] = x;
+    }
+    const uint64_t lower = v[0], ll = v[1], ul = v[2];
     uint64_t *ch = J.tree + rgg_level_base(l + 1) + 4 * z;
     ch[0] = ll;
     ch[1] = lower - ll;

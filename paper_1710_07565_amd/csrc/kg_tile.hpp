@@ -161,7 +161,7 @@ struct TileWalk {
         d.pow2 = uni((dv & (dv - 1)) == 0);
         d.sh = uni(63 - __clzll(dv));
         d.rcp = unid(1.0 / (double)dv);
-        qs = uni64((1ull << s) / dv);
+        qs = uni64(div_est(1ull << s, dv, d.rcp));
         rs = uni((uint32_t)((1ull << s) - qs * dv));
         tc.st = Stream{uni((uint32_t)I.seed), uni((uint32_t)(I.seed >> 32)), c, 0, TAG_TLEAF};
     }
@@ -179,7 +179,7 @@ struct TileWalk {
         if (d.type == 2) {
             d.lbase = lstart;
         } else {
-            const uint64_t q = lstart / d.dv;
+            const uint64_t q = div_est(lstart, d.dv, d.rcp);
             d.c0 = uni((uint32_t)(lstart - q * d.dv));
             d.r0 = uni(row0 + (uint32_t)q);
         }
@@ -604,7 +604,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             const uint64_t full_S = 1ull << s;
             uint64_t lstart = (t - w.gstart) << s;
             if (d.type != 2) {
-                const uint64_t q = lstart / d.dv;
+                const uint64_t q = div_est(lstart, d.dv, d.rcp);
                 d.c0 = uni((uint32_t)(lstart - q * d.dv));
                 d.r0 = uni(w.row0 + (uint32_t)q);
             }
