@@ -22,6 +22,7 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint64_t kGrabBig = 32;       // tiles per range a workgroup takes from the shared counter ...
 constexpr uint64_t kGrabSmall = 8;      // ... and near the end of the walk
 constexpr uint64_t kTailTiles = 64;     // tiles per workgroup handed out in small ranges
+constexpr uint64_t kStaticTiles = 16;   // fewer tiles per workgroup than this are shared out in advance
 
 // Wave-uniform 64-bit load through the scalar data cache.  Only for data
 // that no lane writes while the kernel runs (sizes and offsets written by
@@ -52,57 +53,72 @@ __device__ __forceinline__ uint64_t chunk_of_tile(const Job &job, uint64_t t)
     return lo;
 }
 
-// Ranges of tiles for a persistent grid, in tile order: workgroup b takes
-// range b first, then the next one not yet handed out, from the counter
-// status[5] (cleared by the scan kernel), so a workgroup whose tiles were
-// cheap takes more and none waits on a slow tail.  Ranges of kGrabBig tiles
-// first, then, for the last kTailTiles tiles per workgroup of the grid,
-// ranges of kGrabSmall, so that the walk ends evenly and the counter, the
-// chunk search and the chunk set-up are paid once per kGrabBig tiles for
-// most of it.  Walks with fewer than 4 x kGrabBig tiles per workgroup take
-// smaller ranges (down to one tile) so that small jobs still spread over the
-// grid; when the grid holds every range, no workgroup touches the counter.
+// Ranges of tiles for a persistent grid: workgroup b takes a fixed range
+// first, then the next one not yet handed out, from the counter status[5]
+// (cleared by the scan kernel), so a workgroup whose tiles were cheap takes
+// more and none waits on a slow tail.  The counter is one address for all
+// dies: a take costs about 17 ns of everybody's time, as much as ten tiles of
+// the whole grid, so it is kept for what balancing needs.  Grids with fewer
+// than kStaticTiles tiles per workgroup take none (an equal share each; a view
+// of 16,640 tiles on 4,096 workgroups, which took four ranges each from the
+// counter: whole call 287 -> 119 us; with a limit of 32, 64 the directed
+// calls gain a few per cent and a batch of 16 uneven graphs goes from 331 to
+// 425 us); up to 4 x kGrabBig, half of the
+// share is fixed and the rest goes in ranges of kGrabSmall; beyond that the
+// first range has kGrabBig tiles, then ranges of kGrabBig, and of kGrabSmall
+// for the last kTailTiles tiles per workgroup, so that the walk ends evenly
+// while the counter, the chunk search and the chunk set-up are paid once per
+// kGrabBig tiles for most of it.
 struct TileGrab {
-    uint64_t T, head, qh, Q;   // tiles, tiles in large ranges, large ranges, all ranges
-    uint64_t big, small;       // range sizes
+    uint64_t T, fixed, head, qh, Q;   // tiles; tiles in fixed ranges; then in large ranges; large ranges, all ranges
+    uint32_t each, more;              // tiles of a fixed range; workgroups with one more
     bool first;
 
     __device__ __forceinline__ TileGrab(uint64_t tiles)
     {
         T = tiles;
-        const uint64_t W = gridDim.x;
-        const uint64_t fair = T / (4 * W);
-        small = fair >= kGrabSmall ? kGrabSmall : fair > 0 ? fair : 1;
-        big = fair >= kGrabBig ? kGrabBig : fair > small ? fair : small;
-        const uint64_t tail = W * kTailTiles;
-        head = T > tail ? T - tail : 0;
-        qh = (head + big - 1) / big;
-        Q = qh + (T - head + small - 1) / small;
+        const uint32_t W = gridDim.x;
+        more = 0;
+        each = kGrabBig;
+        uint64_t tail = (uint64_t)W * kTailTiles;
+        if (T < (uint64_t)W * 4 * kGrabBig) {
+            each = (uint32_t)T / W;
+            if (each < kStaticTiles) {
+                more = (uint32_t)T - each * W;
+            } else {
+                each /= 2;
+                tail = T;
+            }
+        }
+        fixed = (uint64_t)each * W + more;
+        const uint64_t rest = T - fixed;
+        head = rest > tail ? rest - tail : 0;
+        qh = (head + kGrabBig - 1) / kGrabBig;
+        Q = qh + (rest - head + kGrabSmall - 1) / kGrabSmall;
         first = true;
     }
 
     // the next range [t0, t1); false once every range has been handed out
     __device__ __forceinline__ bool next(const Job &job, uint64_t &t0, uint64_t &t1)
     {
-        const uint64_t W = gridDim.x;
-        uint64_t q;
         if (first) {
-            q = blockIdx.x;
             first = false;
-        } else if (Q <= W) {
-            return false;
-        } else {
-            uint64_t b = 0;
-            if (threadIdx.x == 0) b = atomicAdd((unsigned long long *)(job.status + 5), 1ull);
-            q = W + uni64(b);
+            const uint32_t b = blockIdx.x;
+            t0 = (uint64_t)each * b + (b < more ? b : more);
+            t1 = t0 + each + (b < more ? 1 : 0);
+            return t0 < t1;
         }
+        if (Q == 0) return false;
+        uint64_t q = 0;
+        if (threadIdx.x == 0) q = atomicAdd((unsigned long long *)(job.status + 5), 1ull);
+        q = uni64(q);
         if (q >= Q) return false;
         if (q < qh) {
-            t0 = q * big;
-            t1 = t0 + big < head ? t0 + big : head;
+            t0 = fixed + q * kGrabBig;
+            t1 = t0 + kGrabBig < fixed + head ? t0 + kGrabBig : fixed + head;
         } else {
-            t0 = head + (q - qh) * small;
-            t1 = t0 + small < T ? t0 + small : T;
+            t0 = fixed + head + (q - qh) * kGrabSmall;
+            t1 = t0 + kGrabSmall < T ? t0 + kGrabSmall : T;
         }
         return true;
     }
