@@ -414,11 +414,10 @@ struct Decoder {
     uint32_t sh;
     uint32_t wide;      // some dividend c0 + x of the tile needs 33 bits
     uint32_t dv;        // directed: n - 1; rectangle: section width
-    uint32_t r0, c0;    // row of the tile start and its offset in that row
-    uint32_t b;         // rectangle: first column
-    uint32_t a, h;      // triangle: section start and size
+    uint32_t r0, c0;    // row of the tile start and its offset in that row; triangle: section start
+    uint32_t b;         // rectangle: first column; triangle: section size
     double rcp;         // 1 / dv
-    uint64_t Ttri, lbase;  // triangle: its slots, tile start
+    uint64_t lbase;     // triangle: tile start
 
     __device__ __forceinline__ uint32_t divmod(uint32_t x, uint32_t &rem) const
     {
@@ -450,8 +449,9 @@ struct Decoder {
             const uint32_t u = r0 + q;
             return type == 0 ? make_uint2(u, r + (r >= u)) : make_uint2(u, b + r);
         }
+        const uint64_t h = b;
         const uint64_t l = lbase + x;
-        const uint64_t lr = Ttri - 1 - l;
+        const uint64_t lr = h * (h - (h > 0)) / 2 - 1 - l;
         // largest q with q(q+1)/2 <= lr: the binary64 estimate is within one
         // of it (lr < 2^63: the rounding of lr moves the square root by far
         // less than one), so each correction runs at most twice
@@ -460,7 +460,7 @@ struct Decoder {
         for (int i = 0; i < 2 && (q + 1) * (q + 2) / 2 <= lr; ++i) ++q;
         const uint64_t r = h - 2 - q;
         const uint64_t st = r * h - r * (r + 1) / 2;
-        return make_uint2((uint32_t)(a + r), (uint32_t)(a + r + 1 + (l - st)));
+        return make_uint2((uint32_t)(r0 + r), (uint32_t)(r0 + r + 1 + (l - st)));
     }
 };
 

@@ -244,7 +244,6 @@ __global__ __launch_bounds__(64) void skip_write_kernel(Job job)
 {
     __shared__ __attribute__((aligned(16))) uint32_t s_key[kSkipKeys];
     if (ld_uni(job.status + 1)) return;
-    const uint64_t T = ld_uni(job.status + 2);
     const double p = job.one.p;
     const bool flip = p > 0.5;
     const bool all = p >= 1.0;
@@ -252,7 +251,7 @@ __global__ __launch_bounds__(64) void skip_write_kernel(Job job)
     TileWalk w;
     TileCtx &tc = w.tc;
     tc.edges = job.edges;
-    TileGrab grab(T);
+    TileGrab grab;
     uint64_t t, t1;
     while (grab.next(job, t, t1)) {
         uint64_t g = chunk_of_tile(job, t);
@@ -284,7 +283,6 @@ __global__ __launch_bounds__(64) void skip_write_kernel(Job job)
 // with more events than its row holds is generated again by the write path.
 __global__ __launch_bounds__(64) void skip_gen_kernel(Job job, uint32_t *slab, uint32_t cap)
 {
-    const uint64_t T = ld_uni(job.status + 2);
     const double p = job.one.p;
     const bool flip = p > 0.5;
     const bool all = p >= 1.0;
@@ -292,7 +290,7 @@ __global__ __launch_bounds__(64) void skip_gen_kernel(Job job, uint32_t *slab, u
     const uint32_t lane = threadIdx.x;
     TileWalk w;
     TileCtx &tc = w.tc;
-    TileGrab grab(T);
+    TileGrab grab;
     uint64_t t, t1;
     while (grab.next(job, t, t1)) {
         uint64_t g = chunk_of_tile(job, t);
@@ -343,7 +341,6 @@ __global__ __launch_bounds__(64) void skip_emit_kernel(Job job, const uint32_t *
 {
     __shared__ __attribute__((aligned(16))) uint32_t s_key[kSkipKeys];
     if (ld_uni(job.status + 1)) return;
-    const uint64_t T = ld_uni(job.status + 2);
     const double p = job.one.p;
     const bool flip = p > 0.5;
     const bool all = p >= 1.0;
@@ -352,7 +349,7 @@ __global__ __launch_bounds__(64) void skip_emit_kernel(Job job, const uint32_t *
     TileWalk w;
     TileCtx &tc = w.tc;
     tc.edges = job.edges;
-    TileGrab grab(T);
+    TileGrab grab;
     uint64_t t, t1;
     while (grab.next(job, t, t1)) {
         uint64_t g = chunk_of_tile(job, t);

@@ -69,17 +69,18 @@ __device__ __forceinline__ uint64_t chunk_of_tile(const Job &job, uint64_t t)
 // for the last kTailTiles tiles per workgroup, so that the walk ends evenly
 // while the counter, the chunk search and the chunk set-up are paid once per
 // kGrabBig tiles for most of it.
+// The bounds are formed anew at each take (a few scalar instructions) instead
+// of being held in scalar registers, which the tile loop has none to spare of.
 struct TileGrab {
-    uint64_t T, fixed, head, qh, Q;   // tiles; tiles in fixed ranges; then in large ranges; large ranges, all ranges
-    uint32_t each, more;              // tiles of a fixed range; workgroups with one more
-    bool first;
+    bool first = true;
 
-    __device__ __forceinline__ TileGrab(uint64_t tiles)
+    // the next range [t0, t1) of T tiles; false once every range has been handed out
+    __device__ __forceinline__ bool next(const Job &job, uint64_t &t0, uint64_t &t1)
     {
-        T = tiles;
+        const uint64_t T = ld_uni(job.status + 2);
         const uint32_t W = gridDim.x;
-        more = 0;
-        each = kGrabBig;
+        // tiles of a fixed range, workgroups with one more
+        uint32_t each = kGrabBig, more = 0;
         uint64_t tail = (uint64_t)W * kTailTiles;
         if (T < (uint64_t)W * 4 * kGrabBig) {
             each = (uint32_t)T / W;
@@ -90,17 +91,6 @@ struct TileGrab {
                 tail = T;
             }
         }
-        fixed = (uint64_t)each * W + more;
-        const uint64_t rest = T - fixed;
-        head = rest > tail ? rest - tail : 0;
-        qh = (head + kGrabBig - 1) / kGrabBig;
-        Q = qh + (rest - head + kGrabSmall - 1) / kGrabSmall;
-        first = true;
-    }
-
-    // the next range [t0, t1); false once every range has been handed out
-    __device__ __forceinline__ bool next(const Job &job, uint64_t &t0, uint64_t &t1)
-    {
         if (first) {
             first = false;
             const uint32_t b = blockIdx.x;
@@ -108,19 +98,22 @@ struct TileGrab {
             t1 = t0 + each + (b < more ? 1 : 0);
             return t0 < t1;
         }
-        if (Q == 0) return false;
+        const uint64_t fixed = (uint64_t)each * W + more;
+        if (fixed == T) return false;
+        const uint64_t rest = T - fixed;
+        const uint64_t head = rest > tail ? rest - tail : 0;    // tiles in large ranges
+        const uint64_t qh = (head + kGrabBig - 1) / kGrabBig;
         uint64_t q = 0;
         if (threadIdx.x == 0) q = atomicAdd((unsigned long long *)(job.status + 5), 1ull);
         q = uni64(q);
-        if (q >= Q) return false;
         if (q < qh) {
             t0 = fixed + q * kGrabBig;
             t1 = t0 + kGrabBig < fixed + head ? t0 + kGrabBig : fixed + head;
-        } else {
-            t0 = fixed + head + (q - qh) * kGrabSmall;
-            t1 = t0 + kGrabSmall < T ? t0 + kGrabSmall : T;
+            return true;
         }
-        return true;
+        t0 = fixed + head + (q - qh) * kGrabSmall;
+        t1 = t0 + kGrabSmall < T ? t0 + kGrabSmall : T;
+        return t0 < T;
     }
 };
 
@@ -159,8 +152,8 @@ struct TileWalk {
         const Chunk ch = chunk_geometry(I, c);
         N = uni64(ch.N);
         Decoder &d = tc.dec;
-        d.r0 = d.c0 = d.b = d.a = d.h = 0;
-        d.Ttri = d.lbase = 0;
+        d.r0 = d.c0 = d.b = 0;
+        d.lbase = 0;
         d.wide = 0;
         uint64_t dv;
         if (I.directed) {
@@ -169,7 +162,7 @@ struct TileWalk {
             d.type = 1; dv = ch.w; d.b = uni((uint32_t)ch.b); row0 = uni((uint32_t)ch.a);
         } else {
             d.type = 2; dv = 1; row0 = uni((uint32_t)ch.a);
-            d.a = row0; d.h = uni((uint32_t)ch.h); d.Ttri = N;
+            d.r0 = row0; d.b = uni((uint32_t)ch.h);
         }
         if (dv == 0) dv = 1;
         d.type = uni(d.type);
@@ -260,9 +253,10 @@ __device__ __forceinline__ void cx(uint32_t &a, uint32_t &b)
 // from two buckets is already in order and never exchanged, so every bucket
 // is sorted on its own, as a sequence of at most R elements, which R rounds
 // of odd-even transposition sort (Knuth, TAOCP vol. 3, 5.3.4) always sort.
-// Returns the number of equal adjacent pairs among the first V positions.
+// Returns whether two adjacent positions are equal (repeats; count_repeats
+// counts them).
 template <int W>
-__device__ __forceinline__ uint32_t oddeven(uint32_t *s, uint32_t V, uint32_t R)
+__device__ __forceinline__ bool oddeven(uint32_t *s, uint32_t R)
 {
     const uint32_t lane = lane_here();
     const uint32_t p0 = W * lane;
@@ -280,14 +274,26 @@ __device__ __forceinline__ uint32_t oddeven(uint32_t *s, uint32_t V, uint32_t R)
         v[0] = v[0] > pv ? v[0] : pv;
     }
     wstore<W>(s, p0, v);
-    uint32_t eq = 0;
-#pragma unroll
-    for (int i = 0; i + 1 < W; ++i) eq += __popcll(__ballot(v[i] == v[i + 1]));
     const uint32_t nx = from_next_lane(v[0], ~v[W - 1]);       // lane 63: a value unequal to its last key
-    eq += __popcll(__ballot(v[W - 1] == nx));
-    // the pairs inside the padding [V, 64 W) are all equal; (V - 1, V) is not
-    constexpr uint32_t span = 64 * W;
-    return V < span ? eq - (span - 1 - V) : eq;
+    uint64_t eq = __ballot(v[W - 1] == nx);
+#pragma unroll
+    for (int i = 0; i + 1 < W; ++i) eq |= __ballot(v[i] == v[i + 1]);
+    return eq != 0;
+}
+
+// The number of repeats in the sorted keys s[0..V); `dup` is the place of the
+// last one.
+__device__ __forceinline__ uint32_t count_repeats(const uint32_t *s, uint32_t V, uint32_t &dup)
+{
+    const uint32_t lane = lane_here();
+    uint32_t n = 0;
+    for (uint32_t b = 0; b < V; b += 64) {
+        const uint32_t p = b + lane;
+        const uint64_t m = __ballot(p > 0 && p < V && s[p] == s[p - 1]);
+        if (m) dup = b + 63 - (uint32_t)__builtin_clzll(m);
+        n += (uint32_t)__popcll(m);
+    }
+    return n;
 }
 
 // Maximum over the 64 lanes (DPP row shifts, then row broadcasts; lane 63
@@ -313,13 +319,100 @@ __device__ __forceinline__ uint32_t wave_max32(uint32_t v)
 // starts; pass 2 places each draw at its bucket start plus its rank; as
 // many rounds of odd-even transposition as the fullest bucket has keys (8 to
 // 14 keys per lane) then sort inside buckets, and repeats are counted.
-// While fewer than ke distinct values are seen, J grows by the shortfall
-// (each draw adds at most one new value).  Leaves the sorted set in s[0..ke)
-// and returns true, or returns false once J would exceed lim (or in the rare
-// cases the queue kernel handles); the counters are zero again whenever it
-// returns.
+// The set is that of the first J draws with J the least count giving ke
+// distinct valid values.  J starts at ke, or, where rejections or repeats are
+// expected (a chunk's partial last tile, a dense tile), three standard
+// deviations below the expected count; while more than kMissing values are
+// missing the pass is repeated with a larger J, again by a low estimate (a
+// guess that turns out too large falls back to steps that cannot be), and
+// the last kMissing are drawn one by one and inserted (add_missing).  Leaves
+// the sorted set in s[0..ke) and returns true, or returns false once J would
+// exceed lim (or in the rare cases the queue kernel handles); the counters
+// are zero again whenever it returns.
 constexpr uint32_t kBucketWords = 512;   // one 32-bit counter per bucket
 constexpr uint32_t kMaxRounds = 32;      // a fuller bucket sends the tile to the queue
+constexpr uint32_t kMissing = 6;         // values inserted one by one (a pass costs about as much as six)
+
+// Draws J, J + 1, ... of the tile one by one until the sorted keys s[0..V)
+// hold ke distinct values: a new value takes the place of a repeat (`dup`: the
+// later position of one, if V exceeds the D distinct values), or the array
+// grows by one.  An insertion moves the keys between the two places by one
+// position.  Without it every tile with a repeat (12 % of the tiles at
+// 1024 keys of 2^22 slots) drew, placed and sorted all its keys a second time.
+// Returns the new V; kNone for a key equal to the padding value.
+__device__ __forceinline__ uint32_t add_missing(const TileCtx &t, uint32_t *s, uint32_t J, uint32_t V, uint32_t D,
+                                                uint32_t ke, uint32_t dup)
+{
+    const uint32_t lane = lane_here();
+    uint32_t base = J >> 2;
+    U4 w = t.st.block_uniform_key(base + lane);
+    bool known = true;                  // dup is the place of a repeat
+    while (D < ke) {
+        const uint32_t l = (J >> 2) - base;
+        if (l >= 64) {
+            base += 64;
+            w = t.st.block_uniform_key(base + lane);
+            continue;
+        }
+        const uint32_t q = J & 3;
+        const uint32_t wq = q == 0 ? w.x : q == 1 ? w.y : q == 2 ? w.z : w.w;
+        const uint32_t x = __builtin_amdgcn_readlane(wq, l) & t.mask;
+        ++J;
+        if (!t.full && x >= (uint32_t)t.S) continue;
+        if (x == kNone) return kNone;
+        // r: the keys below x, by two probes of 64 lanes
+        const uint32_t st = (V + 63) >> 6;
+        uint32_t p = lane * st;
+        uint32_t r = (uint32_t)__popcll(__ballot(p < V && s[p] < x));
+        if (r) {
+            const uint32_t lo = (r - 1) * st;
+            p = lo + lane;
+            r = lo + (uint32_t)__popcll(__ballot(lane < st && p < V && s[p] < x));
+        }
+        if (r < V && uni(s[r]) == x) continue;
+        uint32_t a = V;                 // the place that the new key's neighbours move into
+        if (V > D) {
+            if (!known) (void)count_repeats(s, V, dup);
+            known = false;
+            a = dup;
+        } else {
+            ++V;
+        }
+        if (a < r) {
+            for (uint32_t b = a; b + 1 < r; b += 64) {
+                p = b + lane;
+                const bool in = p + 1 < r;
+                const uint32_t y = in ? s[p + 1] : 0;
+                __syncthreads();
+                if (in) s[p] = y;
+            }
+            __syncthreads();
+            if (lane == 0) s[r - 1] = x;
+        } else {
+            for (uint32_t b = 0; r + b < a; b += 64) {
+                const bool in = r + b + lane < a;
+                p = a - b - lane;
+                const uint32_t y = in ? s[p - 1] : 0;
+                __syncthreads();
+                if (in) s[p] = y;
+            }
+            __syncthreads();
+            if (lane == 0) s[r] = x;
+        }
+        __syncthreads();
+        ++D;
+    }
+    return V;
+}
+
+// Draws to add, at least, when e values are missing and a draw is a new one
+// with probability f: three standard deviations below the mean e / f.
+__device__ __forceinline__ uint32_t draws_for(float e, float f)
+{
+    const float g = __builtin_amdgcn_rcpf(f);
+    const float x = e * g - 3.0f * __builtin_amdgcn_sqrtf(e * (1.0f - f)) * g - 1.0f;
+    return (uint32_t)fmaxf(e, x);
+}
 
 __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t *cnt, uint32_t ke, uint32_t lim)
 {
@@ -327,7 +420,17 @@ __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t
     const uint32_t S32 = (uint32_t)t.S;                 // used only when S < 2^bits <= 2^32
     const uint32_t shift = t.bits > 9 ? t.bits - 9 : 0;
     uint4 *cw = reinterpret_cast<uint4 *>(cnt) + 2 * lane;   // this lane's 8 counter words
-    uint32_t J = ke;
+    uint32_t J = ke;             // draws of this pass
+    uint32_t sure = ke;          // draws that are needed for certain
+    const bool sparse = t.full && (uint64_t)ke * ke <= 8 * t.S;    // at most 4 repeats expected
+    bool guess = !sparse;
+    if (guess) {
+        // on average a draw is valid and new with probability (S - ke / 2) / 2^bits
+        const float f = ((float)S32 - 0.5f * (float)ke) * __builtin_amdgcn_ldexpf(1.0f, -(int)t.bits);
+        const uint32_t g = uni(draws_for((float)ke, f));
+        J = g < lim ? g : lim;
+        J = J < ke ? ke : J;
+    }
     for (;;) {
         if (J > lim) return false;
         // the counters are zero here: cleared at the start of the kernel and
@@ -442,44 +545,66 @@ __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t
         cw[1] = make_uint4(0, 0, 0, 0);
         __syncthreads();
         if (R > kMaxRounds) return false;
-        uint32_t ndup;
+        uint32_t ndup, dup = 0;
         {
-            // keys per lane from V: 4, 8, 12, 16, 18 or 20; [V, 64 W) is padded with ~0
+            // keys per lane from V: 4, 8, 12, 16, 18 or 20; [V, 64 W) is padded
             const int mode = V <= 256 ? 0 : V <= 512 ? 1 : V <= 768 ? 2 : V <= 1024 ? 3 : V <= 1152 ? 4 : 5;
             constexpr uint32_t kSpan[6] = {256, 512, 768, 1024, 1152, 1280};
             const uint32_t span = kSpan[mode];
-            for (uint32_t p = V + lane; p < span; p += 64) s[p] = kNone;
+            // ascending above every key, so that no two are equal (in a tile of
+            // 2^32 slots they all are ~0, and the repeats are counted always)
+            for (uint32_t p = V + lane; p < span; p += 64) s[p] = t.bits < 32 ? 0x80000000u | p : kNone;
             __syncthreads();
-            if (mode == 0) ndup = oddeven<4>(s, V, R);
-            else if (mode == 1) ndup = oddeven<8>(s, V, R);
-            else if (mode == 2) ndup = oddeven<12>(s, V, R);
-            else if (mode == 3) ndup = oddeven<16>(s, V, R);
-            else if (mode == 4) ndup = oddeven<18>(s, V, R);
-            else ndup = oddeven<20>(s, V, R);
+            bool rep;
+            if (mode == 0) rep = oddeven<4>(s, R);
+            else if (mode == 1) rep = oddeven<8>(s, R);
+            else if (mode == 2) rep = oddeven<12>(s, R);
+            else if (mode == 3) rep = oddeven<16>(s, R);
+            else if (mode == 4) rep = oddeven<18>(s, R);
+            else rep = oddeven<20>(s, R);
             __syncthreads();
+            ndup = rep ? count_repeats(s, V, dup) : 0u;
         }
         const uint32_t D = V - ndup;
-        if (D == ke) {
-            if (ndup) {
-                uint32_t kept = 0;
-                for (uint32_t b0 = 0; b0 < V; b0 += 64) {
-                    const uint32_t p = b0 + lane;
-                    uint32_t xv = 0;
-                    bool keep = false;
-                    if (p < V) {
-                        xv = s[p];
-                        keep = p == 0 || s[p - 1] != xv;
-                    }
-                    const uint64_t bal = __ballot(keep);
-                    __syncthreads();
-                    if (keep) s[kept + __popcll(bal & lanemask_lt(lane))] = xv;
-                    kept += __popcll(bal);
-                    __syncthreads();
-                }
-            }
-            return true;
+        if (D > ke) {
+            guess = false;
+            J = sure;
+            continue;
         }
-        J += ke - D;
+        if (D + kMissing < ke) {
+            const uint32_t e = ke - D;
+            sure = J + e;
+            J = sure;
+            if (guess) {
+                const float f = ((float)S32 - (float)D) * __builtin_amdgcn_ldexpf(1.0f, -(int)t.bits);
+                J = sure - e + uni(draws_for((float)e, f));
+                J = J < lim ? J : sure < lim ? lim : sure;
+            }
+            continue;
+        }
+        if (D < ke) {
+            V = add_missing(t, s, J, V, D, ke, dup);
+            if (V == kNone) return false;
+        }
+        if (V > ke) {
+            // repeats are left: squeeze them out
+            uint32_t kept = 0;
+            for (uint32_t b0 = 0; b0 < V; b0 += 64) {
+                const uint32_t p = b0 + lane;
+                uint32_t xv = 0;
+                bool keep = false;
+                if (p < V) {
+                    xv = s[p];
+                    keep = p == 0 || s[p - 1] != xv;
+                }
+                const uint64_t bal = __ballot(keep);
+                __syncthreads();
+                if (keep) s[kept + __popcll(bal & lanemask_lt(lane))] = xv;
+                kept += __popcll(bal);
+                __syncthreads();
+            }
+        }
+        return true;
     }
 }
 
@@ -616,7 +741,7 @@ __device__ __forceinline__ void emit_tile(const TileCtx &t, const uint32_t *s, u
         TriV v;
         v.row = uni(e.x);
         v.off = uni(e.y - e.x - 1);
-        v.L = d.a + d.h - 1 - v.row;
+        v.L = d.r0 + d.b - 1 - v.row;
         if (v.L < (1u << 26) && (uint64_t)v.off + t.S + v.L < (1ull << 32)) {
             v.B = (double)v.L + 0.5;
             v.BB = v.B * v.B;
@@ -641,61 +766,61 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];   // bucket counters, then starts
     if (ld_uni(job.status + 1)) return;
-    const uint64_t T = ld_uni(job.status + 2);
     {
         uint4 *cw = reinterpret_cast<uint4 *>(s_cnt) + 2 * threadIdx.x;
         cw[0] = make_uint4(0, 0, 0, 0);
         cw[1] = make_uint4(0, 0, 0, 0);
         __syncthreads();
     }
-    const uint32_t lim = job.fast_cap < kFastDraws ? job.fast_cap : kFastDraws;
     TileWalk w;
     TileCtx &tc = w.tc;
     Decoder &d = tc.dec;
     tc.edges = job.edges;
-    TileGrab grab(T);
+    TileGrab grab;
     uint64_t t, t1;
     while (grab.next(job, t, t1)) {
         uint64_t g = chunk_of_tile(job, t);
         // tile offsets are read two tiles ahead: they come from HBM (the output
         // stream evicts them from the caches), so a tile never waits for its own
+        // (the read after the last offset lands in the queue behind them, unused)
         uint64_t o_next = ld_uni(job.tile_off + t);
         uint64_t o_pre = ld_uni(job.tile_off + t + 1);
         for (;;) {
             // chunk constants, then the decoder at the wave's first tile of the chunk
             w.enter(job, g);
-            const uint64_t tend = w.gend < t1 ? w.gend : t1;
             const uint32_t s = w.s;
-            const uint64_t full_S = 1ull << s;
-            uint64_t lstart = (t - w.gstart) << s;
+            // tiles of the range in this chunk; after `full` of them comes the
+            // chunk's last tile, of last_S slots (0: 2^32)
+            const uint64_t tend = w.gend < t1 ? w.gend : t1;
+            const uint32_t count = (uint32_t)(tend - t), full = (uint32_t)(w.gend - 1 - t);
+            const uint32_t last_S = (uint32_t)(w.N - ((w.gend - 1 - w.gstart) << s));
+            tc.st.b = uni((uint32_t)(t - w.gstart));
+            d.lbase = (t - w.gstart) << s;
             if (d.type != 2) {
-                const uint64_t q = div_est(lstart, d.dv, d.rcp);
-                d.c0 = uni((uint32_t)(lstart - q * d.dv));
+                const uint64_t q = div_est(d.lbase, d.dv, d.rcp);
+                d.c0 = uni((uint32_t)(d.lbase - q * d.dv));
                 d.r0 = uni(w.row0 + (uint32_t)q);
             }
             const uint32_t qs32 = (uint32_t)w.qs;
-            for (; t < tend; ++t) {
+            for (uint32_t i = 0; i < count; ++i) {
                 const uint64_t o0 = o_next;
                 o_next = o_pre;
-                if (t + 2 <= T) o_pre = ld_uni(job.tile_off + t + 2);
+                o_pre = ld_uni(job.tile_off + t + i + 2);
                 const uint64_t k = o_next - o0;
                 if (k != 0) {
                     // slots of the tile: 2^s except for the chunk's last tile
-                    if (t + 1 < w.gend) {
-                        tc.S = full_S;
-                        tc.bits = s;
-                        tc.mask = s >= 32 ? 0xFFFFFFFFu : (1u << s) - 1;
-                        tc.full = 1;
-                    } else {
-                        tc.S = uni64(w.N - lstart);
-                        tc.bits = uni(tc.S <= 1 ? 0 : 64 - __clzll(tc.S - 1));
-                        tc.mask = uni(tc.bits >= 32 ? 0xFFFFFFFFu : ((1u << tc.bits) - 1));
+                    tc.S = 1ull << s;
+                    tc.bits = s;
+                    tc.full = 1;
+                    if (i == full && last_S != (uint32_t)tc.S) {
+                        tc.S = last_S;
+                        tc.bits = uni(last_S <= 1 ? 0 : 32 - __clz(last_S - 1));
                         tc.full = uni(tc.S == (1ull << tc.bits));
                     }
-                    tc.st.b = uni((uint32_t)(t - w.gstart));
-                    d.lbase = lstart;
+                    tc.mask = (uint32_t)((1ull << tc.bits) - 1);
                     d.wide = s == 32 ? uni((uint64_t)d.c0 + tc.S > (1ull << 32)) : 0u;
                     tc.o0 = o0;
+                    const uint32_t lim = job.fast_cap < kFastDraws ? job.fast_cap : kFastDraws;
                     const bool comp = 2 * k > tc.S;
                     const uint64_t ke = comp ? tc.S - k : k;
                     if (ke == 0) {
@@ -705,12 +830,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                         else emit_complement(tc, s_key, (uint32_t)ke, 0, tc.S, 0);
                     } else if (threadIdx.x == 0) {
                         const uint64_t q = atomicAdd((unsigned long long *)(job.status + 4), 1ull);
-                        job.queue[q] = t;
+                        job.queue[q] = t + i;
                     }
                     __syncthreads();
                 }
                 // next tile of the chunk: 2^s = qs dv + rs slots further
-                lstart += full_S;
+                ++tc.st.b;
+                d.lbase += 1ull << s;
                 if (d.type != 2) {
                     uint32_t c0 = d.c0 + w.rs, r0 = d.r0 + qs32;
                     if (c0 >= d.dv) { c0 -= d.dv; ++r0; }
@@ -718,6 +844,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                     d.r0 = r0;
                 }
             }
+            t = tend;
             if (t >= t1) break;
             // next chunk that has tiles
             ++g;
