@@ -16,6 +16,7 @@
 #include "kg_skip.hpp"
 #include "kg_rgg.hpp"
 #include "kg_rgg3.hpp"
+#include "kg_rgg_block.hpp"
 #include "kg_hash.hpp"
 
 namespace kg {
@@ -538,33 +539,125 @@ uint32_t rgg_level(uint64_t n, double r)
     return L;
 }
 
-struct RggLayout {
-    uint32_t L;
-    uint64_t C, nw, nbc, nbw;
-    uint64_t tree, coff, pcell, ecnt, bits, wsum, woff, sums, status, total;
+// The block kernels (kg_rgg_block.hpp) take grids with few points per cell,
+// which the level rule gives unless the radius (or the level limit) keeps the
+// cells large: in two dimensions up to 32 points per cell, in three up to 22,
+// so that a block's result words hold its candidates (at most 6, of 18, cells'
+// points) with four standard deviations to spare; denser grids keep a lane per
+// vertex, whose waves share the work of one cell.  A block is one cell, or
+// 2^D where a cell's points (below 8, 5) would leave too little to share the
+// window's set-up; from 10 points per cell in three dimensions on, the
+// candidates need 16 words per vertex.
+struct RggBlocks {
+    int B = -1;                // block level (cells of side 2^B); -1: not taken
+    uint32_t words = 8, Q = 13, list = 0;      // result words per vertex, position bits, kept list words per block
+    uint64_t nb = 0;
 };
 
-RggLayout rgg_layout(uint64_t n, double r)
+RggBlocks rgg_blocks(int D, uint64_t n, uint32_t L)
+{
+    RggBlocks P;
+    const double a = ldexp((double)n, -(int)(D * L));     // points per cell
+    if (n == 0 || a > (D == 2 ? 32.0 : 22.0)) return P;
+    P.B = L >= 1 && a < (D == 2 ? 8.0 : 5.0) ? 1 : 0;
+    if (D == 3 && a >= 10.0) P.words = 16;
+    if (D == 2 && P.B == 0) P.Q = 14;
+    if (D == 3) P.list = P.B ? RggWindow<3, 1, 8>::LIST : RggWindow<3, 0, 8>::LIST;
+    P.nb = (1ull << (D * L)) >> (D * P.B);
+    return P;
+}
+
+// Squares of quantised distances: below lo an edge for certain, above
+// lo + band none.  Rounding the positions down moves a distance by less than
+// sqrt(D) units (0.01 covers the rounding of the coordinates and the predicate).
+void rgg_block_band(int D, double r, uint32_t L, uint32_t Q, uint32_t &lo, uint32_t &band)
+{
+    const double rq = fmin(ldexp(r, (int)(L + Q)), 65536.0), e = sqrt((double)D) + 0.01;
+    const double most = 2147483647.0;
+    const double a = rq > e ? floor((rq - e) * (rq - e)) : 0.0, b = ceil((rq + e) * (rq + e));
+    lo = (uint32_t)fmin(a, most);
+    band = (uint32_t)(fmin(b, most) - (double)lo);
+}
+
+struct RggLayout {
+    uint32_t L;
+    RggBlocks P;
+    uint64_t C, nw, nbc, nbw;
+    uint64_t tree, coff, pcell, ecnt, q, list, bits, wsum, woff, sums, status, total;
+};
+
+// nw: the entries of the edge counts' scan (blocks, or waves of 64 vertices)
+RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
 {
     RggLayout Y;
-    Y.L = rgg_level(n, r);
-    Y.C = 1ull << (2 * Y.L);
-    Y.nw = (n + 63) / 64;
+    Y.L = L;
+    Y.P = rgg_blocks(D, n, L);
+    const bool blk = Y.P.B >= 0;
+    Y.C = 1ull << (D * L);
+    Y.nw = blk ? Y.P.nb : (n + 63) / 64;
     Y.nbc = (Y.C + kScanTile - 1) / kScanTile;
     Y.nbw = Y.nw ? (Y.nw + kScanTile - 1) / kScanTile : 1;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { const uint64_t at = o; o += (bytes + 255) & ~255ull; return at; };
-    Y.tree = take(((1ull << (2 * (Y.L + 1))) - 1) / 3 * 8);
+    Y.tree = take(((1ull << (D * (L + 1))) - 1) / ((1u << D) - 1) * 8);
     Y.coff = take((Y.C + 1) * 8);
-    Y.pcell = take(n * 4);
-    Y.ecnt = take(n * 4);
-    Y.bits = take(n * 8 * kRggBitWords);
+    Y.pcell = take(blk ? 0 : n * 4);
+    Y.ecnt = take(blk ? 0 : n * 4);
+    Y.q = take(blk ? n * 4 * (D - 1) : 0);
+    Y.list = take(blk ? Y.P.nb * Y.P.list * 4 : 0);
+    Y.bits = take(blk ? n * 4 * Y.P.words : n * 8 * (D == 2 ? kRggBitWords : kRgg3BitWords));
     Y.wsum = take((Y.nw + 1) * 8);
     Y.woff = take((Y.nw + 1) * 8);
     Y.sums = take((std::max(Y.nbc, Y.nbw) + 1) * 8);
     Y.status = take(4 * 8);
     Y.total = o;
     return Y;
+}
+
+RggLayout rgg_layout(uint64_t n, double r) { return rgg_layout_any(2, n, rgg_level(n, r)); }
+
+RggBlockJob rgg_block_job(int D, uint64_t n, double r, uint64_t capacity, const RggLayout &Y, char *ws,
+                          const double *pts, uint32_t *edges)
+{
+    RggBlockJob J;
+    memset(&J, 0, sizeof(J));
+    J.n = n;
+    J.capacity = capacity;
+    J.r2 = r * r;
+    J.nb = Y.P.nb;
+    J.G = 1u << Y.L;
+    J.Q = Y.P.Q;
+    rgg_block_band(D, r, Y.L, Y.P.Q, J.lo, J.band);
+    J.coff = (const uint64_t *)(ws + Y.coff);
+    J.q = (const uint32_t *)(ws + Y.q);
+    J.list = (uint32_t *)(ws + Y.list);
+    J.bits = (uint32_t *)(ws + Y.bits);
+    J.bcnt = (uint64_t *)(ws + Y.wsum);
+    J.boff = (const uint64_t *)(ws + Y.woff);
+    J.status = (const uint64_t *)(ws + Y.status);
+    J.pts = pts;
+    J.edges = (uint2 *)edges;
+    return J;
+}
+
+void rgg_block_count(int D, const RggBlocks &P, const RggBlockJob &J, hipStream_t s)
+{
+    const dim3 grid((uint32_t)((P.nb + kBlocksPerWave - 1) / kBlocksPerWave)), wave(64);
+    if (D == 2 && P.B == 0) hipLaunchKernelGGL((rgg_block_count_kernel<2, 0, 8>), grid, wave, 0, s, J);
+    else if (D == 2) hipLaunchKernelGGL((rgg_block_count_kernel<2, 1, 8>), grid, wave, 0, s, J);
+    else if (P.B == 1) hipLaunchKernelGGL((rgg_block_count_kernel<3, 1, 8>), grid, wave, 0, s, J);
+    else if (P.words == 8) hipLaunchKernelGGL((rgg_block_count_kernel<3, 0, 8>), grid, wave, 0, s, J);
+    else hipLaunchKernelGGL((rgg_block_count_kernel<3, 0, 16>), grid, wave, 0, s, J);
+}
+
+void rgg_block_write(int D, const RggBlocks &P, const RggBlockJob &J, hipStream_t s)
+{
+    const dim3 grid((uint32_t)((P.nb + kBlocksPerWave - 1) / kBlocksPerWave)), wave(64);
+    if (D == 2 && P.B == 0) hipLaunchKernelGGL((rgg_block_write_kernel<2, 0, 8>), grid, wave, 0, s, J);
+    else if (D == 2) hipLaunchKernelGGL((rgg_block_write_kernel<2, 1, 8>), grid, wave, 0, s, J);
+    else if (P.B == 1) hipLaunchKernelGGL((rgg_block_write_kernel<3, 1, 8>), grid, wave, 0, s, J);
+    else if (P.words == 8) hipLaunchKernelGGL((rgg_block_write_kernel<3, 0, 8>), grid, wave, 0, s, J);
+    else hipLaunchKernelGGL((rgg_block_write_kernel<3, 0, 16>), grid, wave, 0, s, J);
 }
 
 uint32_t rgg3_level(uint64_t n, double r)
@@ -574,34 +667,7 @@ uint32_t rgg3_level(uint64_t n, double r)
     return L;
 }
 
-struct Rgg3Layout {
-    uint32_t L;
-    uint64_t C, nw, nbc, nbw;
-    uint64_t tree, coff, pcell, ecnt, bits, wsum, woff, sums, status, total;
-};
-
-Rgg3Layout rgg3_layout(uint64_t n, double r)
-{
-    Rgg3Layout Y;
-    Y.L = rgg3_level(n, r);
-    Y.C = 1ull << (3 * Y.L);
-    Y.nw = (n + 63) / 64;
-    Y.nbc = (Y.C + kScanTile - 1) / kScanTile;
-    Y.nbw = Y.nw ? (Y.nw + kScanTile - 1) / kScanTile : 1;
-    uint64_t o = 0;
-    auto take = [&](uint64_t bytes) { const uint64_t at = o; o += (bytes + 255) & ~255ull; return at; };
-    Y.tree = take(((1ull << (3 * (Y.L + 1))) - 1) / 7 * 8);
-    Y.coff = take((Y.C + 1) * 8);
-    Y.pcell = take(n * 4);
-    Y.ecnt = take(n * 4);
-    Y.bits = take(n * 8 * kRgg3BitWords);
-    Y.wsum = take((Y.nw + 1) * 8);
-    Y.woff = take((Y.nw + 1) * 8);
-    Y.sums = take((std::max(Y.nbc, Y.nbw) + 1) * 8);
-    Y.status = take(4 * 8);
-    Y.total = o;
-    return Y;
-}
+RggLayout rgg3_layout(uint64_t n, double r) { return rgg_layout_any(3, n, rgg3_level(n, r)); }
 
 kg_status rgg3_check(uint64_t n, double r)
 {
@@ -890,6 +956,10 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     J.out_total = d_total;
     J.pts = (double2 *)d_points;
     J.edges = (uint2 *)d_edges;
+    const bool blk = Y.P.B >= 0;
+    J.q = blk ? (uint32_t *)(ws.base + Y.q) : nullptr;
+    J.Q = Y.P.Q;
+    const RggBlockJob JB = rgg_block_job(2, n, r, capacity_edges, Y, ws.base, d_points, d_edges);
     {
         KernelTimer tm(KG_KERNEL_COUNT, s);
         hipLaunchKernelGGL(rgg_root_kernel, dim3(1), dim3(64), 0, s, J);
@@ -908,7 +978,8 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     const uint64_t nwg = Y.nw ? Y.nw : 1;
     {
         KernelTimer tm(KG_KERNEL_PLAN, s);
-        hipLaunchKernelGGL(rgg_edges_kernel<false>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
+        if (blk) rgg_block_count(2, Y.P, JB, s);
+        else hipLaunchKernelGGL(rgg_edges_kernel<false>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
     }
     {
         KernelTimer tm(KG_KERNEL_SCAN, s);
@@ -917,7 +988,8 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     }
     {
         KernelTimer tm(KG_KERNEL_SAMPLE, s);
-        hipLaunchKernelGGL(rgg_edges_kernel<true>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
+        if (blk) rgg_block_write(2, Y.P, JB, s);
+        else hipLaunchKernelGGL(rgg_edges_kernel<true>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
     }
     if (!launched_ok()) st = KG_EDEVICE;
     release(ws, s);
@@ -949,7 +1021,7 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     int dev = 0;
     st = ensure_init(&dev);
     if (st) return st;
-    const Rgg3Layout Y = rgg3_layout(n, r);
+    const RggLayout Y = rgg3_layout(n, r);
     Workspace ws;
     st = acquire(ws, d_workspace, workspace_bytes, Y.total, s);
     if (st) return st;
@@ -975,6 +1047,10 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     J.out_total = d_total;
     J.pts = d_points;
     J.edges = (uint2 *)d_edges;
+    const bool blk = Y.P.B >= 0;
+    J.q = blk ? (uint32_t *)(ws.base + Y.q) : nullptr;
+    J.Q = Y.P.Q;
+    const RggBlockJob JB = rgg_block_job(3, n, r, capacity_edges, Y, ws.base, d_points, d_edges);
     {
         KernelTimer tm(KG_KERNEL_COUNT, s);
         hipLaunchKernelGGL(rgg3_root_kernel, dim3(1), dim3(64), 0, s, J);
@@ -993,7 +1069,8 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     const uint64_t nwg = Y.nw ? Y.nw : 1;
     {
         KernelTimer tm(KG_KERNEL_PLAN, s);
-        hipLaunchKernelGGL(rgg3_edges_kernel<false>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
+        if (blk) rgg_block_count(3, Y.P, JB, s);
+        else hipLaunchKernelGGL(rgg3_edges_kernel<false>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
     }
     {
         KernelTimer tm(KG_KERNEL_SCAN, s);
@@ -1002,7 +1079,8 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     }
     {
         KernelTimer tm(KG_KERNEL_SAMPLE, s);
-        hipLaunchKernelGGL(rgg3_edges_kernel<true>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
+        if (blk) rgg_block_write(3, Y.P, JB, s);
+        else hipLaunchKernelGGL(rgg3_edges_kernel<true>, dim3((uint32_t)nwg), dim3(64), 0, s, J);
     }
     if (!launched_ok()) st = KG_EDEVICE;
     release(ws, s);

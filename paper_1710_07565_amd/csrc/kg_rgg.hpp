@@ -42,6 +42,8 @@ struct RggJob {
     uint64_t *sums;            // scan partials
     uint64_t *status;          // [0] edges [1] overflow
     uint64_t *out_total;
+    uint32_t *q;               // n packed positions in their cells for the block kernels, or null
+    uint32_t Q;                // their bits
     double2 *pts;
     uint2 *edges;
 };
@@ -226,7 +228,9 @@ __global__ __launch_bounds__(64) void rgg_points_kernel(RggJob J)
             const double U = unit_of(((uint64_t)w.y << 32) | w.x);
             const double V = unit_of(((uint64_t)w.w << 32) | w.z);
             J.pts[p] = make_double2((cx + U) * J.h, (cy + V) * J.h);
-            J.pcell[p] = z;
+            // the top Q bits of the draws: floor(2^Q U), floor(2^Q V)
+            if (J.q) J.q[p] = w.y >> (32 - J.Q) | w.w >> (32 - J.Q) << 16;
+            else J.pcell[p] = z;
         }
     }
 }

@@ -47,6 +47,8 @@ struct Rgg3Job {
     uint64_t *sums;            // scan partials
     uint64_t *status;          // [0] edges [1] overflow
     uint64_t *out_total;
+    uint32_t *q;               // n packed (two words) positions in their cells for the block kernels, or null
+    uint32_t Q;                // their bits
     double *pts;               // 3 n: x, y, z of every vertex
     uint2 *edges;
 };
@@ -136,7 +138,14 @@ __global__ __launch_bounds__(64) void rgg3_points_kernel(Rgg3Job J)
             double *q = J.pts + 3 * p;
 #pragma unroll
             for (int a = 0; a < 3; ++a) q[a] = ((double)gather3(z >> a) + unit_of(d[a])) * J.h;
-            J.pcell[p] = z;
+            if (J.q) {
+                uint32_t w[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) w[a] = (uint32_t)(d[a] >> (64 - J.Q));
+                reinterpret_cast<uint2 *>(J.q)[p] = make_uint2(w[0] | w[1] << 16, w[2]);
+            } else {
+                J.pcell[p] = z;
+            }
         }
     }
 }
