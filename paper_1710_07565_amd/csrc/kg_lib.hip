@@ -582,9 +582,13 @@ void rgg_block_band(int D, double r, uint32_t L, uint32_t Q, uint32_t &lo, uint3
 struct RggLayout {
     uint32_t L;
     RggBlocks P;
-    uint64_t C, nw, nbc, nbw;
-    uint64_t tree, coff, pcell, ecnt, q, list, bits, wsum, woff, sums, status, total;
+    uint64_t C, nw, nbw;
+    uint64_t mid, coff, pcell, ecnt, q, list, bits, wsum, woff, sums, status, total;
 };
+
+// Nodes of the last level but one launch's: two launches below depth 22, three
+// (of at most 10 levels) up to 30.
+constexpr uint64_t kSplitMid = (1ull << 20) + 32;
 
 // nw: the entries of the edge counts' scan (blocks, or waves of 64 vertices)
 RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
@@ -595,11 +599,10 @@ RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
     const bool blk = Y.P.B >= 0;
     Y.C = 1ull << (D * L);
     Y.nw = blk ? Y.P.nb : (n + 63) / 64;
-    Y.nbc = (Y.C + kScanTile - 1) / kScanTile;
     Y.nbw = Y.nw ? (Y.nw + kScanTile - 1) / kScanTile : 1;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { const uint64_t at = o; o += (bytes + 255) & ~255ull; return at; };
-    Y.tree = take(((1ull << (D * (L + 1))) - 1) / ((1u << D) - 1) * 8);
+    Y.mid = take(2 * kSplitMid * 8);
     Y.coff = take((Y.C + 1) * 8);
     Y.pcell = take(blk ? 0 : n * 4);
     Y.ecnt = take(blk ? 0 : n * 4);
@@ -608,7 +611,7 @@ RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
     Y.bits = take(blk ? n * 4 * Y.P.words : n * 8 * (D == 2 ? kRggBitWords : kRgg3BitWords));
     Y.wsum = take((Y.nw + 1) * 8);
     Y.woff = take((Y.nw + 1) * 8);
-    Y.sums = take((std::max(Y.nbc, Y.nbw) + 1) * 8);
+    Y.sums = take((Y.nbw + 1) * 8);
     Y.status = take(4 * 8);
     Y.total = o;
     return Y;
@@ -689,12 +692,34 @@ kg_status rgg_check(uint64_t n, double r)
     return KG_OK;
 }
 
-void rgg_scan(const uint64_t *a, uint64_t len, uint64_t *sums, uint64_t *out, hipStream_t s)
+void rgg_scan(const uint64_t *a, uint64_t len, uint64_t *sums, uint64_t *out, uint64_t *status, uint64_t capacity,
+              uint64_t *total, hipStream_t s)
 {
     const uint64_t nb = len ? (len + kScanTile - 1) / kScanTile : 1;
     hipLaunchKernelGGL(scan_reduce_kernel, dim3((uint32_t)nb), dim3(256), 0, s, a, len, sums);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, s, sums, nb);
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(1024), 0, s, sums, nb, status, capacity, total);
     hipLaunchKernelGGL(scan_apply_kernel, dim3((uint32_t)nb), dim3(256), 0, s, a, len, (const uint64_t *)sums, out);
+}
+
+// First vertex of every cell: the D L levels of the binary tree in launches of
+// equally many (at most kSplitMost) levels, one workgroup per node of a
+// launch's first level.  The first launch has one workgroup, which takes all
+// the lanes it can get; of the later ones many run at once.
+void rgg_split(int D, uint64_t n, uint64_t seed, uint32_t L, uint64_t *mid, uint64_t *coff, hipStream_t s)
+{
+    const uint32_t depth = D * L, launches = depth ? (depth + kSplitMost - 1) / kSplitMost : 1;
+    const uint64_t *in = nullptr;
+    for (uint32_t i = 0, p = 0; i < launches; ++i) {
+        const uint32_t q = (depth - p) / (launches - i);
+        uint64_t *out = i + 1 == launches ? coff : mid + (i & 1) * kSplitMid;
+        const dim3 grid((uint32_t)(1ull << p)), block(i == 0 ? 1024 : 256);
+        if (D == 2)
+            hipLaunchKernelGGL(rgg_split_kernel<2>, grid, block, 0, s, seed, n, (uint32_t)TAG_RTREE, in, out, p, q);
+        else
+            hipLaunchKernelGGL(rgg_split_kernel<3>, grid, block, 0, s, seed, n, (uint32_t)TAG_RTREE3, in, out, p, q);
+        in = out;
+        p += q;
+    }
 }
 
 }  // namespace
@@ -944,7 +969,6 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     J.L = Y.L;
     J.G = 1u << Y.L;
     J.C = Y.C;
-    J.tree = (uint64_t *)(ws.base + Y.tree);
     J.coff = (uint64_t *)(ws.base + Y.coff);
     J.pcell = (uint32_t *)(ws.base + Y.pcell);
     J.ecnt = (uint32_t *)(ws.base + Y.ecnt);
@@ -962,14 +986,7 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     const RggBlockJob JB = rgg_block_job(2, n, r, capacity_edges, Y, ws.base, d_points, d_edges);
     {
         KernelTimer tm(KG_KERNEL_COUNT, s);
-        hipLaunchKernelGGL(rgg_root_kernel, dim3(1), dim3(64), 0, s, J);
-        for (uint32_t l = 0; l < Y.L; ++l)
-            hipLaunchKernelGGL(rgg_split_kernel, dim3((uint32_t)(((1ull << (2 * l)) + 63) / 64)), dim3(64), 0, s,
-                               J, l);
-    }
-    {
-        KernelTimer tm(KG_KERNEL_SCAN, s);
-        rgg_scan(J.tree + ((Y.C - 1) / 3), Y.C, J.sums, J.coff, s);
+        rgg_split(2, n, seed, Y.L, (uint64_t *)(ws.base + Y.mid), J.coff, s);
     }
     {
         KernelTimer tm(KG_KERNEL_QUEUE, s);
@@ -983,8 +1000,7 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     }
     {
         KernelTimer tm(KG_KERNEL_SCAN, s);
-        rgg_scan(J.wsum, Y.nw, J.sums, J.woff, s);
-        hipLaunchKernelGGL(rgg_total_kernel, dim3(1), dim3(64), 0, s, J, Y.nw);
+        rgg_scan(J.wsum, Y.nw, J.sums, J.woff, J.status, capacity_edges, d_total, s);
     }
     {
         KernelTimer tm(KG_KERNEL_SAMPLE, s);
@@ -1035,7 +1051,6 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     J.L = Y.L;
     J.G = 1u << Y.L;
     J.C = Y.C;
-    J.tree = (uint64_t *)(ws.base + Y.tree);
     J.coff = (uint64_t *)(ws.base + Y.coff);
     J.pcell = (uint32_t *)(ws.base + Y.pcell);
     J.ecnt = (uint32_t *)(ws.base + Y.ecnt);
@@ -1053,14 +1068,7 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     const RggBlockJob JB = rgg_block_job(3, n, r, capacity_edges, Y, ws.base, d_points, d_edges);
     {
         KernelTimer tm(KG_KERNEL_COUNT, s);
-        hipLaunchKernelGGL(rgg3_root_kernel, dim3(1), dim3(64), 0, s, J);
-        for (uint32_t l = 0; l < Y.L; ++l)
-            hipLaunchKernelGGL(rgg3_split_kernel, dim3((uint32_t)(((1ull << (3 * l)) + 63) / 64)), dim3(64), 0, s,
-                               J, l);
-    }
-    {
-        KernelTimer tm(KG_KERNEL_SCAN, s);
-        rgg_scan(J.tree + ((Y.C - 1) / 7), Y.C, J.sums, J.coff, s);
+        rgg_split(3, n, seed, Y.L, (uint64_t *)(ws.base + Y.mid), J.coff, s);
     }
     {
         KernelTimer tm(KG_KERNEL_QUEUE, s);
@@ -1074,8 +1082,7 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     }
     {
         KernelTimer tm(KG_KERNEL_SCAN, s);
-        rgg_scan(J.wsum, Y.nw, J.sums, J.woff, s);
-        hipLaunchKernelGGL(rgg3_total_kernel, dim3(1), dim3(64), 0, s, J, Y.nw);
+        rgg_scan(J.wsum, Y.nw, J.sums, J.woff, J.status, capacity_edges, d_total, s);
     }
     {
         KernelTimer tm(KG_KERNEL_SAMPLE, s);

@@ -32,7 +32,6 @@ struct RggJob {
     double r2, h;              // r * r, cell side 2^-L
     uint32_t L, G;             // level, cells per side
     uint64_t C;                // cells
-    uint64_t *tree;            // node counts, level l at (4^l - 1) / 3, Morton order
     uint64_t *coff;            // C + 1 first vertex id of every cell
     uint32_t *pcell;           // n: cell of every vertex
     uint32_t *ecnt;            // n: edges (u, v > u) of every vertex u; top bit: more candidates than recorded
@@ -47,8 +46,6 @@ struct RggJob {
     double2 *pts;
     uint2 *edges;
 };
-
-__device__ __forceinline__ uint64_t rgg_level_base(uint32_t l) { return ((1ull << (2 * l)) - 1) / 3; }
 
 // Morton index <-> cell coordinates (L <= 14, so 28 bits)
 __device__ __forceinline__ uint32_t spread_bits(uint32_t x)
@@ -71,36 +68,85 @@ __device__ __forceinline__ uint32_t gather_bits(uint32_t z)
     return z;
 }
 
-__global__ __launch_bounds__(64) void rgg_root_kernel(RggJob J)
-{
-    if (threadIdx.x == 0) J.tree[0] = J.n;
-}
+// ---------------------------------------------------------------------------
+// Points per cell.  The quadrant (octant) recursion is a binary tree over the
+// Morton index: depth D l + r splits node i by Bin(count, 1/2), the variate of
+// level-l node z = i >> r with slot 2^r - 1 + (i mod 2^r), into children 2 i
+// and 2 i + 1.  A workgroup expands one node at depth p by q levels in LDS
+// and writes its descendants' first vertices: the node's own first vertex plus
+// the counts before them.  So a launch covers q levels for all nodes of depth
+// p, the offsets need no scan of their own, and the tree is never stored.
+// In the launches of few workgroups, while a level has few nodes, its variates'
+// latency is the time, and 8 lanes try proposals of each; elsewhere a node has
+// one lane.
+// Measured against one launch per level and a scan (14 launches instead of 2):
+// n = 1,000,003 in two dimensions 110 -> 43 us, n = 2^26 0.31 -> 0.28 ms; three
+// dimensions 0.62 -> 0.57 ms.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kSplitMost = 12;      // levels of one launch, at most
+constexpr uint32_t kSplitLanes = 8;      // lanes per variate while they last ...
+constexpr uint32_t kSplitFew = 256;      // ... in launches that leave the chip half empty
 
-// One level of the quadrant recursion: lane per node of level l.
-__global__ __launch_bounds__(64) void rgg_split_kernel(RggJob J, uint32_t l)
+template <int D>
+__global__ __launch_bounds__(1024) void rgg_split_kernel(uint64_t seed, uint64_t n, uint32_t tag, const uint64_t *in,
+                                                         uint64_t *out, uint32_t p, uint32_t q)
 {
-    const uint64_t z = (uint64_t)blockIdx.x * 64 + threadIdx.x;
-    if (z >= (1ull << (2 * l))) return;
-    const uint64_t k = J.tree[rgg_level_base(l) + z];
-    // lower half, its left quadrant, the upper half's left quadrant (one copy
-    // of the variate's code)
-    uint64_t v[3];
-#pragma unroll 1
-    for (uint32_t i = 0; i < 3; ++i) {
-        const uint64_t of = i == 0 ? k : i == 1 ? v[0] : k - v[0];
-        const uint64_t x = binom(make_stream(J.seed, (uint32_t)z, 3 * l + i, TAG_RTREE), of, 0.5);
-        if (i == 0) v[0] = x; else if (i == 1) v[1] = x; else v[2] = x;
+    __shared__ uint32_t s_n[2][1u << kSplitMost];
+    __shared__ uint32_t s_w[16];
+    const uint32_t t = threadIdx.x, NT = blockDim.x;
+    const uint64_t node = blockIdx.x;
+    const uint64_t first = p ? in[node] : 0, last = p ? in[node + 1] : n;
+    if (t == 0) s_n[0][0] = (uint32_t)(last - first);
+    __syncthreads();
+    uint32_t cur = 0;
+    for (uint32_t d = 0; d < q; ++d, cur ^= 1) {
+        const uint32_t m = 1u << d, depth = p + d, l = depth / D, r = depth - D * l;
+        auto stream = [&](uint32_t i) {
+            const uint32_t g = (uint32_t)(node << d) + i;
+            const uint32_t slot = (1u << r) - 1 + (g & ((1u << r) - 1));
+            return make_stream(seed, g >> r, ((1u << D) - 1) * l + slot, tag);
+        };
+        auto put = [&](uint32_t i, uint32_t k, uint32_t x) {
+            s_n[cur ^ 1][2 * i] = x;
+            s_n[cur ^ 1][2 * i + 1] = k - x;
+        };
+        if (m * kSplitLanes <= NT && gridDim.x <= kSplitFew) {
+            const uint32_t i = t / kSplitLanes;
+            if (i < m) {
+                const uint32_t k = s_n[cur][i];
+                const uint32_t x = (uint32_t)binom<kSplitLanes>(stream(i), k, 0.5);
+                if (t % kSplitLanes == 0) put(i, k, x);
+            }
+        } else {
+            for (uint32_t i = t; i < m; i += NT) {
+                const uint32_t k = s_n[cur][i];
+                put(i, k, (uint32_t)binom(stream(i), k, 0.5));
+            }
+        }
+        __syncthreads();
     }
-    const uint64_t lower = v[0], ll = v[1], ul = v[2];
-    uint64_t *ch = J.tree + rgg_level_base(l + 1) + 4 * z;
-    ch[0] = ll;
-    ch[1] = lower - ll;
-    ch[2] = ul;
-    ch[3] = k - lower - ul;
+    // exclusive prefix sums of the 2^q counts (a contiguous run per thread)
+    const uint32_t m = 1u << q, per = (m + NT - 1) / NT, lane = t & 63, w = t >> 6;
+    const uint32_t i0 = min(t * per, m), i1 = min(i0 + per, m);
+    uint32_t sum = 0;
+    for (uint32_t i = i0; i < i1; ++i) sum += s_n[cur][i];
+    const uint32_t incl = wave_incl_scan32(sum);
+    if (lane == 63) s_w[w] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+    for (uint32_t j = 0; j < w; ++j) run += s_w[j];
+    for (uint32_t i = i0; i < i1; ++i) {
+        const uint32_t c = s_n[cur][i];
+        s_n[cur][i] = run;
+        run += c;
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < m; i += NT) out[node * m + i] = first + s_n[cur][i];
+    if (t == 0 && node + 1 == gridDim.x) out[(uint64_t)gridDim.x * m] = n;
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of a u64 array of any length in three launches: tiles of
+// Exclusive scan of the edge counts (u64, any length) in three launches: tiles of
 // 4096 (256 threads x 16 consecutive items) reduced, the tile sums scanned by
 // one workgroup, the tiles scanned again with their prefix.  out[len] = total.
 // ---------------------------------------------------------------------------
@@ -140,8 +186,10 @@ __global__ __launch_bounds__(256) void scan_reduce_kernel(const uint64_t *a, uin
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// in place over sums[0, nb); sums[nb] = total
-__global__ __launch_bounds__(1024) void scan_sums_kernel(uint64_t *sums, uint64_t nb)
+// in place over sums[0, nb); sums[nb] = total, and the edge total with the
+// overflow flag (the scans are of edge counts)
+__global__ __launch_bounds__(1024) void scan_sums_kernel(uint64_t *sums, uint64_t nb, uint64_t *status,
+                                                         uint64_t capacity, uint64_t *out_total)
 {
     __shared__ uint64_t s_w[16];
     const uint32_t t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -162,7 +210,12 @@ __global__ __launch_bounds__(1024) void scan_sums_kernel(uint64_t *sums, uint64_
         carry += total;
         __syncthreads();
     }
-    if (t == 0) sums[nb] = carry;
+    if (t == 0) {
+        sums[nb] = carry;
+        status[0] = carry;
+        status[1] = carry > capacity ? 1 : 0;
+        if (out_total) *out_total = carry;
+    }
 }
 
 __global__ __launch_bounds__(256) void scan_apply_kernel(const uint64_t *a, uint64_t len, const uint64_t *sums,
@@ -498,16 +551,6 @@ __global__ __launch_bounds__(64) void rgg_edges_kernel(RggJob J)
         __syncthreads();
         for (uint64_t i = threadIdx.x; i < wtotal; i += 64) J.edges[o + i] = s_e[i];
     }
-}
-
-// The total, the overflow flag and the caller's copy of the total.
-__global__ __launch_bounds__(64) void rgg_total_kernel(RggJob J, uint64_t nw)
-{
-    if (threadIdx.x != 0) return;
-    const uint64_t E = J.woff[nw];
-    J.status[0] = E;
-    J.status[1] = E > J.capacity ? 1 : 0;
-    if (J.out_total) *J.out_total = E;
 }
 
 }  // namespace kg

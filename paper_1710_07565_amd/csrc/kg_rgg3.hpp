@@ -37,7 +37,6 @@ struct Rgg3Job {
     double r2, h;              // r * r, cell side 2^-L
     uint32_t L, G;             // level, cells per side
     uint64_t C;                // cells
-    uint64_t *tree;            // node counts, level l at (8^l - 1) / 7, Morton order
     uint64_t *coff;            // C + 1 first vertex id of every cell
     uint32_t *pcell;           // n: cell of every vertex
     uint32_t *ecnt;            // n: edges (u, v > u) of every vertex u; top bit: more candidates than recorded
@@ -52,8 +51,6 @@ struct Rgg3Job {
     double *pts;               // 3 n: x, y, z of every vertex
     uint2 *edges;
 };
-
-__device__ __forceinline__ uint64_t rgg3_level_base(uint32_t l) { return ((1ull << (3 * l)) - 1) / 7; }
 
 // Morton index <-> cell coordinates (L <= 10, so 30 bits): every third bit
 __device__ __forceinline__ uint32_t spread3(uint32_t x)
@@ -74,31 +71,6 @@ __device__ __forceinline__ uint32_t gather3(uint32_t z)
     z = (z | (z >> 8)) & 0x030000FFu;
     z = (z | (z >> 16)) & 0x3FFu;
     return z;
-}
-
-__global__ __launch_bounds__(64) void rgg3_root_kernel(Rgg3Job J)
-{
-    if (threadIdx.x == 0) J.tree[0] = J.n;
-}
-
-// One level of the octant recursion: lane per node of level l.
-__global__ __launch_bounds__(64) void rgg3_split_kernel(Rgg3Job J, uint32_t l)
-{
-    const uint64_t z = (uint64_t)blockIdx.x * 64 + threadIdx.x;
-    if (z >= (1ull << (3 * l))) return;
-    const uint64_t k = J.tree[rgg3_level_base(l) + z];
-    const uint32_t a = (uint32_t)z, b = 7 * l;
-    const uint64_t lz = binom(make_stream(J.seed, a, b + 0, TAG_RTREE3), k, 0.5);
-    const uint64_t y0 = binom(make_stream(J.seed, a, b + 1, TAG_RTREE3), lz, 0.5);
-    const uint64_t y1 = binom(make_stream(J.seed, a, b + 2, TAG_RTREE3), k - lz, 0.5);
-    const uint64_t quarter[4] = {y0, lz - y0, y1, k - lz - y1};     // (y, z) = 00, 10, 01, 11
-    uint64_t *ch = J.tree + rgg3_level_base(l + 1) + 8 * z;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint64_t x0 = binom(make_stream(J.seed, a, b + 3 + (uint32_t)i, TAG_RTREE3), quarter[i], 0.5);
-        ch[2 * i] = x0;
-        ch[2 * i + 1] = quarter[i] - x0;
-    }
 }
 
 // Points: a wave per 64 consecutive cells, lane per point (as in two
@@ -323,16 +295,6 @@ __global__ __launch_bounds__(64) void rgg3_edges_kernel(Rgg3Job J)
         __syncthreads();
         for (uint64_t i = lane; i < wtotal; i += 64) J.edges[o + i] = s_e[i];
     }
-}
-
-// The total, the overflow flag and the caller's copy of the total.
-__global__ __launch_bounds__(64) void rgg3_total_kernel(Rgg3Job J, uint64_t nw)
-{
-    if (threadIdx.x != 0) return;
-    const uint64_t E = J.woff[nw];
-    J.status[0] = E;
-    J.status[1] = E > J.capacity ? 1 : 0;
-    if (J.out_total) *J.out_total = E;
 }
 
 }  // namespace kg
