@@ -159,10 +159,12 @@ struct Draws64 {
     }
 };
 
-// Top 52 bits plus half an ulp: exact, strictly inside (0, 1).
+// Top 52 bits plus half an ulp, (a + 1/2) 2^-52: exact, strictly inside
+// (0, 1).  The bits are placed as the fraction of a number in [1, 2); both
+// additions are exact.
 __device__ __forceinline__ double unit_of(uint64_t x)
 {
-    return ((double)(x >> 12) + 0.5) * 0x1p-52;
+    return (__longlong_as_double((long long)((x >> 12) | 0x3FF0000000000000ull)) - 1.0) + 0x1p-53;
 }
 
 // Uniform integer in [0, R) by power-of-two mask and rejection.
@@ -281,12 +283,11 @@ __device__ __forceinline__ double lnf_diff(uint64_t x, uint64_t y)
 }
 
 // floor(a * b / d) for a*b < 2^117, d >= 1 and a quotient below 2^53,
-// exactly: an estimate in binary64 (off by a few), corrected by the remainder.
+// exactly: an estimate `est` (off by a few), corrected by the remainder.
 // Below d = 2^60 the remainder of the estimate fits a signed 64-bit word, so
 // the products are needed modulo 2^64 only.
-__device__ __forceinline__ uint64_t muldiv_floor(uint64_t a, uint64_t b, uint64_t d)
+__device__ __forceinline__ uint64_t muldiv_floor(uint64_t a, uint64_t b, uint64_t d, double est)
 {
-    const double est = floor(((double)a * (double)b) / (double)d);
     uint64_t q = est <= 0.0 ? 0ull : (uint64_t)est;
     if (d < (1ull << 60)) {
         int64_t r = (int64_t)(a * b - q * d);
@@ -393,11 +394,11 @@ struct RouQuick {
         if (!(most <= 1.0f / 16.0f && fabsf(q) <= 1.0f / 16.0f)) iy[0] = 1e30f;   // every t is out of range
     }
 
-    // 1: accepted, 0: rejected, -1: too close to say.  X = M + d64 is in
+    // 1: accepted, 0: rejected, -1: too close to say.  X = M + dd is in
     // range, so every A_i + d is at least 0 and every t above -1.
-    __device__ __forceinline__ int decide(int64_t d64, double U) const
+    __device__ __forceinline__ int decide(double dd, double U) const
     {
-        const float d = (float)d64;
+        const float d = (float)dd;
         // 2 ln U; the hardware's base-2 logarithm is good to 1 ulp
         const float lu = 1.3862943611f * __builtin_amdgcn_logf((float)U);
         float most = iy[0];
@@ -446,35 +447,45 @@ __device__ __forceinline__ bool rou_accept(const Ratio &ratio, uint64_t X, doubl
     return 2.0 * log_f64(U) <= T;
 }
 
-// Proposal j of a variate: accepted or not, and its X.
+// Proposal j of a variate: accepted or not, and its X (a whole number).
+// Md is the mode, excl = upper + 1.
 template <class Ratio, class Quick>
-__device__ __forceinline__ bool rou_try(const Stream &s, uint32_t j, double a, double h, uint64_t upper,
-                                        const Ratio &ratio, const Quick &quick, uint64_t &X)
+__device__ __forceinline__ bool rou_try(const Stream &s, uint32_t j, double a, double h, uint64_t upper, double excl,
+                                        double Md, const Ratio &ratio, const Quick &quick, double &X)
 {
     const U4 w = s.block(j);
     const double U = unit_of(((uint64_t)w.y << 32) | w.x);
     const double V = unit_of(((uint64_t)w.w << 32) | w.z);
     const double t = a + h * (V - 0.5) / U;
-    if (!(t >= 0.0 && t < (double)upper + 1.0)) return false;
-    X = (uint64_t)floor(t);
-    if (X > upper) return false;           // upper + 1 rounds in binary64 above 2^53
-    const int dec = quick.decide((int64_t)(X - ratio.M), U);
-    return __builtin_expect(dec < 0, 0) ? rou_accept(ratio, X, U) : dec != 0;
+    if (!(t >= 0.0 && t < excl)) return false;
+    X = floor(t);
+    if (upper >> 53 && (uint64_t)X > upper) return false;      // upper + 1 rounds in binary64
+    const int dec = quick.decide(X - Md, U);
+    return __builtin_expect(dec < 0, 0) ? rou_accept(ratio, (uint64_t)X, U) : dec != 0;
 }
 
 // Aligned groups of PAR lanes: the lowest lane of the caller's group with
 // `acc` set decides; its X to the whole group.  False when no lane has it.
 template <int PAR>
-__device__ __forceinline__ bool group_first(bool acc, uint64_t &X)
+__device__ __forceinline__ bool group_first(bool acc, double &X)
 {
-    const uint32_t lane = __lane_id();
-    const uint32_t base = lane & ~(uint32_t)(PAR - 1);
-    const uint32_t won = (uint32_t)(__ballot(acc) >> base) & (uint32_t)((1ull << PAR) - 1);
-    if (!won) return false;
-    const int src = (int)(base + __builtin_ctz(won));
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)X, src);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(X >> 32), src);
-    X = ((uint64_t)hi << 32) | lo;
+    const uint64_t all = __ballot(acc);
+    const uint64_t bits = (uint64_t)__double_as_longlong(X);
+    uint32_t lo, hi;
+    if (PAR == 64) {
+        if (!all) return false;
+        const int src = __builtin_ctzll(all);
+        lo = __builtin_amdgcn_readlane((uint32_t)bits, src);
+        hi = __builtin_amdgcn_readlane((uint32_t)(bits >> 32), src);
+    } else {
+        const uint32_t base = __lane_id() & ~(uint32_t)(PAR - 1);
+        const uint32_t won = (uint32_t)(all >> base) & (uint32_t)((1ull << (PAR & 63)) - 1);
+        if (!won) return false;
+        const int src = (int)(base + __builtin_ctz(won));
+        lo = (uint32_t)__shfl((int)(uint32_t)bits, src);
+        hi = (uint32_t)__shfl((int)(uint32_t)(bits >> 32), src);
+    }
+    X = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
     return true;
 }
 
@@ -484,39 +495,48 @@ __device__ __forceinline__ bool group_first(bool acc, uint64_t &X)
 // so the variate is the one the sequential loop returns.  Used where a
 // variate's latency, not the lanes' throughput, bounds a kernel.
 template <int PAR, class Ratio, class Quick>
-__device__ __forceinline__ uint64_t rou_sample(const Stream &s, double a, double h, uint64_t upper,
+__device__ __forceinline__ uint64_t rou_sample(const Stream &s, double a, double h, uint64_t upper, double Md,
                                                const Ratio &ratio, const Quick &quick)
 {
-    static_assert(PAR >= 1 && PAR <= 16 && (PAR & (PAR - 1)) == 0, "1, 2, 4, 8 or 16 proposals at once");
+    static_assert(PAR == 1 || PAR == 2 || PAR == 4 || PAR == 8 || PAR == 64, "lanes per variate");
     const uint32_t q = __lane_id() & (PAR - 1);
+    const double excl = (double)upper + 1.0;
     for (uint32_t j0 = 0;; j0 += PAR) {
-        uint64_t X = 0;
-        const bool acc = rou_try(s, j0 + q, a, h, upper, ratio, quick, X);
-        if (PAR == 1) {
-            if (acc) return X;
-        } else if (group_first<PAR>(acc, X)) {
-            return X;
-        }
+        double X = 0.0;
+        const bool acc = rou_try(s, j0 + q, a, h, upper, excl, Md, ratio, quick, X);
+        if (PAR == 1 ? acc : group_first<PAR>(acc, X)) return (uint64_t)X;
     }
 }
 
 // The quick test's arguments of HYP(N, K, k) and BIN(N, p).
-__device__ __forceinline__ RouQuick<4> quick_of(const HypRatio &r)
+// (The differences of the binary64 values are exact or lose nothing that
+// matters: k and M are below 2^53, and M is at most half of K.)
+__device__ __forceinline__ RouQuick<4> quick_of(const HypRatio &r, double Kd, double kd, double Md)
 {
-    const double y1 = (double)r.M + 0.5, y2 = (double)(r.k - r.M) + 0.5, y3 = (double)(r.K - r.M) + 0.5;
+    const double y1 = Md + 0.5, y2 = (kd - Md) + 0.5, y3 = (Kd - Md) + 0.5;
     const double y4 = (double)(r.N - r.K - r.k + r.M) + 0.5;
     RouQuick<4> q;
     const double den = y2 * y3;
     q.init({y1, y2, y3, y4}, y1 * y4 - den, den);
     return q;
 }
-__device__ __forceinline__ RouQuick<2> quick_of(const BinRatio &r)
+__device__ __forceinline__ RouQuick<2> quick_of(const BinRatio &r, double Nd, double Md)
 {
-    const double y1 = (double)r.M + 0.5, y2 = (double)(r.N - r.M) + 0.5;
+    const double y1 = Md + 0.5, y2 = (Nd - Md) + 0.5;
     RouQuick<2> q;
     const double den = y2 * r.p;
     q.init({y1, y2}, y1 * (1.0 - r.p) - den, den);
     return q;
+}
+
+// The mode floor((k + 1)(K + 1) / (N + 2)).
+__device__ __forceinline__ uint64_t hyp_mode(uint64_t N, uint64_t K, uint64_t k, double Nd, double Kd, double kd)
+{
+    // the quotient to about 2^-50: the hardware's reciprocal (2^-26), one step
+    const double d = Nd + 2.0;
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+    return muldiv_floor(k + 1, K + 1, N + 2, floor((kd + 1.0) * (Kd + 1.0) * r));
 }
 
 // Hypergeometric: how many of k draws without replacement from N items land
@@ -548,8 +568,9 @@ __device__ __forceinline__ uint64_t hyp(const Stream &s, uint64_t N, uint64_t K,
         const double c = sqrt(var + 0.5);
         const double h = kRouD1 * c + kRouD2;
         const double a = mu + 0.5;
-        const HypRatio r{N, hi, lo, muldiv_floor(lo + 1, hi + 1, N + 2)};
-        x = rou_sample<PAR>(s, a, h, lo, r, quick_of(r));
+        const HypRatio r{N, hi, lo, hyp_mode(N, hi, lo, Nd, Kd, kd)};
+        const double Md = (double)r.M;
+        x = rou_sample<PAR>(s, a, h, lo, Md, r, quick_of(r, Kd, kd, Md));
     }
     if (c2) x = k1 - x;
     if (c1) x = K - x;
@@ -564,7 +585,7 @@ struct HypRun {
     HypRatio r;           // r.K marked items, r.k draws, after the symmetries
     RouQuick<4> quick;
     uint64_t K, k1, x;
-    double a, h;
+    double a, h, Md, excl;
     uint32_t j;
     bool c1, c2, done;
 
@@ -599,8 +620,10 @@ struct HypRun {
             const double c = sqrt(var + 0.5);
             h = kRouD1 * c + kRouD2;
             a = mu + 0.5;
-            r.M = muldiv_floor(lo + 1, hi + 1, N + 2);
-            quick = quick_of(r);
+            r.M = hyp_mode(N, hi, lo, Nd, Kd, kd);
+            Md = (double)r.M;
+            excl = kd + 1.0;
+            quick = quick_of(r, Kd, kd, Md);
             done = false;
         }
     }
@@ -612,10 +635,10 @@ struct HypRun {
     __device__ __forceinline__ bool step()
     {
         if (done) return true;
-        uint64_t X = 0;
-        const bool acc = rou_try(s, j + (__lane_id() & (PAR - 1)), a, h, r.k, r, quick, X);
+        double X = 0.0;
+        const bool acc = rou_try(s, j + (__lane_id() & (PAR - 1)), a, h, r.k, excl, Md, r, quick, X);
         j += PAR;
-        if (PAR == 1 ? acc : group_first<PAR>(acc, X)) { x = X; done = true; }
+        if (PAR == 1 ? acc : group_first<PAR>(acc, X)) { x = (uint64_t)X; done = true; }
         return done;
     }
 
@@ -671,8 +694,9 @@ __device__ __forceinline__ uint64_t bin_core(const Stream &s, uint64_t N, double
     const double c = sqrt(var + 0.5);
     const double h = kRouD1 * c + kRouD2;
     const double a = mu + 0.5;
-    const BinRatio r{N, (uint64_t)floor((Nd + 1.0) * p), p};
-    return rou_sample<PAR>(s, a, h, N, r, quick_of(r));
+    const double Md = floor((Nd + 1.0) * p);
+    const BinRatio r{N, (uint64_t)Md, p};
+    return rou_sample<PAR>(s, a, h, N, Md, r, quick_of(r, Nd, Md));
 }
 
 template <int PAR = 1>
