@@ -18,6 +18,8 @@ struct Job {
     uint32_t leaf_cap;       // samples sorted per LDS pass, <= kCapMax
     uint32_t fast_cap;       // draws of the register base case (tile_kernel); larger tiles are queued
     uint32_t unit_log;       // planner units hold <= 2^unit_log tiles (launch shape only)
+    uint32_t counts_only;    // the chunk counts are wanted, not their offsets
+    uint32_t pad_;
     uint64_t G;              // chunks over all instances
     uint64_t capacity;       // output room in edges
     uint64_t tile_cap;       // tile_off has tile_cap + 1 entries
@@ -38,9 +40,13 @@ struct Job {
 
 constexpr int kCapMax = 1024;            // LDS sort capacity of a wave
 
-__device__ __forceinline__ const Inst &inst_at(const Job &job, uint32_t i)
+// (by value: the one instance's fields are kernel arguments, scalar loads)
+__device__ __forceinline__ Inst inst_at(const Job &job, uint32_t i)
 {
-    return job.ninst == 1 ? job.one : job.insts[i];
+    Inst I;
+    if (job.ninst == 1) I = job.one;
+    else I = job.insts[i];
+    return I;
 }
 
 // instance owning global chunk g: last i with chunk_base <= g
@@ -92,6 +98,20 @@ __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v)
     return v;
 }
 
+// The totals and the status words, once the offsets are known (one lane), and
+// the sampler's range counter.
+__device__ __forceinline__ void finish_offsets(const Job &job, uint64_t E, uint64_t T, uint64_t U)
+{
+    job.off[job.G] = E; job.tstart[job.G] = T; job.ustart[job.G] = U;
+    job.status[0] = E;
+    job.status[1] = (E > job.capacity || T > job.tile_cap) ? 1 : 0;
+    job.status[2] = T; job.status[3] = U;
+    job.status[4] = 0;
+    job.status[5] = 0;
+    if (T <= job.tile_cap) job.tile_off[T] = E;
+    if (job.out_total) *job.out_total = E;
+}
+
 // ---------------------------------------------------------------------------
 // count: a group of PAR lanes per chunk, a workgroup per 64 chunks.
 // The count of a chunk is a root path of dependent variates (Sec. 4.1, 4.2)
@@ -100,7 +120,9 @@ __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v)
 // variate at once (the first accepted proposal in proposal order
 // wins, so the counts are those of the one-proposal loop).  Writes the
 // chunk's edge count, tile count and planner-unit count, and the workgroup's
-// three sums to bsum (the first phase of the offset scan).
+// three sums to bsum (the first phase of the offset scan).  A job of one
+// workgroup (up to 64 chunks) gets its offsets and totals here, without the
+// scan's launches.
 // ---------------------------------------------------------------------------
 template <int PAR>
 __global__ __launch_bounds__(64 * PAR) void count_kernel(Job job)
@@ -113,7 +135,7 @@ __global__ __launch_bounds__(64 * PAR) void count_kernel(Job job)
     uint64_t cnt = 0, T = 0, Us = 0;
     if (g < job.G) {
         const uint32_t i = inst_of_chunk(job, g);
-        const Inst &I = inst_at(job, i);
+        const Inst I = inst_at(job, i);
         const uint64_t c = chunk_ordinal(I, g - I.chunk_base);
         const Chunk ch = chunk_geometry(I, c);
         if (I.model == 1) {
@@ -123,7 +145,7 @@ __global__ __launch_bounds__(64 * PAR) void count_kernel(Job job)
         }
         T = tiles_of(ch.N, I.s);
         Us = T ? (1ull << unit_depth(T, job.unit_log)) : 0;
-        if (lead) {
+        if (lead && (gridDim.x > 1 || job.counts_only)) {
             job.off[g] = cnt;
             job.tstart[g] = T;
             job.ustart[g] = Us;
@@ -137,6 +159,23 @@ __global__ __launch_bounds__(64 * PAR) void count_kernel(Job job)
         s_sum[wv][2] = su;
     }
     __syncthreads();
+    if (gridDim.x == 1 && !job.counts_only) {
+        uint64_t p[3] = {0, 0, 0}, all[3] = {0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < kCountWaves; ++w)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if ((uint32_t)w < wv) p[a] += s_sum[w][a];
+                all[a] += s_sum[w][a];
+            }
+        if (lead && g < job.G) {
+            job.off[g] = p[0] + sc - cnt;
+            job.tstart[g] = p[1] + st - T;
+            job.ustart[g] = p[2] + su - Us;
+        }
+        if (threadIdx.x == 0) finish_offsets(job, all[0], all[1], all[2]);
+        return;
+    }
     if (threadIdx.x < 3) {
         const uint32_t a = threadIdx.x;
         uint64_t t = 0;
@@ -210,16 +249,50 @@ __global__ __launch_bounds__(1024) void scan_kernel(Job job)
 #pragma unroll
             for (int i = 0; i < 4; ++i) cur[a][i] = nxt[a][i];
     }
-    if (t == 0) {
-        const uint64_t E = carry[0], T = carry[1], U = carry[2];
-        job.off[job.G] = E; job.tstart[job.G] = T; job.ustart[job.G] = U;
-        const uint64_t overflow = (E > job.capacity || T > job.tile_cap) ? 1 : 0;
-        job.status[0] = E; job.status[1] = overflow; job.status[2] = T; job.status[3] = U;
-        job.status[4] = 0;
-        job.status[5] = 0;
-        if (T <= job.tile_cap) job.tile_off[T] = E;
-        if (job.out_total) *job.out_total = E;
+    if (t == 0) finish_offsets(job, carry[0], carry[1], carry[2]);
+}
+
+// All three phases for up to 4096 chunks: one workgroup reads the chunks'
+// values, four consecutive ones per lane, and writes their offsets (one
+// launch of about 5 us instead of two).
+constexpr uint64_t kScanOne = 4096;
+
+__global__ __launch_bounds__(1024) void scan_one_kernel(Job job)
+{
+    __shared__ uint64_t s_wave[3][16];
+    const uint32_t t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint64_t *arr[3] = {job.off, job.tstart, job.ustart};
+    uint64_t v[3][4], run[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        uint64_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t g = 4 * (uint64_t)t + i;
+            v[a][i] = g < job.G ? arr[a][g] : 0;
+            sum += v[a][i];
+        }
+        const uint64_t incl = wave_incl_scan64(sum);
+        if (lane == 63) s_wave[a][wv] = incl;
+        run[a] = incl - sum;
     }
+    __syncthreads();
+    uint64_t all[3] = {0, 0, 0};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        for (uint32_t w = 0; w < 16; ++w) {
+            const uint64_t x = s_wave[a][w];
+            if (w < wv) run[a] += x;
+            all[a] += x;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t g = 4 * (uint64_t)t + i;
+            if (g < job.G) arr[a][g] = run[a];
+            run[a] += v[a][i];
+        }
+    }
+    if (t == 0) finish_offsets(job, all[0], all[1], all[2]);
 }
 
 // Third phase: exclusive offsets of every chunk (one wave per 64 chunks).
@@ -264,7 +337,7 @@ __global__ __launch_bounds__(256) void inst_offsets_kernel(Job job)
 constexpr int kPlanStack = 8;   // > depth of a unit subtree (6 for 64 tiles)
 
 template <int PAR>
-__global__ __launch_bounds__(64) void plan_kernel(Job job)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void plan_kernel(Job job)
 {
     __shared__ uint64_t st_k[kPlanStack][64];
     __shared__ uint32_t st_lo[kPlanStack][64], st_hi[kPlanStack][64], st_heap[kPlanStack][64];
@@ -292,7 +365,7 @@ __global__ __launch_bounds__(64) void plan_kernel(Job job)
     hr.done = true;
     if (active) {
         g = last_le(job.ustart, job.G, u);
-        const Inst &I = inst_at(job, inst_of_chunk(job, g));
+        const Inst I = inst_at(job, inst_of_chunk(job, g));
         const uint64_t cc = chunk_ordinal(I, g - I.chunk_base);
         const Chunk ch = chunk_geometry(I, cc);
         seed = I.seed; c = (uint32_t)cc; s = I.s; Nc = ch.N;
@@ -317,7 +390,7 @@ __global__ __launch_bounds__(64) void plan_kernel(Job job)
                         active = false;
                     } else {
                         while (job.ustart[g + 1] <= u) ++g;
-                        const Inst &I = inst_at(job, inst_of_chunk(job, g));
+                        const Inst I = inst_at(job, inst_of_chunk(job, g));
                         const uint64_t cc = chunk_ordinal(I, g - I.chunk_base);
                         const Chunk ch = chunk_geometry(I, cc);
                         seed = I.seed; c = (uint32_t)cc; s = I.s; Nc = ch.N;

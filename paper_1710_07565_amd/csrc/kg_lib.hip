@@ -36,6 +36,11 @@ namespace {
 typedef unsigned __int128 u128;
 
 constexpr uint32_t kSpecVersion = 1;
+// Tiles per compute unit up to which a wave per tile walks the tile tree by
+// itself (tile_one_kernel): calls of 2^16 vertices and degree 16 take 35 us so
+// and 44 with the planner, of 2^17 42 and 47, of 2^18 (17 tiles) 64 and 53: the
+// wave repeats its path in every lane, which only a chip with idle issue slots hides.
+constexpr uint64_t kOneTiles = 9;
 constexpr uint64_t kMaxChunks = 1ull << 36;   // chunks of one call (a batch: all instances)
 
 // Non-semantic knobs.
@@ -386,9 +391,12 @@ Job make_job(const Prepared &P, const Workspace &ws, uint32_t *edges, uint64_t c
 }
 
 // The count kernel's lanes per chunk: its time is the latency of each
-// chunk's chain of variates, so a chunk gets as many lanes (8, 4, then 2) as
+// chunk's chain of variates, so a chunk gets as many lanes (4, then 2) as
 // keep every workgroup of the launch resident at once; a launch too large
-// for that takes one lane per chunk (the least work per variate).  Launch
+// for that takes one lane per chunk (the least work per variate).  Eight
+// lanes, two waves on each SIMD of a workgroup's compute unit, are slower
+// (2^16 vertices in 64 chunks 41.7 us a call against 37.2 with four lanes, the
+// view of 256 chunks 109.5 against 100.1) and are left to the option.  Launch
 // shape only: the counts are the same for every choice.
 void launch_count(const Job &job, uint64_t nb, int dev, hipStream_t s)
 {
@@ -397,7 +405,7 @@ void launch_count(const Job &job, uint64_t nb, int dev, hipStream_t s)
         v = g_count_lanes == 8 ? 3 : g_count_lanes == 4 ? 2 : g_count_lanes == 2 ? 1 : 0;
     } else {
         const uint64_t cu = (uint64_t)g_num_cu[dev];
-        for (int c = kCountVariants - 1; c >= 1; --c)
+        for (int c = 2; c >= 1; --c)
             if (nb <= cu * (uint64_t)g_count_blocks_per_cu[dev][c]) { v = c; break; }
     }
     if (v == 3) hipLaunchKernelGGL(count_kernel<8>, dim3((uint32_t)nb), dim3(512), 0, s, job);
@@ -422,8 +430,14 @@ kg_status launch_counts(const Prepared &P, Job &job, int dev, hipStream_t s, boo
     }
     {
         KernelTimer tm(KG_KERNEL_SCAN, s);
-        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, job);
-        hipLaunchKernelGGL(fix_kernel, dim3((uint32_t)nb), dim3(64), 0, s, job);
+        if (nb == 1) {
+            // the count kernel's one workgroup has written the offsets
+        } else if (P.G <= kScanOne) {
+            hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, s, job);
+        } else {
+            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, job);
+            hipLaunchKernelGGL(fix_kernel, dim3((uint32_t)nb), dim3(64), 0, s, job);
+        }
     }
     if (job.inst_off)
         hipLaunchKernelGGL(inst_offsets_kernel, dim3((job.ninst + 1 + 255) / 256), dim3(256), 0, s, job);
@@ -433,6 +447,12 @@ kg_status launch_counts(const Prepared &P, Job &job, int dev, hipStream_t s, boo
 kg_status launch_generate(const Prepared &P, Job &job, int dev, hipStream_t s)
 {
     const int64_t cu = g_num_cu[dev];
+    // small jobs: at most kOneTiles tiles per compute unit, a workgroup each
+    if (P.Tb <= (uint64_t)cu * kOneTiles) {
+        KernelTimer tm(KG_KERNEL_SAMPLE, s);
+        hipLaunchKernelGGL(tile_one_kernel, dim3((uint32_t)P.Tb), dim3(64), 0, s, job);
+        return launched_ok() ? KG_OK : KG_EDEVICE;
+    }
     // planner units: at most 2 per 2^unit_log tiles plus one per chunk; one lane each
     const uint64_t ub = 2 * (P.Tb >> job.unit_log) + P.G + 1;
     uint64_t pgrid = (uint64_t)(cu * opt_or(g_plan_waves, g_plan_blocks_per_cu[dev]));
@@ -492,6 +512,7 @@ kg_status run(const kg_instance *inst, uint32_t count, uint32_t *edges, uint64_t
     if (d_counts) {
         // counts only: run the count kernel and copy the per-chunk counts out
         const uint64_t nb = (P.G + 63) / 64;
+        job.counts_only = 1;
         launch_count(job, nb, dev, s);
         if (!launched_ok()) st = KG_EDEVICE;
         else if (hipMemcpyAsync(d_counts, job.off, P.G * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)

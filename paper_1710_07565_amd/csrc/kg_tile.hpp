@@ -180,6 +180,22 @@ struct TileWalk {
     // the chunk of tile t, entered
     __device__ __forceinline__ void locate(const Job &job, uint64_t t) { enter(job, chunk_of_tile(job, t)); }
 
+    // stream counter and decoder at tile t of the current chunk, from which
+    // tiles advance by 2^s slots; returns the slots of the chunk's last tile
+    // (0: 2^32)
+    __device__ __forceinline__ uint32_t place(uint64_t t)
+    {
+        Decoder &d = tc.dec;
+        tc.st.b = uni((uint32_t)(t - gstart));
+        d.lbase = (t - gstart) << s;
+        if (d.type != 2) {
+            const uint64_t q = div_est(d.lbase, d.dv, d.rcp);
+            d.c0 = uni((uint32_t)(d.lbase - q * d.dv));
+            d.r0 = uni(row0 + (uint32_t)q);
+        }
+        return (uint32_t)(N - ((gend - 1 - gstart) << s));
+    }
+
     // slot count, stream counter and decoding constants of tile t (of the
     // current chunk)
     __device__ __forceinline__ void tile(uint64_t t)
@@ -761,6 +777,45 @@ __device__ __forceinline__ void emit_tile(const TileCtx &t, const uint32_t *s, u
     }
 }
 
+// Slots of the tile whose stream and decoder the context holds, and its edges:
+// `last_S` slots if it is the chunk's `last` tile (0: 2^32), else 2^s.
+__device__ __forceinline__ bool sample_tile(TileCtx &tc, uint32_t *s_key, uint32_t *s_cnt, uint64_t o0, uint64_t k,
+                                            uint32_t s, bool last, uint32_t last_S, uint32_t fast_cap)
+{
+    Decoder &d = tc.dec;
+    tc.S = 1ull << s;
+    tc.bits = s;
+    tc.full = 1;
+    if (last && last_S != (uint32_t)tc.S) {
+        tc.S = last_S;
+        tc.bits = uni(last_S <= 1 ? 0 : 32 - __clz(last_S - 1));
+        tc.full = uni(tc.S == (1ull << tc.bits));
+    }
+    tc.mask = (uint32_t)((1ull << tc.bits) - 1);
+    d.wide = s == 32 ? uni((uint64_t)d.c0 + tc.S > (1ull << 32)) : 0u;
+    tc.o0 = o0;
+    const uint32_t lim = fast_cap < kFastDraws ? fast_cap : kFastDraws;
+    const bool comp = 2 * k > tc.S;
+    const uint64_t ke = comp ? tc.S - k : k;
+    if (ke == 0) {
+        emit_complement(tc, s_key, 0, 0, tc.S, 0);
+    } else if (ke <= lim && fast_set(tc, s_key, s_cnt, (uint32_t)ke, lim)) {
+        if (!comp) emit_tile(tc, s_key, (uint32_t)ke);
+        else emit_complement(tc, s_key, (uint32_t)ke, 0, tc.S, 0);
+    } else {
+        return false;
+    }
+    return true;
+}
+
+__device__ __forceinline__ void clear_counters(uint32_t *s_cnt)
+{
+    uint4 *cw = reinterpret_cast<uint4 *>(s_cnt) + 2 * threadIdx.x;
+    cw[0] = make_uint4(0, 0, 0, 0);
+    cw[1] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+}
+
 // 4 waves per SIMD (up to 128 VGPRs, no spills); the LDS of a wave (keys of
 // up to 1280 draws and 512 bucket counters, 7.2 KB) would allow 5
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void tile_kernel(Job job)
@@ -768,12 +823,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];   // bucket counters, then starts
     if (ld_uni(job.status + 1)) return;
-    {
-        uint4 *cw = reinterpret_cast<uint4 *>(s_cnt) + 2 * threadIdx.x;
-        cw[0] = make_uint4(0, 0, 0, 0);
-        cw[1] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-    }
+    clear_counters(s_cnt);
     TileWalk w;
     TileCtx &tc = w.tc;
     Decoder &d = tc.dec;
@@ -792,17 +842,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             w.enter(job, g);
             const uint32_t s = w.s;
             // tiles of the range in this chunk; after `full` of them comes the
-            // chunk's last tile, of last_S slots (0: 2^32)
+            // chunk's last tile
             const uint64_t tend = w.gend < t1 ? w.gend : t1;
             const uint32_t count = (uint32_t)(tend - t), full = (uint32_t)(w.gend - 1 - t);
-            const uint32_t last_S = (uint32_t)(w.N - ((w.gend - 1 - w.gstart) << s));
-            tc.st.b = uni((uint32_t)(t - w.gstart));
-            d.lbase = (t - w.gstart) << s;
-            if (d.type != 2) {
-                const uint64_t q = div_est(d.lbase, d.dv, d.rcp);
-                d.c0 = uni((uint32_t)(d.lbase - q * d.dv));
-                d.r0 = uni(w.row0 + (uint32_t)q);
-            }
+            const uint32_t last_S = w.place(t);
             const uint32_t qs32 = (uint32_t)w.qs;
             for (uint32_t i = 0; i < count; ++i) {
                 const uint64_t o0 = o_next;
@@ -810,27 +853,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 o_pre = ld_uni(job.tile_off + t + i + 2);
                 const uint64_t k = o_next - o0;
                 if (k != 0) {
-                    // slots of the tile: 2^s except for the chunk's last tile
-                    tc.S = 1ull << s;
-                    tc.bits = s;
-                    tc.full = 1;
-                    if (i == full && last_S != (uint32_t)tc.S) {
-                        tc.S = last_S;
-                        tc.bits = uni(last_S <= 1 ? 0 : 32 - __clz(last_S - 1));
-                        tc.full = uni(tc.S == (1ull << tc.bits));
-                    }
-                    tc.mask = (uint32_t)((1ull << tc.bits) - 1);
-                    d.wide = s == 32 ? uni((uint64_t)d.c0 + tc.S > (1ull << 32)) : 0u;
-                    tc.o0 = o0;
-                    const uint32_t lim = job.fast_cap < kFastDraws ? job.fast_cap : kFastDraws;
-                    const bool comp = 2 * k > tc.S;
-                    const uint64_t ke = comp ? tc.S - k : k;
-                    if (ke == 0) {
-                        emit_complement(tc, s_key, 0, 0, tc.S, 0);
-                    } else if (ke <= lim && fast_set(tc, s_key, s_cnt, (uint32_t)ke, lim)) {
-                        if (!comp) emit_tile(tc, s_key, (uint32_t)ke);
-                        else emit_complement(tc, s_key, (uint32_t)ke, 0, tc.S, 0);
-                    } else if (threadIdx.x == 0) {
+                    if (!sample_tile(tc, s_key, s_cnt, o0, k, s, i == full, last_S, job.fast_cap) && threadIdx.x == 0) {
                         const uint64_t q = atomicAdd((unsigned long long *)(job.status + 4), 1ull);
                         job.queue[q] = t + i;
                     }
@@ -852,6 +875,41 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             ++g;
             while (ld_uni(job.tstart + g + 1) <= t) ++g;
         }
+    }
+}
+
+// The sampler of small jobs (at most a tile per workgroup): the wave walks
+// the tile tree's path to its tile itself, 64 proposals of each variate at
+// once, and takes the general base case where the register one does not do,
+// so the job needs neither the planner's nor the queue's launch.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void tile_one_kernel(Job job)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[kCapMax + 8];
+    const uint64_t t = blockIdx.x;
+    if (ld_uni(job.status + 1) || t >= ld_uni(job.status + 2)) return;
+    clear_counters(s_cnt);
+    TileWalk w;
+    TileCtx &tc = w.tc;
+    tc.edges = job.edges;
+    const uint64_t g = chunk_of_tile(job, t);
+    w.enter(job, g);
+    const uint32_t last_S = w.place(t);
+    uint64_t o0 = ld_uni(job.off + g), k = ld_uni(job.off + g + 1) - o0;
+    const uint32_t tl = tc.st.b;
+    uint32_t lo = 0, hi = (uint32_t)(w.gend - w.gstart), heap = 1;
+    while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo + 1) / 2;
+        const uint64_t X = uni64(hyp<64>(Stream{tc.st.k0, tc.st.k1, tc.st.a, heap, TAG_TTREE},
+                                         tile_range_slots(lo, hi, w.s, w.N), tile_range_slots(lo, mid, w.s, w.N), k));
+        if (tl < mid) { hi = mid; k = X; heap = 2 * heap; }
+        else { lo = mid; o0 += X; k -= X; heap = 2 * heap + 1; }
+    }
+    if (k == 0) return;
+    if (!sample_tile(tc, s_key, s_cnt, o0, k, w.s, t + 1 == w.gend, last_S, job.fast_cap)) {
+        __syncthreads();
+        leaf_sample<kCapMax>(tc, s_key, s_hist, k, job.leaf_cap < kCapMax ? job.leaf_cap : kCapMax);
     }
 }
 
