@@ -73,6 +73,21 @@ __device__ __forceinline__ uint64_t last_le(const uint64_t *a, uint64_t G, uint6
 }
 
 // ---------------------------------------------------------------------------
+// Table of the skip sampler's quick logarithm: for m in the i-th of 256 equal
+// parts of [1/2, 1), the reciprocal of the part's centre and its logarithm's
+// negative.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kGapTab = 256;
+extern __device__ double2 g_gap_tab[kGapTab];
+
+__global__ void gap_init_kernel()
+{
+    const double c = 0.5 + ((double)threadIdx.x + 0.5) / (2.0 * kGapTab);
+    const double r = 1.0 / c;
+    g_gap_tab[threadIdx.x] = make_double2(r, -log_f64(r));
+}
+
+// ---------------------------------------------------------------------------
 // lnf table: T[0] = 0, T[k] = T[k-1] + log k (sequential, one lane).
 // ---------------------------------------------------------------------------
 __global__ void lnf_init_kernel()
@@ -86,15 +101,27 @@ __global__ void lnf_init_kernel()
     }
 }
 
-// Inclusive sum over the 64 lanes of a wave (shuffles up by 1, 2, ..., 32).
+// One step of the wave scans: the value of another lane by DPP, 0 for lanes
+// without one.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_or_zero64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Inclusive sum over the 64 lanes of a wave: shifts by 1, 2, 4 and 8 inside
+// rows of 16 lanes, then the last lane of row 0 / 2 to row 1 / 3 and the last
+// lane of row 1 to rows 2 and 3 (no LDS, unlike shuffles).  All lanes active.
 __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v)
 {
-    const uint32_t lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint64_t o = __shfl_up(v, d, 64);
-        if (lane >= (uint32_t)d) v += o;
-    }
+    v += dpp_or_zero64<0x111, 0xF>(v);   // row_shr:1
+    v += dpp_or_zero64<0x112, 0xF>(v);   // row_shr:2
+    v += dpp_or_zero64<0x114, 0xF>(v);   // row_shr:4
+    v += dpp_or_zero64<0x118, 0xF>(v);   // row_shr:8
+    v += dpp_or_zero64<0x142, 0xA>(v);   // row_bcast:15
+    v += dpp_or_zero64<0x143, 0xC>(v);   // row_bcast:31
     return v;
 }
 

@@ -21,6 +21,7 @@
 
 namespace kg {
 __device__ double g_lnf_tab[kLnfTab + 1];
+__device__ double2 g_gap_tab[kGapTab];
 }
 
 // Static scratch of kg_gnm_static (KG_STATIC_SCRATCH_BYTES, kg.h): the
@@ -197,6 +198,7 @@ kg_status ensure_init(int *dev_out)
     if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp) return KG_EDEVICE;
     g_scratch_ptr[dev] = sp;
     hipLaunchKernelGGL(lnf_init_kernel, dim3(1), dim3(64), 0, 0);
+    hipLaunchKernelGGL(gap_init_kernel, dim3(1), dim3(kGapTab), 0, 0);
     if (!launched_ok()) return KG_EDEVICE;
     if (hipDeviceSynchronize() != hipSuccess) return KG_EDEVICE;
     g_init_done[dev] = true;

@@ -167,46 +167,113 @@ constexpr uint32_t kSkipKeys = 1408;   // LDS batch (11 rounds of 128 events)
 // events (tile-local, counted from `pos`), whether they fall below S, how
 // many of the round's 128 events do (they are a prefix in lane order), and
 // the wave's inclusive sum of the advances for the next round's `pos`.
+// `next` holds only where all 128 do.
 struct SkipRound {
     uint64_t x0, x1, next;
     bool v0, v1;
     uint32_t nv;
 };
 
-__device__ __forceinline__ SkipRound skip_round(const TileCtx &tc, uint32_t r, uint64_t pos, double L)
+// Inclusive sum over the wave's lanes that stays at 2^32 - 1 once it reaches it.
+__device__ __forceinline__ uint32_t wave_incl_scan_sat(uint32_t v)
+{
+    v = __builtin_elementwise_add_sat(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));
+    v = __builtin_elementwise_add_sat(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false));
+    v = __builtin_elementwise_add_sat(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false));
+    v = __builtin_elementwise_add_sat(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false));
+    v = __builtin_elementwise_add_sat(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));
+    v = __builtin_elementwise_add_sat(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));
+    return v;
+}
+
+// The gap floor(log U / L), log U / L rounded as the project's binary64
+// routines round it.  Quick form (a table in LDS): log U = E ln 2 + log m with
+// m = c (1 + r), |r| < 2^-9, four terms of log(1 + r): off by less than 2^-46,
+// so the quotient is off by less than 2^-45 / |L| plus 2^-50 of itself (the
+// roundings on both sides).  Where a whole number is nearer than `open`
+// (2^-44 / |L| + 2^-49 S; about one gap in 10^5), the full form decides.
+// 18 binary64 operations and a 16-byte LDS read instead of about 60.  The gap
+// pass is bound by vector instructions; with this form, the sums below and
+// one 8-byte store a pair, directed n = 2^25, 536 million edges: 2204 ->
+// 1330 us (0.40 million gaps a microsecond), the call 3570 -> 2700 us.
+struct GapLaw {
+    double L, iL, open;
+    const double2 *tab;      // LDS copy of g_gap_tab, or null (full form only)
+
+    __device__ __forceinline__ double operator()(double U) const
+    {
+        if (tab) {
+            const double2 c = tab[(uint32_t)((uint64_t)__double_as_longlong(U) >> 44) & (kGapTab - 1)];
+            const double r = __builtin_fma(__builtin_amdgcn_frexp_mant(U), c.x, -1.0);
+            double q = __builtin_fma(r, -0.25, 1.0 / 3.0);
+            q = __builtin_fma(r, q, -0.5);
+            q = __builtin_fma(r * r, q, r);
+            const double e = (__builtin_fma((double)__builtin_amdgcn_frexp_exp(U), 0x1.62e42fefa39efp-1, c.y) + q) * iL;
+            const double f = floor(e);
+            if (__builtin_expect(fabs((e - f) - 0.5) < 0.5 - open, 1)) return f;
+        }
+        return floor(log_f64(U) / L);
+    }
+};
+
+__device__ __forceinline__ GapLaw gap_law(double L, uint32_t s, const double2 *tab)
+{
+    return GapLaw{L, 1.0 / L, 0x1p-44 / fabs(L) + (double)(1ull << s) * 0x1p-49, tab};
+}
+
+// The quick logarithm's table into LDS (one wave).
+__device__ __forceinline__ void load_gap_tab(double2 *tab)
+{
+    for (uint32_t i = threadIdx.x; i < kGapTab; i += 64) tab[i] = g_gap_tab[i];
+    __syncthreads();
+}
+
+__device__ __forceinline__ SkipRound skip_round(const TileCtx &tc, uint32_t r, uint64_t pos, const GapLaw &gap)
 {
     const uint32_t lane = threadIdx.x;
     const uint64_t S = tc.S;
     const U4 q = tc.st.block_uniform_key(64 * r + lane);
-    const double U0 = unit_of(((uint64_t)q.y << 32) | q.x);
-    const double U1 = unit_of(((uint64_t)q.w << 32) | q.z);
-    const double g0 = floor(log_f64(U0) / L), g1 = floor(log_f64(U1) / L);
+    const double g0 = gap(unit_of(((uint64_t)q.y << 32) | q.x)), g1 = gap(unit_of(((uint64_t)q.w << 32) | q.z));
+    // a gap of S or more ends the tile wherever it starts
     const double cap = (double)S;
-    const uint64_t a0 = (uint64_t)(g0 < cap ? g0 : cap) + 1;
-    const uint64_t a1 = (uint64_t)(g1 < cap ? g1 : cap) + 1;
-    const uint64_t sum = a0 + a1;
-    const uint64_t incl = wave_incl_scan64(sum);
+    const double c0 = g0 < cap ? g0 : cap, c1 = g1 < cap ? g1 : cap;
     SkipRound o;
-    o.x0 = pos + (incl - sum) + a0 - 1;
-    o.x1 = o.x0 + a1;
-    o.v0 = o.x0 < S;
-    o.v1 = o.x1 < S;
+    if (S <= (1ull << 31)) {
+        // 32-bit sums that stay at 2^32 - 1 once they reach it (past any S)
+        const uint32_t a0 = (uint32_t)c0 + 1, a1 = (uint32_t)c1 + 1, at = (uint32_t)pos;
+        const uint32_t incl = wave_incl_scan_sat(__builtin_elementwise_add_sat(a0, a1));
+        const uint32_t ex = __builtin_amdgcn_update_dpp(0, (int)incl, 0x138, 0xF, 0xF, false);   // wave_shr:1
+        const uint32_t x0 = __builtin_elementwise_add_sat(__builtin_elementwise_add_sat(at, ex), a0) - 1;
+        const uint32_t x1 = __builtin_elementwise_add_sat(at, incl) - 1;
+        o.x0 = x0;
+        o.x1 = x1;
+        o.v0 = x0 < (uint32_t)S;
+        o.v1 = x1 < (uint32_t)S;
+        o.next = at + __builtin_amdgcn_readlane(incl, 63);
+    } else {
+        const uint64_t a0 = (uint64_t)c0 + 1, a1 = (uint64_t)c1 + 1, sum = a0 + a1;
+        const uint64_t incl = wave_incl_scan64(sum);
+        o.x0 = pos + (incl - sum) + a0 - 1;
+        o.x1 = o.x0 + a1;
+        o.v0 = o.x0 < S;
+        o.v1 = o.x1 < S;
+        o.next = pos + (__builtin_amdgcn_readlane((uint32_t)incl, 63) |
+                        ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(incl >> 32), 63) << 32));
+    }
     o.nv = (uint32_t)(__popcll(__ballot(o.v0)) + __popcll(__ballot(o.v1)));
-    o.next = pos + (__builtin_amdgcn_readlane((uint32_t)incl, 63) |
-                    ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(incl >> 32), 63) << 32));
     return o;
 }
 
 // A tile's events generated and stored at output offset o0, in LDS batches
 // of up to kSkipKeys (for p > 1/2 the complement of the failures is stored).
-__device__ __forceinline__ void skip_write_tile(TileCtx &tc, uint32_t *s_key, uint64_t o0, bool flip, double L)
+__device__ __forceinline__ void skip_write_tile(TileCtx &tc, uint32_t *s_key, uint64_t o0, bool flip, const GapLaw &gap)
 {
     const uint32_t lane = threadIdx.x;
     const uint64_t S = tc.S;
     uint64_t pos = 0, rlo = 0, done = 0;
     uint32_t nb = 0;
     for (uint32_t r = 0;; ++r) {
-        const SkipRound R = skip_round(tc, r, pos, L);
+        const SkipRound R = skip_round(tc, r, pos, gap);
         if (nb + R.nv > kSkipKeys) {
             // batch full: out with it (a wave-uniform decision)
             __syncthreads();
@@ -247,7 +314,9 @@ __global__ __launch_bounds__(64) void skip_write_kernel(Job job)
     const double p = job.one.p;
     const bool flip = p > 0.5;
     const bool all = p >= 1.0;
-    const double L = log1p_f64(flip ? -(1.0 - p) : -p);
+    __shared__ double2 s_tab[kGapTab];
+    load_gap_tab(s_tab);
+    const GapLaw gap = gap_law(all ? -1.0 : log1p_f64(flip ? -(1.0 - p) : -p), job.one.s, s_tab);
     TileWalk w;
     TileCtx &tc = w.tc;
     tc.edges = job.edges;
@@ -266,7 +335,7 @@ __global__ __launch_bounds__(64) void skip_write_kernel(Job job)
                 tc.st.tag = TAG_SKIP;
                 tc.o0 = o0;
                 if (all) emit_complement(tc, s_key, 0, 0, tc.S, 0);
-                else skip_write_tile(tc, s_key, o0, flip, L);
+                else skip_write_tile(tc, s_key, o0, flip, gap);
             }
             if (t >= t1) break;
             ++g;
@@ -286,7 +355,9 @@ __global__ __launch_bounds__(64) void skip_gen_kernel(Job job, uint32_t *slab, u
     const double p = job.one.p;
     const bool flip = p > 0.5;
     const bool all = p >= 1.0;
-    const double L = all ? 0.0 : log1p_f64(flip ? -(1.0 - p) : -p);
+    __shared__ double2 s_tab[kGapTab];
+    load_gap_tab(s_tab);
+    const GapLaw gap = gap_law(all ? -1.0 : log1p_f64(flip ? -(1.0 - p) : -p), job.one.s, s_tab);
     const uint32_t lane = threadIdx.x;
     TileWalk w;
     TileCtx &tc = w.tc;
@@ -306,10 +377,12 @@ __global__ __launch_bounds__(64) void skip_gen_kernel(Job job, uint32_t *slab, u
                     uint32_t *row = slab + t * (uint64_t)cap;
                     uint64_t pos = 0;
                     for (uint32_t r = 0;; ++r) {
-                        const SkipRound R = skip_round(tc, r, pos, L);
+                        const SkipRound R = skip_round(tc, r, pos, gap);
+                        // i0 and cap are even: the pair fits or none of it
+                        // does; the row's end past its events is not read
                         const uint64_t i0 = nev + 2 * lane;
-                        if (R.v0 && i0 < cap) row[i0] = (uint32_t)R.x0;
-                        if (R.v1 && i0 + 1 < cap) row[i0 + 1] = (uint32_t)R.x1;
+                        if (R.v0 && i0 < cap)
+                            *reinterpret_cast<uint2 *>(row + i0) = make_uint2((uint32_t)R.x0, (uint32_t)R.x1);
                         nev += R.nv;
                         if (R.nv < 128) break;
                         pos = R.next;
@@ -336,7 +409,9 @@ __global__ __launch_bounds__(64) void skip_sums_kernel(Job job)
 }
 
 // Emission pass of the slab variant: each tile's stored positions through
-// LDS to the decoders (the complement of them for p > 1/2).
+// LDS to the decoders (the complement of them for p > 1/2).  Bound by memory:
+// 4 bytes read and 8 written per edge, 1.40 ms for 536 million edges
+// (4.6 TB/s, what a large copy reaches).
 __global__ __launch_bounds__(64) void skip_emit_kernel(Job job, const uint32_t *slab, uint32_t cap)
 {
     __shared__ __attribute__((aligned(16))) uint32_t s_key[kSkipKeys];
@@ -344,7 +419,8 @@ __global__ __launch_bounds__(64) void skip_emit_kernel(Job job, const uint32_t *
     const double p = job.one.p;
     const bool flip = p > 0.5;
     const bool all = p >= 1.0;
-    const double L = all ? 0.0 : log1p_f64(flip ? -(1.0 - p) : -p);
+    // (rarely used: no table)
+    const GapLaw gap = gap_law(all ? -1.0 : log1p_f64(flip ? -(1.0 - p) : -p), job.one.s, nullptr);
     const uint32_t lane = threadIdx.x;
     TileWalk w;
     TileCtx &tc = w.tc;
@@ -370,7 +446,7 @@ __global__ __launch_bounds__(64) void skip_emit_kernel(Job job, const uint32_t *
                 }
                 const uint64_t nev = flip ? S - k : k;
                 if (nev > cap) {
-                    skip_write_tile(tc, s_key, o0, flip, L);
+                    skip_write_tile(tc, s_key, o0, flip, gap);
                     continue;
                 }
                 // the row to LDS, 16 bytes per lane (rows start 16-byte
