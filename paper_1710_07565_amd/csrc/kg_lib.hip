@@ -568,9 +568,12 @@ uint32_t rgg_level(uint64_t n, double r)
 // so that a block's result words hold its candidates (at most 6, of 18, cells'
 // points) with four standard deviations to spare; denser grids keep a lane per
 // vertex, whose waves share the work of one cell.  A block is one cell, or
-// 2^D where a cell's points (below 8, 5) would leave too little to share the
-// window's set-up; from 10 points per cell in three dimensions on, the
-// candidates need 16 words per vertex.
+// 2^D where a cell's points would leave too little to share the window's
+// set-up: in two dimensions below 8; in three, where 16 points share a matrix
+// product, below 7.5 (n = 10.9 and 14.7 million, 5.2 and 7 points per cell: one
+// cell 2.15 and 2.40 ms, eight 1.22 and 2.27; at 8 points 2.55 and 2.98).  From
+// 5 points per cell in three dimensions on (10 with one cell), the candidates
+// need 16 words per vertex.
 struct RggBlocks {
     int B = -1;                // block level (cells of side 2^B); -1: not taken
     uint32_t words = 8, Q = 13, list = 0;      // result words per vertex, position bits, kept list words per block
@@ -582,8 +585,8 @@ RggBlocks rgg_blocks(int D, uint64_t n, uint32_t L)
     RggBlocks P;
     const double a = ldexp((double)n, -(int)(D * L));     // points per cell
     if (n == 0 || a > (D == 2 ? 32.0 : 22.0)) return P;
-    P.B = L >= 1 && a < (D == 2 ? 8.0 : 5.0) ? 1 : 0;
-    if (D == 3 && a >= 10.0) P.words = 16;
+    P.B = L >= 1 && a < (D == 2 ? 8.0 : 7.5) ? 1 : 0;
+    if (D == 3 && (P.B == 1 ? a >= 5.0 : a >= 10.0)) P.words = 16;
     if (D == 2 && P.B == 0) P.Q = 14;
     if (D == 3) P.list = P.B ? RggWindow<3, 1, 8>::LIST : RggWindow<3, 0, 8>::LIST;
     P.nb = (1ull << (D * L)) >> (D * P.B);
@@ -609,9 +612,18 @@ struct RggLayout {
     uint64_t mid, coff, pcell, ecnt, q, list, bits, wsum, woff, sums, status, total;
 };
 
-// Nodes of the last level but one launch's: two launches below depth 22, three
-// (of at most 10 levels) up to 30.
-constexpr uint64_t kSplitMid = (1ull << 20) + 32;
+// The split tree's launches (one up to depth 12, two up to 24, three up to 30)
+// take equally many levels each; between two launches the nodes' first vertices
+// are kept, in two buffers of this many words.
+uint32_t split_launches(uint32_t depth) { return depth ? (depth + kSplitMost - 1) / kSplitMost : 1; }
+
+uint64_t split_words(uint32_t depth)
+{
+    const uint32_t launches = split_launches(depth);
+    uint32_t p = 0;
+    for (uint32_t i = 0; i + 1 < launches; ++i) p += (depth - p) / (launches - i);
+    return launches > 1 ? (1ull << p) + 32 : 0;
+}
 
 // nw: the entries of the edge counts' scan (blocks, or waves of 64 vertices)
 RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
@@ -625,7 +637,7 @@ RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
     Y.nbw = Y.nw ? (Y.nw + kScanTile - 1) / kScanTile : 1;
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) { const uint64_t at = o; o += (bytes + 255) & ~255ull; return at; };
-    Y.mid = take(2 * kSplitMid * 8);
+    Y.mid = take(2 * split_words(D * L) * 8);
     Y.coff = take((Y.C + 1) * 8);
     Y.pcell = take(blk ? 0 : n * 4);
     Y.ecnt = take(blk ? 0 : n * 4);
@@ -642,13 +654,10 @@ RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
 
 RggLayout rgg_layout(uint64_t n, double r) { return rgg_layout_any(2, n, rgg_level(n, r)); }
 
-RggBlockJob rgg_block_job(int D, uint64_t n, double r, uint64_t capacity, const RggLayout &Y, char *ws,
-                          const double *pts, uint32_t *edges)
+RggBlockJob rgg_block_job(int D, double r, const RggLayout &Y, char *ws, const double *pts, uint32_t *edges)
 {
     RggBlockJob J;
     memset(&J, 0, sizeof(J));
-    J.n = n;
-    J.capacity = capacity;
     J.r2 = r * r;
     J.nb = Y.P.nb;
     J.G = 1u << Y.L;
@@ -669,11 +678,12 @@ RggBlockJob rgg_block_job(int D, uint64_t n, double r, uint64_t capacity, const 
 void rgg_block_count(int D, const RggBlocks &P, const RggBlockJob &J, hipStream_t s)
 {
     const dim3 grid((uint32_t)((P.nb + kBlocksPerWave - 1) / kBlocksPerWave)), wave(64);
-    if (D == 2 && P.B == 0) hipLaunchKernelGGL((rgg_block_count_kernel<2, 0, 8>), grid, wave, 0, s, J);
-    else if (D == 2) hipLaunchKernelGGL((rgg_block_count_kernel<2, 1, 8>), grid, wave, 0, s, J);
-    else if (P.B == 1) hipLaunchKernelGGL((rgg_block_count_kernel<3, 1, 8>), grid, wave, 0, s, J);
-    else if (P.words == 8) hipLaunchKernelGGL((rgg_block_count_kernel<3, 0, 8>), grid, wave, 0, s, J);
-    else hipLaunchKernelGGL((rgg_block_count_kernel<3, 0, 16>), grid, wave, 0, s, J);
+    if (D == 2 && P.B == 0) hipLaunchKernelGGL((rgg_block_count2_kernel<0, 8>), grid, wave, 0, s, J);
+    else if (D == 2) hipLaunchKernelGGL((rgg_block_count2_kernel<1, 8>), grid, wave, 0, s, J);
+    else if (P.B == 1 && P.words == 16) hipLaunchKernelGGL((rgg_block_count3_kernel<1, 16>), grid, wave, 0, s, J);
+    else if (P.B == 1) hipLaunchKernelGGL((rgg_block_count3_kernel<1, 8>), grid, wave, 0, s, J);
+    else if (P.words == 8) hipLaunchKernelGGL((rgg_block_count3_kernel<0, 8>), grid, wave, 0, s, J);
+    else hipLaunchKernelGGL((rgg_block_count3_kernel<0, 16>), grid, wave, 0, s, J);
 }
 
 void rgg_block_write(int D, const RggBlocks &P, const RggBlockJob &J, hipStream_t s)
@@ -681,6 +691,7 @@ void rgg_block_write(int D, const RggBlocks &P, const RggBlockJob &J, hipStream_
     const dim3 grid((uint32_t)((P.nb + kBlocksPerWave - 1) / kBlocksPerWave)), wave(64);
     if (D == 2 && P.B == 0) hipLaunchKernelGGL((rgg_block_write_kernel<2, 0, 8>), grid, wave, 0, s, J);
     else if (D == 2) hipLaunchKernelGGL((rgg_block_write_kernel<2, 1, 8>), grid, wave, 0, s, J);
+    else if (P.B == 1 && P.words == 16) hipLaunchKernelGGL((rgg_block_write_kernel<3, 1, 16>), grid, wave, 0, s, J);
     else if (P.B == 1) hipLaunchKernelGGL((rgg_block_write_kernel<3, 1, 8>), grid, wave, 0, s, J);
     else if (P.words == 8) hipLaunchKernelGGL((rgg_block_write_kernel<3, 0, 8>), grid, wave, 0, s, J);
     else hipLaunchKernelGGL((rgg_block_write_kernel<3, 0, 16>), grid, wave, 0, s, J);
@@ -730,11 +741,11 @@ void rgg_scan(const uint64_t *a, uint64_t len, uint64_t *sums, uint64_t *out, ui
 // the lanes it can get; of the later ones many run at once.
 void rgg_split(int D, uint64_t n, uint64_t seed, uint32_t L, uint64_t *mid, uint64_t *coff, hipStream_t s)
 {
-    const uint32_t depth = D * L, launches = depth ? (depth + kSplitMost - 1) / kSplitMost : 1;
+    const uint32_t depth = D * L, launches = split_launches(depth);
     const uint64_t *in = nullptr;
     for (uint32_t i = 0, p = 0; i < launches; ++i) {
         const uint32_t q = (depth - p) / (launches - i);
-        uint64_t *out = i + 1 == launches ? coff : mid + (i & 1) * kSplitMid;
+        uint64_t *out = i + 1 == launches ? coff : mid + (i & 1) * split_words(depth);
         const dim3 grid((uint32_t)(1ull << p)), block(i == 0 ? 1024 : 256);
         if (D == 2)
             hipLaunchKernelGGL(rgg_split_kernel<2>, grid, block, 0, s, seed, n, (uint32_t)TAG_RTREE, in, out, p, q);
@@ -1006,7 +1017,7 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     const bool blk = Y.P.B >= 0;
     J.q = blk ? (uint32_t *)(ws.base + Y.q) : nullptr;
     J.Q = Y.P.Q;
-    const RggBlockJob JB = rgg_block_job(2, n, r, capacity_edges, Y, ws.base, d_points, d_edges);
+    const RggBlockJob JB = rgg_block_job(2, r, Y, ws.base, d_points, d_edges);
     {
         KernelTimer tm(KG_KERNEL_COUNT, s);
         rgg_split(2, n, seed, Y.L, (uint64_t *)(ws.base + Y.mid), J.coff, s);
@@ -1088,7 +1099,7 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     const bool blk = Y.P.B >= 0;
     J.q = blk ? (uint32_t *)(ws.base + Y.q) : nullptr;
     J.Q = Y.P.Q;
-    const RggBlockJob JB = rgg_block_job(3, n, r, capacity_edges, Y, ws.base, d_points, d_edges);
+    const RggBlockJob JB = rgg_block_job(3, r, Y, ws.base, d_points, d_edges);
     {
         KernelTimer tm(KG_KERNEL_COUNT, s);
         rgg_split(3, n, seed, Y.L, (uint64_t *)(ws.base + Y.mid), J.coff, s);

@@ -11,15 +11,19 @@
 // side apart, which is at least r.
 //
 // Task u G + g tests point u against the g-th of G equal parts of the
-// candidates; a pass runs 64 tasks, a lane each, and G (1 to 8) is the one that
-// needs the fewest instructions for the block's points and candidates.  All
-// lanes of a part read the same LDS address, and task order is output order.  The test is made on the points' positions inside
-// their cells, rounded down to 2^-13 or 2^-14 of a cell (two 16-bit numbers
-// to a word, written by the points kernel): one packed subtraction and one
+// candidates, a bit per candidate; task order is output order.  The test is
+// made on the points' positions inside their cells, rounded down to 2^-13 or
+// 2^-14 of a cell (two 16-bit numbers to a word, written by the points kernel).
+// The rounding moves a distance by less than sqrt(D) units, so only squares
+// within [lo, lo + band] are open; a word that holds one (a few in 100) is tested
+// again, the open candidates in binary64.
+//
+// Two dimensions: a pass runs 64 tasks, a lane each, and G (1 to 8) is the one
+// that needs the fewest instructions for the block's points and candidates;
+// all lanes of a part read the same LDS address, one packed subtraction and one
 // dot product give d^2 minus the threshold, whose sign bit is shifted into the
-// lane's result word.  The rounding moves a distance by less than sqrt(D)
-// units, so only squares within [lo, lo + band] are open; a word that holds
-// one (a few in 100) is tested again, the open candidates in binary64.
+// lane's result word.  Three dimensions: the matrix units form these
+// differences, G = 4 (rgg_block_count3_kernel).
 //
 // Count pass: the result words and the block's edge count.  Write pass: the
 // words' set bits are the edges, in output order; they are gathered in LDS and
@@ -27,12 +31,12 @@
 // candidates than its words hold (hardly ever at the densities this path is
 // chosen for) is tested in binary64 in both passes.
 //
-// What bounds it: vector instructions in the count pass (3.5 per test in two
-// dimensions, 5.5 in three, of about 80 and 144 tests per vertex, and as much
-// again for the window, the lists and the masks), latency in the write pass.
-// n = 2^26 at r = 0.55 (ln n / n)^(1/d), lane per vertex before: two
-// dimensions count 4.4 -> 2.0 ms, write 2.6 -> 2.2 ms (call 7.8 -> 4.8 ms);
-// three dimensions count 10.7 -> 3.8 ms, write 8.3 -> 2.2 ms (20.8 -> 7.1 ms).
+// What bounds it: vector instructions (in two dimensions 3.5 per test of about
+// 80 per vertex, and more than that again for the window, the lists and the
+// masks), in the write pass also latency.  n = 2^26 at
+// r = 0.55 (ln n / n)^(1/d), lane per vertex before: two dimensions count 4.4 ->
+// 1.9 ms, write 2.6 -> 2.2 ms (call 7.8 -> 4.4 ms); three dimensions count
+// 10.7 -> 3.2 ms, write 8.3 -> 1.6 ms (20.8 -> 5.6 ms).
 #pragma once
 #include "kg_rgg.hpp"
 #include "kg_rgg3.hpp"
@@ -41,7 +45,6 @@
 namespace kg {
 
 struct RggBlockJob {
-    uint64_t n, capacity;
     double r2;
     uint64_t nb;               // blocks
     uint32_t G;                // cells per side
@@ -79,6 +82,12 @@ __device__ __forceinline__ uint32_t cell_spread(uint32_t x) { return D == 2 ? sp
 template <int D>
 __device__ __forceinline__ uint32_t cell_gather(uint32_t z) { return D == 2 ? gather_bits(z) : gather3(z); }
 
+// The bits from position `first` on (any, also below 0 or above 31).
+__device__ __forceinline__ uint32_t bits_from(int32_t first)
+{
+    return (uint32_t)(0xFFFFFFFFull << (uint32_t)min(max(first, 0), 32));
+}
+
 // v of lane (lane xor X) within groups of 16 by DPP, across them by a shuffle
 template <int X>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
@@ -93,32 +102,47 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
     return (uint32_t)__shfl_xor((int)v, X, 64);
 }
 
-template <int X>
-__device__ __forceinline__ void lane_cx(uint32_t &v, uint32_t bit)
+// The median of two values and 0 is their minimum, of two and 2^32 - 1 their
+// maximum: one instruction for both sides of an exchange.
+__device__ __forceinline__ uint32_t median(uint32_t a, uint32_t b, uint32_t c)
 {
-    const uint32_t t = lane_xor<X>(v);
-    const uint32_t a = min(v, t), b = max(v, t);
-    v = (threadIdx.x & bit) ? b : a;
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
 // Ascending sort of one value per lane inside groups of 16, 32 or 64 lanes: a
 // merge first compares each lane with its mirror image, then at halving
 // distances, always with the smaller value to the lower lane.
-template <int N>
-__device__ __forceinline__ uint32_t lane_sort(uint32_t v)
-{
-    lane_cx<1>(v, 1);
-    lane_cx<3>(v, 2); lane_cx<1>(v, 1);
-    lane_cx<7>(v, 4); lane_cx<2>(v, 2); lane_cx<1>(v, 1);
-    lane_cx<15>(v, 8); lane_cx<4>(v, 4); lane_cx<2>(v, 2); lane_cx<1>(v, 1);
-    if (N >= 32) {
-        lane_cx<31>(v, 16); lane_cx<8>(v, 8); lane_cx<4>(v, 4); lane_cx<2>(v, 2); lane_cx<1>(v, 1);
+struct LaneSort {
+    uint32_t upper[6];       // all ones in the lanes with bit 1, 2, 4, 8, 16, 32
+
+    __device__ __forceinline__ LaneSort()
+    {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) upper[i] = (threadIdx.x >> i & 1) ? ~0u : 0u;
     }
-    if (N >= 64) {
-        lane_cx<63>(v, 32); lane_cx<16>(v, 16); lane_cx<8>(v, 8); lane_cx<4>(v, 4); lane_cx<2>(v, 2); lane_cx<1>(v, 1);
+
+    // lane against lane xor X, the smaller value to the lane without bit i
+    template <int X>
+    __device__ __forceinline__ void cx(uint32_t &v, int i) const { v = median(v, lane_xor<X>(v), upper[i]); }
+
+    template <int N>
+    __device__ __forceinline__ uint32_t sort(uint32_t v) const
+    {
+        cx<1>(v, 0);
+        cx<3>(v, 1); cx<1>(v, 0);
+        cx<7>(v, 2); cx<2>(v, 1); cx<1>(v, 0);
+        cx<15>(v, 3); cx<4>(v, 2); cx<2>(v, 1); cx<1>(v, 0);
+        if (N >= 32) {
+            cx<31>(v, 4); cx<8>(v, 3); cx<4>(v, 2); cx<2>(v, 1); cx<1>(v, 0);
+        }
+        if (N >= 64) {
+            cx<63>(v, 5); cx<16>(v, 4); cx<8>(v, 3); cx<4>(v, 2); cx<2>(v, 1); cx<1>(v, 0);
+        }
+        return v;
     }
-    return v;
-}
+};
 
 // Inclusive prefix sums over groups of 16 lanes, or the wave.
 template <bool ROWS>
@@ -155,6 +179,7 @@ struct RggWindow {
     uint32_t st, incl;         // per lane: first vertex of its cell, points up to it
     uint32_t split;            // per lane: parts() of its block
     uint64_t full;             // lanes whose cell holds points
+    LaneSort order;
 
     // The parts of a block's candidates (k, C the same in each 8 lanes): the G
     // of 1 .. 8 with the fewest vector instructions, about 4 (6 in three
@@ -163,6 +188,13 @@ struct RggWindow {
     // the lists are too small.
     static __device__ __forceinline__ uint32_t parts(uint32_t k, uint32_t C)
     {
+        if (D == 3) {
+            // four parts, as the matrix units' rows take them; an odd multiple
+            // of 4 spreads the parts' reads over the LDS banks
+            if (C > 32 * WORDS) return 0;
+            const uint32_t q = (C + 15) / 16;
+            return (q < 2 * WORDS ? q | 1 : q) << 6 | 4;
+        }
         const uint32_t g = (threadIdx.x & 7) + 1;
         const uint32_t c = 4 * (uint32_t)((float)(C + 4 * g - 1) * __builtin_amdgcn_rcpf((float)(4 * g)) + 0.0001f);
         uint32_t cost = ((k * g + 63) >> 6) * ((D == 2 ? 4 : 6) * c + 60);
@@ -174,6 +206,9 @@ struct RggWindow {
         v = min(v, lane_xor<7>(v));
         return v >> 14 == 0xFFFF ? 0 : v & 0x3FFF;
     }
+
+    // the last two bits of the first coordinate of a Morton index
+    static __device__ __forceinline__ uint32_t low2(uint32_t z) { return (z & 1) | (z >> (D - 1) & 2); }
 
     // the windows of blocks b, b + 1, ... (BLOCKS of them)
     __device__ __forceinline__ void find(const RggBlockJob &J, uint64_t b, RggCells &s)
@@ -190,7 +225,7 @@ struct RggWindow {
                 if (m >= z0) zz = m;
             }
         }
-        zz = lane_sort<(NC <= 16 ? 16 : NC <= 32 ? 32 : 64)>(zz);
+        zz = order.sort<(NC <= 16 ? 16 : NC <= 32 ? 32 : 64)>(zz);
         uint32_t len = 0;
         st = 0;
         if (zz != kRggNone) {
@@ -210,9 +245,10 @@ struct RggWindow {
             const uint32_t at = row * LANES + n;
             s.base[at] = st - off;
             s.len[at] = len;
-            const uint32_t ox = cell_gather<D>(zz) - bx + 1, oy = cell_gather<D>(zz >> 1) - by + 1;
+            // 0 .. 3 in each dimension: the coordinates' last two bits tell
+            const uint32_t ox = (low2(zz) - bx + 1) & 3, oy = (low2(zz >> 1) - by + 1) & 3;
             s.pos[at] = (ox << J.Q) | (oy << J.Q << 16);
-            if (D == 3) s.posz[at] = (cell_gather<D>(zz >> 2) - bz + 1) << J.Q;
+            if (D == 3) s.posz[at] = ((low2(zz >> 2) - bz + 1) & 3) << J.Q;
             if (n && off <= 32 * MAP)
                 atomicOr(&(&s.map[0][0])[row * MAP + ((off - 1) >> 5)], 1u << ((off - 1) & 31));
         }
@@ -274,7 +310,17 @@ struct RggBlock {
         light = G != 0;
         live = k * G;
         // floor(65536 / G) + 1, or 65536 / G where that is whole: exact for task * G < 65536
-        magic = light ? uni((uint32_t)(65536.0f * __builtin_amdgcn_rcpf((float)G)) + 1) : 0;
+        magic = D == 2 && light ? uni((uint32_t)(65536.0f * __builtin_amdgcn_rcpf((float)G)) + 1) : 0;
+    }
+
+    // Three dimensions: a part's words (1, 2 or 4, so their number is a shift)
+    // and the candidates of a word but a part's last (a multiple of 4).  Word
+    // w of task t is word t << word_log() + w of the block, in output order.
+    __device__ __forceinline__ uint32_t word_log() const { return Cg <= 32 ? 0 : Cg <= 64 ? 1 : 2; }
+    __device__ __forceinline__ uint32_t word_len() const
+    {
+        const uint32_t l = word_log();
+        return ((Cg / 4 + (1u << l) - 1) >> l) * 4;
     }
 
     // point and first candidate of a task
@@ -295,6 +341,15 @@ struct RggBlock {
             const uint32_t p = t + lane;
             if (p < C) f(p, p + s.base[c], c);
         }
+    }
+
+    // the vertex at position p of the candidates
+    __device__ __forceinline__ uint32_t vertex(const RggCells &s, uint32_t p) const
+    {
+        const uint32_t *map = &s.map[0][0] + Window::MAP * j;
+        uint32_t c = Window::LANES * j + __builtin_popcount(map[p / 32] & ((1u << (p & 31)) - 1));
+        for (uint32_t w = 0; w < p / 32; ++w) c += __builtin_popcount(map[w]);
+        return p + s.base[c];
     }
 
     // binary64 predicate of two vertices
@@ -324,14 +379,13 @@ struct RggBlock {
     }
 };
 
-template <int D, int B, int WORDS>
-__global__ __launch_bounds__(64) void rgg_block_count_kernel(RggBlockJob J)
+template <int B, int WORDS>
+__global__ __launch_bounds__(64) void rgg_block_count2_kernel(RggBlockJob J)
 {
-    typedef RggWindow<D, B, WORDS> Window;
-    typedef RggBlock<D, B, WORDS> Block;
+    typedef RggWindow<2, B, WORDS> Window;
+    typedef RggBlock<2, B, WORDS> Block;
     __shared__ RggCells s;
     __shared__ __attribute__((aligned(16))) uint32_t s_xy[Block::CAND];
-    __shared__ __attribute__((aligned(16))) uint32_t s_z[D == 3 ? Block::CAND : 4];
     __shared__ uint32_t s_id[Block::CAND];
     const uint32_t lane = threadIdx.x;
     const uint64_t b0 = (uint64_t)blockIdx.x * kBlocksPerWave;
@@ -339,44 +393,30 @@ __global__ __launch_bounds__(64) void rgg_block_count_kernel(RggBlockJob J)
     for (uint32_t bi = 0; bi < kBlocksPerWave && b0 + bi < J.nb; ++bi) {
         if (bi % Window::BLOCKS == 0) win.find(J, b0 + bi, s);
         const Block K(win, bi % Window::BLOCKS);
-        if (D == 3) K.keep(J.list + (b0 + bi) * Window::LIST, s);
         uint32_t cnt = 0;
         if (K.k && K.light) {
             K.each(s, [&](uint32_t p, uint32_t v, uint32_t c) {
                 s_id[p] = v;
-                if (D == 2) {
-                    s_xy[p] = J.q[v] + s.pos[c];
-                } else {
-                    const uint2 w = reinterpret_cast<const uint2 *>(J.q)[v];
-                    s_xy[p] = w.x + s.pos[c];
-                    s_z[p] = w.y + s.posz[c];
-                }
+                s_xy[p] = J.q[v] + s.pos[c];
             });
             // padding: the window's corner, further from the block than r
-            for (uint32_t p = K.C + lane; p < K.G * K.Cg; p += 64) {
-                s_xy[p] = 0;
-                if (D == 3) s_z[p] = 0;
-            }
+            for (uint32_t p = K.C + lane; p < K.G * K.Cg; p += 64) s_xy[p] = 0;
             __syncthreads();
             const int32_t base = -(int32_t)J.lo;
-            auto square = [&](uint32_t xy, uint32_t z, uint32_t axy, uint32_t az) -> uint32_t {
-                const int32_t dz = D == 3 ? (int32_t)(z - az) : 0;
-                return (uint32_t)dist2_packed(xy, axy, D == 3 ? __mul24(dz, dz) + base : base);
-            };
+            auto square = [&](uint32_t xy, uint32_t axy) { return (uint32_t)dist2_packed(xy, axy, base); };
             for (uint32_t t = 0; t < K.live; t += 64) {
                 const uint32_t task = t + lane;
                 const uint32_t u = K.point(task), g0 = K.part(task, u);
-                const uint32_t uxy = s_xy[u], uz = D == 3 ? s_z[u] : 0;
+                const uint32_t uxy = s_xy[u];
+                const uint64_t own = __ballot(task < K.live);
                 uint32_t *out = J.bits + (uint64_t)K.u0 * WORDS + task;
                 for (uint32_t w = 0; w < K.Cg; w += 32, out += K.live) {
                     const uint32_t quads = uni(min(8u, (K.Cg - w) / 4)), p0 = g0 + w;
                     uint32_t acc = 0, open = ~0u;
                     for (uint32_t i = 0; i < quads; ++i) {
                         const uint4v c = *reinterpret_cast<const uint4v *>(s_xy + p0 + 4 * i);
-                        uint4v cz = {0, 0, 0, 0};
-                        if (D == 3) cz = *reinterpret_cast<const uint4v *>(s_z + p0 + 4 * i);
-                        const uint32_t t0 = square(c.x, cz.x, uxy, uz), t1 = square(c.y, cz.y, uxy, uz),
-                                       t2 = square(c.z, cz.z, uxy, uz), t3 = square(c.w, cz.w, uxy, uz);
+                        const uint32_t t0 = square(c.x, uxy), t1 = square(c.y, uxy), t2 = square(c.z, uxy),
+                                       t3 = square(c.w, uxy);
                         acc = __builtin_amdgcn_alignbit(acc, t0, 31);
                         acc = __builtin_amdgcn_alignbit(acc, t1, 31);
                         acc = __builtin_amdgcn_alignbit(acc, t2, 31);
@@ -384,29 +424,143 @@ __global__ __launch_bounds__(64) void rgg_block_count_kernel(RggBlockJob J)
                         open = min(open, min(t0, t1));
                         open = min(open, min(t2, t3));
                     }
-                    // bit i: candidate p0 + i, after u and in the list
+                    // bit i: candidate p0 + i
                     uint32_t m = __builtin_bitreverse32(acc << ((32 - 4 * quads) & 31));
-                    const int32_t first = (int32_t)(u + 1) - (int32_t)p0, end = (int32_t)K.C - (int32_t)p0;
-                    uint32_t ok = first <= 0 ? ~0u : first >= 32 ? 0u : ~0u << first;
-                    ok &= end >= 32 ? ~0u : end <= 0 ? 0u : (1u << end) - 1;
-                    if (task >= K.live) ok = 0;
                     // a lane whose word holds an open square: its candidates, a
                     // lane each, by the quantised and, if open, the exact test
-                    for (uint64_t mo = __ballot(open <= J.band && ok != 0); mo; mo &= mo - 1) {
+                    for (uint64_t mo = __ballot(open <= J.band) & own; mo; mo &= mo - 1) {
                         const int l = __builtin_ctzll(mo);
                         const uint32_t lu = __builtin_amdgcn_readlane(u, l), lp = __builtin_amdgcn_readlane(p0, l);
                         const uint32_t p = lp + (lane & 31);
                         bool hit = false;
                         if (lane < 4 * quads && p < K.C) {
-                            const uint32_t t = square(s_xy[p], D == 3 ? s_z[p] : 0, s_xy[lu], D == 3 ? s_z[lu] : 0);
-                            if (t <= J.band) hit = Block::near(J, K.u0 + lu, s_id[p]);
+                            if (square(s_xy[p], s_xy[lu]) <= J.band) hit = Block::near(J, K.u0 + lu, s_id[p]);
                         }
                         const uint32_t found = (uint32_t)__ballot(hit);
                         if ((int)lane == l) m |= found;
                     }
-                    m &= ok;
+                    m &= bits_from((int32_t)(u + 1) - (int32_t)p0);      // after u
+                    if (task < K.live) {
+                        cnt += __builtin_popcount(m);
+                        *out = m;
+                    }
+                }
+            }
+            cnt = wave_incl_scan32(cnt);
+            if (lane == 63) J.bcnt[b0 + bi] = cnt;
+        } else {
+            for (uint32_t u = lane; u < K.k; u += 64) K.heavy(J, s, K.u0 + u, [&](uint32_t) { ++cnt; });
+            const uint64_t total = wave_incl_scan64(cnt);
+            if (lane == 63) J.bcnt[b0 + bi] = total;
+        }
+        __syncthreads();
+    }
+}
+
+// Three dimensions: |u|^2 - 2 u.c + |c|^2 is a product of a column (x, y, z, 1)
+// per point and a row (-2x, -2y, -2z, |c|^2) per candidate, so the matrix
+// units form d^2 minus the threshold for 16 points x 16 candidates in one
+// binary32 instruction (K = 4, the sum starts from |u|^2 - lo).  Rows 4h .. 4h + 3 of a
+// product come out in lanes 16 h .. 16 h + 15: they take candidates of part h,
+// so lane 16 h + c holds the results of point c against part h, in order.
+// Coordinates count from the window's centre: with cell side 2^Q every partial
+// sum is below 48 4^Q, and the roundings together below 2^(2Q - 15.7); `open`
+// squares are taken 2^(2Q - 14) further to both sides.  A product and 6 vector
+// instructions per 256 tests, where the packed form of two dimensions takes
+// 30: 594 vector instructions per block instead of 1056.  n = 2^26,
+// r = 0.55 (ln n / n)^(1/3): 3.9 -> 3.2 ms (products and vector instructions of a
+// SIMD hardly overlap: together they fill 85 % of the time).
+template <int B, int WORDS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void rgg_block_count3_kernel(RggBlockJob J)
+{
+    typedef RggWindow<3, B, WORDS> Window;
+    typedef RggBlock<3, B, WORDS> Block;
+    typedef float float4v __attribute__((ext_vector_type(4)));
+    constexpr uint32_t S = 32 * WORDS + 16;     // 16 words past a multiple of 64: the components' reads
+                                                // fall into different banks; also room for the last 16 points
+    __shared__ RggCells s;
+    __shared__ float s_f[4 * S];                // -2x, -2y, -2z, x^2 + y^2 + z^2 of every candidate
+    const uint32_t lane = threadIdx.x, col = lane & 15, h = lane >> 4;
+    const uint64_t b0 = (uint64_t)blockIdx.x * kBlocksPerWave;
+    const float mid2 = (float)(Window::W << J.Q);               // twice the centre
+    const float margin = (float)(1u << (2 * J.Q - 14));
+    const float thr = (float)J.lo - margin;
+    const float wide_f = (float)J.band + 2.0f * margin;
+    const uint32_t wide = __float_as_uint(wide_f);
+    Window win;
+    for (uint32_t bi = 0; bi < kBlocksPerWave && b0 + bi < J.nb; ++bi) {
+        win.find(J, b0 + bi, s);
+        const Block K(win, 0);
+        K.keep(J.list + (b0 + bi) * Window::LIST, s);
+        uint32_t cnt = 0;
+        if (K.k && K.light) {
+            K.each(s, [&](uint32_t p, uint32_t v, uint32_t c) {
+                const uint2 w = reinterpret_cast<const uint2 *>(J.q)[v];
+                const uint32_t xy = w.x + s.pos[c];
+                const float x = __builtin_fmaf((float)(xy & 0xFFFF), -2.0f, mid2);
+                const float y = __builtin_fmaf((float)(xy >> 16), -2.0f, mid2);
+                const float z = __builtin_fmaf((float)(w.y + s.posz[c]), -2.0f, mid2);
+                s_f[p] = x;
+                s_f[S + p] = y;
+                s_f[2 * S + p] = z;
+                s_f[3 * S + p] = 0.25f * __builtin_fmaf(x, x, __builtin_fmaf(y, y, z * z));
+            });
+            // padding: far away
+            for (uint32_t p = K.C + lane; p < 4 * K.Cg; p += 64) {
+                s_f[p] = s_f[S + p] = s_f[2 * S + p] = 0.0f;
+                s_f[3 * S + p] = 1e15f;
+            }
+            __syncthreads();
+            const uint32_t wlog = K.word_log(), wlen = K.word_len();
+            const float *row = s_f + h * S + (col >> 2) * K.Cg + (col & 3);
+            for (uint32_t t = 0; t < K.k; t += 16) {
+                const uint32_t u = t + col;
+                const float b = h == 3 ? 1.0f : u < K.k ? -0.5f * s_f[h * S + u] : 0.0f;
+                const float c0 = u < K.k ? s_f[3 * S + u] - thr : 1e15f;      // no point: far from all
+                const float4v from = {c0, c0, c0, c0};
+                uint32_t *out = J.bits + (uint64_t)K.u0 * WORDS + ((4 * u + h) << wlog);
+                for (uint32_t w = 0; w < K.Cg; w += wlen, ++out) {
+                    const uint32_t quads = uni(min(wlen, K.Cg - w) / 4), p0 = h * K.Cg + w;
+                    uint32_t acc = 0, open = ~0u;
+                    auto take = [&](const float4v &d) {
+                        const uint32_t t0 = __float_as_uint(d.x), t1 = __float_as_uint(d.y),
+                                       t2 = __float_as_uint(d.z), t3 = __float_as_uint(d.w);
+                        acc = __builtin_amdgcn_alignbit(acc, t0, 31);
+                        acc = __builtin_amdgcn_alignbit(acc, t1, 31);
+                        acc = __builtin_amdgcn_alignbit(acc, t2, 31);
+                        acc = __builtin_amdgcn_alignbit(acc, t3, 31);
+                        open = min(min(open, t0), t1);
+                        open = min(min(open, t2), t3);
+                    };
+                    uint32_t i = 0;
+                    for (; i + 2 <= quads; i += 2) {
+                        const float a0 = row[w + 4 * i], a1 = row[w + 4 * i + 4];
+                        const float4v d0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b, from, 0, 0, 0);
+                        const float4v d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b, from, 0, 0, 0);
+                        take(d0);
+                        take(d1);
+                    }
+                    if (i < quads) take(__builtin_amdgcn_mfma_f32_16x16x4f32(row[w + 4 * i], b, from, 0, 0, 0));
+                    // bit i: candidate p0 + i
+                    uint32_t m = __builtin_bitreverse32(acc << ((32 - 4 * quads) & 31));
+                    // a lane whose word holds an open square: its candidates, a
+                    // lane each, by a direct square and, if open, the exact test
+                    for (uint64_t mo = __ballot(open <= wide); mo; mo &= mo - 1) {
+                        const int l = __builtin_ctzll(mo);
+                        const uint32_t lu = __builtin_amdgcn_readlane(u, l), lp = __builtin_amdgcn_readlane(p0, l);
+                        const uint32_t p = lp + (lane & 31);
+                        bool hit = false;
+                        if (lane < 4 * quads && p < K.C) {
+                            const float dx = s_f[p] - s_f[lu], dy = s_f[S + p] - s_f[S + lu], dz = s_f[2 * S + p] - s_f[2 * S + lu];
+                            const float d = 0.25f * __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz)) - thr;
+                            if (d <= wide_f) hit = d < 0.0f || Block::near(J, K.u0 + lu, K.vertex(s, p));
+                        }
+                        const uint32_t found = (uint32_t)__ballot(hit);
+                        if ((int)lane == l) m |= found;
+                    }
+                    m &= bits_from((int32_t)(u + 1) - (int32_t)p0);      // after u
                     cnt += __builtin_popcount(m);
-                    if (task < K.live) *out = m;
+                    if (u < K.k) *out = m;
                 }
             }
             cnt = wave_incl_scan32(cnt);
@@ -447,45 +601,74 @@ __global__ __launch_bounds__(64) void rgg_block_write_kernel(RggBlockJob J)
         if (total == 0) continue;
         const Block K = D == 2 ? Block(win, bi % Window::BLOCKS) : Block(J.list + (b0 + bi) * Window::LIST, s);
         if (K.light) {
-            const uint32_t nw = (K.Cg + 31) / 32;
             const bool staged = total <= kBlockStage;
-            uint32_t done = 0;
-            uint32_t m = first[0];
-#pragma unroll
-            for (uint32_t j = 1; j < Window::BLOCKS; ++j) m = bi % Window::BLOCKS == j ? first[j] : m;
-            if (D == 3) m = lane < K.live ? J.bits[(uint64_t)K.u0 * WORDS + lane] : 0;
-            K.each(s, [&](uint32_t p, uint32_t v, uint32_t) { s_id[p] = v; });
-            __syncthreads();
-            for (uint32_t t = 0; t < K.live; t += 64) {
-                const uint32_t task = t + lane;
-                const uint32_t *in = J.bits + (uint64_t)K.u0 * WORDS + task;
-                const bool own = task < K.live;
-                const uint32_t lu = K.point(task), u = K.u0 + lu;
-                if (t != 0) m = own ? in[0] : 0;
-                uint32_t cnt = __builtin_popcount(m);
-                for (uint32_t w = 1; w < nw; ++w) cnt += own ? __builtin_popcount(in[w * K.live]) : 0;
-                const uint32_t incl = wave_incl_scan32(cnt);
-                uint32_t at = done + incl - cnt;
-                done += __builtin_amdgcn_readlane(incl, 63);
-                const uint32_t *id = s_id + K.part(task, lu);
-                for (uint32_t w = 0;; id += 32) {
-                    if (staged) {
-                        // two edges per trip: their ids are read together
-                        while (m) {
-                            const uint32_t i0 = __builtin_ctz(m);
-                            m &= m - 1;
-                            const uint32_t i1 = m ? __builtin_ctz(m) : i0;
-                            const uint32_t v0 = id[i0], v1 = id[i1];
-                            s_e[at] = make_uint2(u, v0);
-                            if (m) s_e[at + 1] = make_uint2(u, v1);
-                            at += m ? 2 : 1;
-                            m &= m - 1;
-                        }
-                    } else {
-                        for (; m; m &= m - 1) J.edges[o + at++] = make_uint2(u, id[__builtin_ctz(m)]);
+            // a word's edges, in order: two per trip, their ids are read together
+            auto put = [&](uint32_t u, uint32_t m, const uint32_t *id, uint32_t &at) {
+                if (staged) {
+                    while (m) {
+                        const uint32_t i0 = __builtin_ctz(m);
+                        m &= m - 1;
+                        const uint32_t i1 = m ? __builtin_ctz(m) : i0;
+                        const uint32_t v0 = id[i0], v1 = id[i1];
+                        s_e[at] = make_uint2(u, v0);
+                        if (m) s_e[at + 1] = make_uint2(u, v1);
+                        at += m ? 2 : 1;
+                        m &= m - 1;
                     }
-                    if (++w == nw) break;
-                    m = own ? in[w * K.live] : 0;
+                } else {
+                    for (; m; m &= m - 1) J.edges[o + at++] = make_uint2(u, id[__builtin_ctz(m)]);
+                }
+            };
+            if (D == 3) {
+                // a lane takes n consecutive words of the block; the first
+                // kRowWords stay in registers for the second look
+                const uint32_t wlog = K.word_log(), wlen = K.word_len(), words = K.live << wlog, n = (words + 63) / 64;
+                const uint32_t *in = J.bits + (uint64_t)K.u0 * WORDS + lane * n;
+                const uint32_t mine = lane * n < words ? min(n, words - lane * n) : 0;
+                constexpr uint32_t kRowWords = 8;
+                uint32_t m[kRowWords];
+#pragma unroll
+                for (uint32_t i = 0; i < kRowWords; ++i) m[i] = i < mine ? in[i] : 0;
+                K.each(s, [&](uint32_t p, uint32_t v, uint32_t) { s_id[p] = v; });
+                __syncthreads();
+                uint32_t cnt = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < kRowWords; ++i) cnt += __builtin_popcount(m[i]);
+                for (uint32_t i = kRowWords; i < mine; ++i) cnt += __builtin_popcount(in[i]);
+                uint32_t at = wave_incl_scan32(cnt) - cnt;
+                auto word = [&](uint32_t i, uint32_t m) {
+                    const uint32_t x = lane * n + i, t = x >> wlog;
+                    put(K.u0 + (t >> 2), m, s_id + (t & 3) * K.Cg + (x & ((1u << wlog) - 1)) * wlen, at);
+                };
+#pragma unroll
+                for (uint32_t i = 0; i < kRowWords; ++i)
+                    if (i < n) word(i, m[i]);
+                for (uint32_t i = kRowWords; i < mine; ++i) word(i, in[i]);
+            } else {
+                const uint32_t nw = (K.Cg + 31) / 32;
+                uint32_t done = 0;
+                uint32_t m = first[0];
+#pragma unroll
+                for (uint32_t j = 1; j < Window::BLOCKS; ++j) m = bi % Window::BLOCKS == j ? first[j] : m;
+                K.each(s, [&](uint32_t p, uint32_t v, uint32_t) { s_id[p] = v; });
+                __syncthreads();
+                for (uint32_t t = 0; t < K.live; t += 64) {
+                    const uint32_t task = t + lane;
+                    const uint32_t *in = J.bits + (uint64_t)K.u0 * WORDS + task;
+                    const bool own = task < K.live;
+                    const uint32_t lu = K.point(task), u = K.u0 + lu;
+                    if (t != 0) m = own ? in[0] : 0;
+                    uint32_t cnt = __builtin_popcount(m);
+                    for (uint32_t w = 1; w < nw; ++w) cnt += own ? __builtin_popcount(in[w * K.live]) : 0;
+                    const uint32_t incl = wave_incl_scan32(cnt);
+                    uint32_t at = done + incl - cnt;
+                    done += __builtin_amdgcn_readlane(incl, 63);
+                    const uint32_t *id = s_id + K.part(task, lu);
+                    for (uint32_t w = 0;; id += 32) {
+                        put(u, m, id, at);
+                        if (++w == nw) break;
+                        m = own ? in[w * K.live] : 0;
+                    }
                 }
             }
             __syncthreads();
