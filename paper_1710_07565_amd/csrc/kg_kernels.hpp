@@ -517,6 +517,7 @@ struct Decoder {
     uint32_t r0, c0;    // row of the tile start and its offset in that row; triangle: section start
     uint32_t b;         // rectangle: first column; triangle: section size
     double rcp;         // 1 / dv
+    uint32_t mul, add;  // y / dv = high32(y mul + add) >> sh (dv not a power of two)
     uint64_t lbase;     // triangle: tile start
 
     __device__ __forceinline__ uint32_t divmod(uint32_t x, uint32_t &rem) const

