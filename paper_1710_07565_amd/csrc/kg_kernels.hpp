@@ -19,7 +19,7 @@ struct Job {
     uint32_t fast_cap;       // draws of the register base case (tile_kernel); larger tiles are queued
     uint32_t unit_log;       // planner units hold <= 2^unit_log tiles (launch shape only)
     uint32_t counts_only;    // the chunk counts are wanted, not their offsets
-    uint32_t pad_;
+    uint32_t whole;          // tile_one_kernel finds the chunks' counts too (no count kernel ran)
     uint64_t G;              // chunks over all instances
     uint64_t capacity;       // output room in edges
     uint64_t tile_cap;       // tile_off has tile_cap + 1 entries

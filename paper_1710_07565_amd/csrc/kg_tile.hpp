@@ -134,9 +134,14 @@ struct TileWalk {
 
     __device__ __forceinline__ void enter(const Job &job, uint64_t gg)
     {
+        enter(job, gg, ld_uni(job.tstart + gg), ld_uni(job.tstart + gg + 1));
+    }
+
+    __device__ __forceinline__ void enter(const Job &job, uint64_t gg, uint64_t start, uint64_t end)
+    {
         g = gg;
-        gstart = ld_uni(job.tstart + g);
-        gend = ld_uni(job.tstart + g + 1);
+        gstart = start;
+        gend = end;
         // the fields the sampler needs, through the scalar cache for batches
         Inst I;
         memset(&I, 0, sizeof(I));
@@ -888,33 +893,85 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 // The sampler of small jobs (at most a tile per workgroup): the wave walks
 // the tile tree's path to its tile itself, 64 proposals of each variate at
 // once, and takes the general base case where the register one does not do,
-// so the job needs neither the planner's nor the queue's launch.
+// so the job needs neither the planner's nor the queue's launch.  Where the
+// chunk tree's left counts are the chunks' offsets (directed G(n,m)), the wave
+// walks that path first and the count kernel's launch is not needed either
+// (job.whole): the chain of variates is the same, but not cut by a launch.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void tile_one_kernel(Job job)
 {
     __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
     __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[kCapMax + 8];
     const uint64_t t = blockIdx.x;
-    if (ld_uni(job.status + 1) || t >= ld_uni(job.status + 2)) return;
+    uint64_t g, gs, ge, o0 = 0, k = job.one.m;
+    if (job.whole) {
+        // a lane per chunk: the chunk of tile t by the chunks' tiles
+        const Sections at(job.one);
+        gs = ge = 0;
+        for (g = 0;; g += 64) {
+            if (g >= job.G) return;
+            const uint64_t c = g + threadIdx.x;
+            const uint64_t T = c < job.G ? tiles_of((at(c + 1) - at(c)) * (job.one.n - 1), job.one.s) : 0;
+            const uint64_t incl = ge + wave_incl_scan64(T);
+            const uint64_t past = __ballot(incl > t);
+            if (past) {
+                const int l = __builtin_ctzll(past);
+                g += l;
+                ge = __shfl(incl, l, 64);
+                gs = ge - __shfl(T, l, 64);
+                break;
+            }
+            ge = __shfl(incl, 63, 64);
+        }
+        g = uni64(g); gs = uni64(gs); ge = uni64(ge);
+    } else {
+        if (ld_uni(job.status + 1) || t >= ld_uni(job.status + 2)) return;
+        g = chunk_of_tile(job, t);
+        gs = ld_uni(job.tstart + g);
+        ge = ld_uni(job.tstart + g + 1);
+        o0 = ld_uni(job.off + g);
+        k = ld_uni(job.off + g + 1) - o0;
+    }
     clear_counters(s_cnt);
     TileWalk w;
     TileCtx &tc = w.tc;
     tc.edges = job.edges;
-    const uint64_t g = chunk_of_tile(job, t);
-    w.enter(job, g);
+    w.enter(job, g, gs, ge);
     const uint32_t last_S = w.place(t);
-    uint64_t o0 = ld_uni(job.off + g), k = ld_uni(job.off + g + 1) - o0;
-    const uint32_t tl = tc.st.b;
-    uint32_t lo = 0, hi = (uint32_t)(w.gend - w.gstart), heap = 1;
-    while (hi - lo > 1) {
+    // two trees in one loop (the variate's code appears once): the chunks'
+    // rows [lo, hi) where they are not known yet, then the chunk's tiles
+    bool rows = job.whole != 0;
+    const Sections at(job.one);
+    uint32_t at_me = rows ? (uint32_t)g : tc.st.b;
+    uint32_t lo = 0, hi = rows ? (uint32_t)job.G : (uint32_t)(ge - gs), heap = 1;
+    uint64_t A = 0, B = job.one.n;
+    for (;;) {
+        if (hi - lo <= 1) {
+            if (!rows) break;
+            rows = false;
+            at_me = tc.st.b;
+            lo = 0;
+            hi = (uint32_t)(ge - gs);
+            heap = 1;
+            continue;
+        }
         const uint32_t mid = lo + (hi - lo + 1) / 2;
-        const uint64_t X = uni64(hyp<64>(Stream{tc.st.k0, tc.st.k1, tc.st.a, heap, TAG_TTREE},
-                                         tile_range_slots(lo, hi, w.s, w.N), tile_range_slots(lo, mid, w.s, w.N), k));
-        if (tl < mid) { hi = mid; k = X; heap = 2 * heap; }
-        else { lo = mid; o0 += X; k -= X; heap = 2 * heap + 1; }
+        uint64_t all, left, M = 0;
+        if (rows) {
+            M = at(mid);
+            all = (B - A) * (job.one.n - 1);
+            left = (M - A) * (job.one.n - 1);
+        } else {
+            all = tile_range_slots(lo, hi, w.s, w.N);
+            left = tile_range_slots(lo, mid, w.s, w.N);
+        }
+        const Stream st{tc.st.k0, tc.st.k1, rows ? heap : tc.st.a, rows ? 0 : heap, rows ? TAG_DTREE : TAG_TTREE};
+        const uint64_t X = uni64(hyp<64>(st, all, left, k));
+        if (at_me < mid) { hi = mid; B = M; k = X; heap = 2 * heap; }
+        else { lo = mid; A = M; o0 += X; k -= X; heap = 2 * heap + 1; }
     }
     if (k == 0) return;
-    if (!sample_tile(tc, s_key, s_cnt, o0, k, w.s, t + 1 == w.gend, last_S, job.fast_cap)) {
+    if (!sample_tile(tc, s_key, s_cnt, o0, k, w.s, t + 1 == ge, last_S, job.fast_cap)) {
         __syncthreads();
         leaf_sample<kCapMax>(tc, s_key, s_hist, k, job.leaf_cap < kCapMax ? job.leaf_cap : kCapMax);
     }
