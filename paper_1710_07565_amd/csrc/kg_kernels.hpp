@@ -19,7 +19,9 @@ struct Job {
     uint32_t fast_cap;       // draws of the register base case (tile_kernel); larger tiles are queued
     uint32_t unit_log;       // planner units hold <= 2^unit_log tiles (launch shape only)
     uint32_t counts_only;    // the chunk counts are wanted, not their offsets
+    uint32_t tops;           // plan_top_kernel has run
     uint32_t whole;          // tile_one_kernel finds the chunks' counts too (no count kernel ran)
+    uint32_t pad_;
     uint64_t G;              // chunks over all instances
     uint64_t capacity;       // output room in edges
     uint64_t tile_cap;       // tile_off has tile_cap + 1 entries
@@ -347,6 +349,51 @@ __global__ __launch_bounds__(256) void inst_offsets_kernel(Job job)
 }
 
 // ---------------------------------------------------------------------------
+// plan, deep trees: the offsets of the subtrees of 2^kTopLog units (all but a
+// chunk's first), each by its path from the chunk's root, to tile_off at the
+// subtree's first tile.  The planner's units then start there instead of at the root:
+// a unit's path costs kTopLog variates instead of the tree's depth (10 to 19
+// where a chunk has thousands of tiles).  A lane per 2^kTopLog consecutive
+// units: at most one subtree starts among them.  Bound by the chain of variates,
+// about 2 us each (8 lanes per variate are slower here, 37 us against 30).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kTopLog = 4;
+
+// tiles [lo, hi) of node j of level `lev`, from those of the root
+__device__ __forceinline__ void unit_range(uint64_t j, uint32_t lev, uint64_t &lo, uint64_t &hi)
+{
+    while (lev-- > 0) {
+        const uint64_t mid = lo + (hi - lo + 1) / 2;
+        if ((j >> lev) & 1) lo = mid; else hi = mid;
+    }
+}
+
+__global__ __launch_bounds__(64) void plan_top_kernel(Job job)
+{
+    if (job.status[1]) return;
+    const uint64_t u = ((uint64_t)blockIdx.x * 64 + threadIdx.x) << kTopLog;
+    if (u >= job.status[3]) return;
+    const uint64_t g = last_le(job.ustart, job.G, u);
+    const uint64_t first = job.ustart[g], units = job.ustart[g + 1] - first;
+    const uint64_t j = ((u - first + ((uint64_t)1 << kTopLog) - 1) >> kTopLog);     // the subtree
+    if (j == 0 || j << kTopLog >= units) return;
+    const Inst I = inst_at(job, inst_of_chunk(job, g));
+    const uint64_t cc = chunk_ordinal(I, g - I.chunk_base);
+    const Chunk ch = chunk_geometry(I, cc);
+    const uint64_t obase = job.off[g];
+    uint64_t lo = 0, hi = tiles_of(ch.N, I.s), k = job.off[g + 1] - obase, run = 0;
+    uint32_t heap = 1;
+    for (uint32_t lev = 63 - __clzll(units) - kTopLog; lev-- > 0;) {
+        const uint64_t mid = lo + (hi - lo + 1) / 2;
+        const uint64_t X = hyp<1>(make_stream(I.seed, (uint32_t)cc, heap, TAG_TTREE), tile_range_slots(lo, hi, I.s, ch.N),
+                                  tile_range_slots(lo, mid, I.s, ch.N), k);
+        if ((j >> lev) & 1) { lo = mid; run += X; k -= X; heap = 2 * heap + 1; }
+        else { hi = mid; k = X; heap = 2 * heap; }
+    }
+    job.tile_off[job.tstart[g] + lo] = obase + run;
+}
+
+// ---------------------------------------------------------------------------
 // plan: each lane takes a contiguous range of planner units (a unit is a
 // subtree of <= 64 tiles of one chunk's tile tree, at depth d, index j), so
 // the chunk of its next unit is found by stepping forward.  For each unit
@@ -390,8 +437,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pl
     bool need_node = true, running = false;
     HypRun hr;
     hr.done = true;
-    if (active) {
-        g = last_le(job.ustart, job.G, u);
+    // unit u of chunk g, from the chunk's root or, where the unit's ancestor
+    // kTopLog levels up has its offset already, from there
+    auto open = [&]() {
         const Inst I = inst_at(job, inst_of_chunk(job, g));
         const uint64_t cc = chunk_ordinal(I, g - I.chunk_base);
         const Chunk ch = chunk_geometry(I, cc);
@@ -401,8 +449,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pl
         j = u - job.ustart[g];
         tbase = job.tstart[g];
         obase = job.off[g];
-        lo = 0; hi = tiles_of(Nc, s); k = job.off[g + 1] - obase; heap = 1; lev = 0; run = 0; sp = 0;
+        const uint64_t T = tiles_of(Nc, s);
+        lo = 0; hi = T; k = job.off[g + 1] - obase; heap = 1; lev = 0; run = 0;
+        if (job.tops && d > kTopLog) {
+            lev = d - kTopLog;
+            heap = (1u << lev) | (uint32_t)(j >> kTopLog);
+            unit_range(j >> kTopLog, lev, lo, hi);
+            const uint64_t from = lo ? job.tile_off[tbase + lo] : obase;
+            k = (hi < T ? job.tile_off[tbase + hi] : obase + k) - from;
+            run = from - obase;
+        }
         need_node = false;
+    };
+    if (active) {
+        g = last_le(job.ustart, job.G, u);
+        open();
     }
     while (__any(active)) {
         if (active) {
@@ -417,17 +478,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pl
                         active = false;
                     } else {
                         while (job.ustart[g + 1] <= u) ++g;
-                        const Inst I = inst_at(job, inst_of_chunk(job, g));
-                        const uint64_t cc = chunk_ordinal(I, g - I.chunk_base);
-                        const Chunk ch = chunk_geometry(I, cc);
-                        seed = I.seed; c = (uint32_t)cc; s = I.s; Nc = ch.N;
-                        const uint64_t units = job.ustart[g + 1] - job.ustart[g];
-                        d = 63 - __clzll(units);
-                        j = u - job.ustart[g];
-                        tbase = job.tstart[g];
-                        obase = job.off[g];
-                        lo = 0; hi = tiles_of(Nc, s); k = job.off[g + 1] - obase; heap = 1; lev = 0; run = 0;
-                        need_node = false;
+                        open();
                     }
                 }
             }

@@ -305,6 +305,7 @@ struct InstList {
 struct Prepared {
     InstList insts;
     uint64_t G = 0, Tb = 0;
+    uint64_t chunks_of[32] = {};      // chunks with 2^l .. 2^(l+1) - 1 tiles, by each instance's mean
     Layout L;
 };
 
@@ -314,6 +315,7 @@ kg_status prepare(const kg_instance *in, uint32_t count, Prepared &P)
     P.insts.resize(count);
     P.G = 0;
     P.Tb = 0;
+    memset(P.chunks_of, 0, sizeof(P.chunks_of));
     for (uint32_t i = 0; i < count; ++i) {
         uint64_t tb = 0;
         const kg_status st = plan_instance(in[i], P.insts[i], tb);
@@ -321,6 +323,8 @@ kg_status prepare(const kg_instance *in, uint32_t count, Prepared &P)
         P.insts[i].chunk_base = P.G;
         P.G += P.insts[i].nchunks;
         P.Tb += tb;
+        const uint64_t mean = tb / P.insts[i].nchunks;      // below 2^31 + 2
+        P.chunks_of[mean ? 63 - __builtin_clzll(mean) : 0] += P.insts[i].nchunks;
         // one-dimensional grids of one wave per 64 chunks
         if (P.G > kMaxChunks) return KG_ERANGE;
     }
@@ -457,6 +461,12 @@ bool small_job(const Prepared &P, int dev) { return P.Tb <= (uint64_t)g_num_cu[d
 // search costs.
 constexpr uint64_t kWholeChunks = 1024;
 
+// Levels of units' paths that plan_top_kernel has to save: about 80 ps each,
+// against 30 us for that launch (a batch of 64 instances, 272 thousand units of
+// 3 to 14 levels: the planner 250 -> 186 us, with a unit per lane 118).
+constexpr uint64_t kTopSaved = 500000;
+constexpr uint64_t kPlanRounds = 4;
+
 bool small_whole(const Prepared &P, const Job &job, int dev)
 {
     const Inst &I = job.one;
@@ -478,9 +488,20 @@ kg_status launch_generate(const Prepared &P, Job &job, int dev, hipStream_t s)
     // few units (their bound fits the resident lanes 8, 4 or 2 times over): a
     // group of lanes per unit shortens each unit's chain of variates
     const int par = ub * 8 <= pgrid * 64 ? 8 : ub * 4 <= pgrid * 64 ? 4 : ub * 2 <= pgrid * 64 ? 2 : 1;
+    // a unit per lane, up to kPlanRounds times the resident lanes: with the
+    // resident lanes only, a unit more than lanes gives half the lanes two and
+    // the others none (2^20 tiles in a batch 186 -> 118 us)
+    if (g_plan_waves <= 0) pgrid *= kPlanRounds;
     if (pgrid > (ub * par + 63) / 64) pgrid = (ub * par + 63) / 64;
+    // deep trees: the planner's units start below the root
+    uint64_t saved = 0;
+    for (uint32_t l = job.unit_log + kTopLog + 1; l < 32; ++l)
+        saved += (l - job.unit_log - kTopLog) * (P.chunks_of[l] << (l - job.unit_log));
+    job.tops = saved > kTopSaved;
     {
         KernelTimer tm(KG_KERNEL_PLAN, s);
+        if (job.tops)
+            hipLaunchKernelGGL(plan_top_kernel, dim3((uint32_t)((ub >> kTopLog) / 64 + 1)), dim3(64), 0, s, job);
         if (par == 8) hipLaunchKernelGGL(plan_kernel<8>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
         else if (par == 4) hipLaunchKernelGGL(plan_kernel<4>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
         else if (par == 2) hipLaunchKernelGGL(plan_kernel<2>, dim3((uint32_t)pgrid), dim3(64), 0, s, job);
