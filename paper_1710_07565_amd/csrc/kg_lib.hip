@@ -608,7 +608,8 @@ uint32_t rgg_level(uint64_t n, double r)
 // points) with four standard deviations to spare; denser grids keep a lane per
 // vertex, whose waves share the work of one cell.  A block is one cell, or
 // 2^D where a cell's points would leave too little to share the window's
-// set-up: in two dimensions below 8; in three, where 16 points share a matrix
+// set-up: in two dimensions below 10 (n = 8.9 million, 8.5 points per cell: one cell
+// 801 us, four 654; 11 points 900 and 979); in three, where 16 points share a matrix
 // product, below 7.5 (n = 10.9 and 14.7 million, 5.2 and 7 points per cell: one
 // cell 2.15 and 2.40 ms, eight 1.22 and 2.27; at 8 points 2.55 and 2.98).  From
 // 5 points per cell in three dimensions on (10 with one cell), the candidates
@@ -624,7 +625,7 @@ RggBlocks rgg_blocks(int D, uint64_t n, uint32_t L)
     RggBlocks P;
     const double a = ldexp((double)n, -(int)(D * L));     // points per cell
     if (n == 0 || a > (D == 2 ? 32.0 : 22.0)) return P;
-    P.B = L >= 1 && a < (D == 2 ? 8.0 : 7.5) ? 1 : 0;
+    P.B = L >= 1 && a < (D == 2 ? 10.0 : 7.5) ? 1 : 0;
     if (D == 3 && (P.B == 1 ? a >= 5.0 : a >= 10.0)) P.words = 16;
     if (D == 2 && P.B == 0) P.Q = 14;
     if (D == 3) P.list = P.B ? RggWindow<3, 1, 8>::LIST : RggWindow<3, 0, 8>::LIST;

@@ -23,3 +23,17 @@ def test_products_equal_oracle(kgref, a, f):
     want_points, want_edges = kgref.rgg3d(n, r, 77)
     assert np.array_equal(points.cpu().numpy().view(np.uint64), np.asarray(want_points).view(np.uint64).reshape(n, 3))
     assert np.array_equal(to_np_u32(edges), want_edges)
+
+
+@pytest.mark.parametrize("a", [9.9, 10.1])
+@pytest.mark.parametrize("f", [1.0, 0.6])
+def test_plane_line_equals_oracle(kgref, a, f):
+    """Two dimensions, on both sides of the line between one cell and four."""
+    import torch
+    kg = require_gpu()
+    n, r = int(a * 2**14), f * 2.0**-7
+    points, edges = kg.rgg2d(n, r, seed=78)
+    torch.cuda.synchronize()
+    want_points, want_edges = kgref.rgg2d(n, r, 78)
+    assert np.array_equal(points.cpu().numpy().view(np.uint64), np.asarray(want_points).view(np.uint64).reshape(n, 2))
+    assert np.array_equal(to_np_u32(edges), want_edges)
