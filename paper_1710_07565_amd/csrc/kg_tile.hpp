@@ -22,6 +22,8 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint64_t kGrabBig = 32;       // tiles per range a workgroup takes from the shared counter ...
 constexpr uint64_t kGrabSmall = 8;      // ... and near the end of the walk
 constexpr uint64_t kTailTiles = 64;     // tiles per workgroup handed out in small ranges
+constexpr uint32_t kStripeBig = 8;      // tiles of a batch's fixed ranges ...
+constexpr uint32_t kStripeSmall = 4;    // ... and where all of them are fixed
 constexpr uint64_t kStaticTiles = 16;   // fewer tiles per workgroup than this are shared out in advance
 
 // Wave-uniform 64-bit load through the scalar data cache.  Only for data
@@ -53,7 +55,7 @@ __device__ __forceinline__ uint64_t chunk_of_tile(const Job &job, uint64_t t)
     return lo;
 }
 
-// Ranges of tiles for a persistent grid: workgroup b takes a fixed range
+// Ranges of tiles for a persistent grid: workgroup b takes fixed ranges
 // first, then the next one not yet handed out, from the counter status[5]
 // (cleared by the scan kernel), so a workgroup whose tiles were cheap takes
 // more and none waits on a slow tail.  The counter is one address for all
@@ -61,47 +63,55 @@ __device__ __forceinline__ uint64_t chunk_of_tile(const Job &job, uint64_t t)
 // the whole grid, so it is kept for what balancing needs.  Grids with fewer
 // than kStaticTiles tiles per workgroup take none (an equal share each; a view
 // of 16,640 tiles on 4,096 workgroups, which took four ranges each from the
-// counter: whole call 287 -> 119 us; with a limit of 32, 64 the directed
-// calls gain a few per cent and a batch of 16 uneven graphs goes from 331 to
-// 425 us); up to 4 x kGrabBig, three
+// counter: whole call 287 -> 119 us); up to 4 x kGrabBig, three
 // quarters of the share are fixed and the rest goes in ranges of kGrabSmall
-// (n = 3,000,017: 235 us with half of it fixed, 223 with three quarters; a
-// batch of 16 uneven graphs 314 and 333); beyond that the
-// first range has kGrabBig tiles, then ranges of kGrabBig, and of kGrabSmall
-// for the last kTailTiles tiles per workgroup, so that the walk ends evenly
-// while the counter, the chunk search and the chunk set-up are paid once per
-// kGrabBig tiles for most of it.
+// (n = 3,000,017: 235 us with half of it fixed, 223 with three quarters);
+// beyond that the first range has kGrabBig tiles, then ranges of kGrabBig, and
+// of kGrabSmall for the last kTailTiles tiles per workgroup, so that the walk
+// ends evenly while the counter, the chunk search and the chunk set-up are paid
+// once per kGrabBig tiles for most of it.
+// A graph's tiles cost about the same, but those of a batch differ several
+// times between its graphs, and neighbours are alike: there a fixed share is
+// not one piece but every W-th range of kStripeSmall or kStripeBig tiles (batches of
+// 73, 16 and 10 uneven graphs 1248 -> 799, 226 -> 181 and 325 -> 341 us).
 // The bounds are formed anew at each take (a few scalar instructions) instead
 // of being held in scalar registers, which the tile loop has none to spare of.
 struct TileGrab {
-    bool first = true;
+    uint32_t taken = 0;      // fixed ranges so far
 
     // the next range [t0, t1) of T tiles; false once every range has been handed out
     __device__ __forceinline__ bool next(const Job &job, uint64_t &t0, uint64_t &t1)
     {
         const uint64_t T = ld_uni(job.status + 2);
-        const uint32_t W = gridDim.x;
-        // tiles of a fixed range, workgroups with one more
-        uint32_t each = kGrabBig, more = 0;
+        const uint32_t W = gridDim.x, b = blockIdx.x;
+        // fixed ranges of `each` tiles, workgroups with one more
+        uint32_t each = kGrabBig, more = 0, ranges = 1;
         uint64_t tail = (uint64_t)W * kTailTiles;
         if (T < (uint64_t)W * 4 * kGrabBig) {
             each = (uint32_t)T / W;
-            if (each < kStaticTiles) {
+            const bool all = each < kStaticTiles;
+            if (all) {
                 more = (uint32_t)T - each * W;
             } else {
                 each -= each / 4;
                 tail = T;
             }
+            if (job.ninst > 1) {
+                const uint32_t sub = all ? kStripeSmall : kStripeBig;
+                ranges = each / sub + (all ? 1u : 0u);
+                each = sub;
+                more = 0;
+            }
         }
-        if (first) {
-            first = false;
-            const uint32_t b = blockIdx.x;
-            t0 = (uint64_t)each * b + (b < more ? b : more);
+        uint64_t fixed = ((uint64_t)each * W + more) * ranges;
+        if (taken < ranges) {
+            t0 = (uint64_t)each * (taken * W + b) + (b < more ? b : more);
             t1 = t0 + each + (b < more ? 1 : 0);
+            t1 = t1 < T ? t1 : T;
+            ++taken;
             return t0 < t1;
         }
-        const uint64_t fixed = (uint64_t)each * W + more;
-        if (fixed == T) return false;
+        if (fixed >= T) return false;
         const uint64_t rest = T - fixed;
         const uint64_t head = rest > tail ? rest - tail : 0;    // tiles in large ranges
         const uint64_t qh = (head + kGrabBig - 1) / kGrabBig;
