@@ -281,14 +281,15 @@ kg_status kg_edge_hash(const uint32_t *d_edges, uint64_t n_edges, uint64_t *d_ha
 uint64_t kg_instance_seed(uint64_t base, uint32_t i);
 
 /* Non-semantic launch knobs (never change output bits).  A value of 0
- * restores the default (for the wave counts: as many workgroups as fit on a
- * compute unit at once).  Process-wide; set them before issuing calls. */
+ * restores the default (for the sampler's wave count: as many workgroups as
+ * fit on a compute unit at once; for the planner's: a lane per unit, up to four
+ * times what fits).  Process-wide; set them before issuing calls. */
 enum {
     KG_OPT_LEAF_CAP = 1,        /* samples a wave sorts in LDS per pass (128..1024) */
     KG_OPT_SAMPLE_WAVES = 2,    /* resident sampler waves per compute unit (1..32) */
     KG_OPT_PLAN_WAVES = 3,      /* resident tile-planner waves per compute unit (1..64) */
     KG_OPT_TIME_KERNELS = 4,    /* 1: bracket every kernel launch with hipEvents (not under capture) */
-    KG_OPT_COUNT_LANES = 5,     /* lanes per chunk in the count kernel (1, 2, 4 or 8; 0: the most for
+    KG_OPT_COUNT_LANES = 5,     /* lanes per chunk in the count kernel (1, 2, 4 or 8; 0: the most, up to 4, for
                                    which every workgroup of the launch is resident at once) */
     KG_OPT_SKIP_ROW = 6         /* kg_gnp_skip: positions kept per tile (64..1408; tiles with more
                                    events are generated again in the write pass) */
