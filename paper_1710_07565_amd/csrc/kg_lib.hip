@@ -666,11 +666,11 @@ uint64_t split_words(uint32_t depth)
 }
 
 // nw: the entries of the edge counts' scan (blocks, or waves of 64 vertices)
-RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
+RggLayout rgg_layout_form(int D, uint64_t n, uint32_t L, const RggBlocks &P)
 {
     RggLayout Y;
     Y.L = L;
-    Y.P = rgg_blocks(D, n, L);
+    Y.P = P;
     const bool blk = Y.P.B >= 0;
     Y.C = 1ull << (D * L);
     Y.nw = blk ? Y.P.nb : (n + 63) / 64;
@@ -689,6 +689,15 @@ RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
     Y.sums = take((Y.nbw + 1) * 8);
     Y.status = take(4 * 8);
     Y.total = o;
+    return Y;
+}
+
+// At least what the lane-per-vertex passes take (40 bytes per vertex and the
+// cells in two dimensions, 24 in three), so that the size keeps growing with n and L.
+RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
+{
+    RggLayout Y = rgg_layout_form(D, n, L, rgg_blocks(D, n, L));
+    Y.total = std::max(Y.total, rgg_layout_form(D, n, L, RggBlocks()).total);
     return Y;
 }
 
