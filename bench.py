@@ -583,7 +583,7 @@ def run_skip(args):
         "pct_hbm_write_bw": 100.0 * BYTES_PER_EDGE * value / (HBM_PEAK_GBS * 1e9),
         "roofline": {"bound": "hbm",
                      "limited_by": "write pass: the stored positions read (4 B per edge) and the edges written; "
-                                   "count pass: FP64 log and divide per gap (VALU)",
+                                   "count pass: Philox and the logarithm per gap (VALU)",
                      "kernel": "skip_emit_kernel",
                      "avg_launch_ms": wr_ms / max(wr_n, 1), "count_pass_ms": cnt_ms / max(cnt_n, 1),
                      # per launch: the timers also saw the warm-up launches
@@ -687,8 +687,8 @@ def run_rgg(args, dim=2):
         "pct_hbm_write_bw": 100.0 * sum(bytes_step) / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
         "per_launch_ms": per,
         "roofline": {"bound": "hbm",
-                     "limited_by": "per-vertex distance tests (FP64, neighbour points from L2), two passes",
-                     "kernel": "rgg_edges_kernel<true>" if dim == 2 else "rgg3_edges_kernel<true>",
+                     "limited_by": "distance tests and the lists, masks and set bits around them (VALU), two passes",
+                     "kernel": "rgg_block_write_kernel<%d>" % dim,
                      "avg_launch_ms": wr_ms,
                      "achieved": wr_bytes / (wr_ms * 1e-3) / 1e9, "unit": "GB/s", "peak": HBM_PEAK_GBS,
                      "frac": wr_bytes / (wr_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None},
