@@ -980,14 +980,10 @@ kg_status kg_gnp_skip(uint64_t n, double p, int directed, uint64_t seed, uint32_
         const uint32_t cap = (uint32_t)opt_or(g_skip_row, kSkipKeys) & ~3u;
         {
             KernelTimer tm(KG_KERNEL_PLAN, s);
-            if (rows) {
-                uint64_t ggrid = (uint64_t)g_num_cu[dev] * (uint64_t)g_gen_blocks_per_cu[dev];
-                if (ggrid > P.Tb + 1) ggrid = P.Tb + 1;
-                hipLaunchKernelGGL(skip_gen_kernel, dim3((uint32_t)ggrid), dim3(64), 0, s, job, row0, cap);
-                hipLaunchKernelGGL(skip_sums_kernel, dim3((uint32_t)nw), dim3(64), 0, s, job);
-            } else {
-                hipLaunchKernelGGL(skip_count_kernel, dim3((uint32_t)nw), dim3(64), 0, s, job);
-            }
+            uint64_t ggrid = (uint64_t)g_num_cu[dev] * (uint64_t)g_gen_blocks_per_cu[dev];
+            if (ggrid > P.Tb + 1) ggrid = P.Tb + 1;
+            hipLaunchKernelGGL(skip_gen_kernel, dim3((uint32_t)ggrid), dim3(64), 0, s, job, row0, rows ? cap : 0);
+            hipLaunchKernelGGL(skip_sums_kernel, dim3((uint32_t)nw), dim3(64), 0, s, job);
         }
         Job jw = job;
         jw.capacity = capacity_edges;

@@ -8,9 +8,9 @@
 // successes.  Count pass -> scan of the tile counts -> write pass.  When
 // the workspace holds a row of positions per tile, the count pass keeps the
 // events' positions and the write pass only decodes them (skip_gen_kernel,
-// skip_emit_kernel); otherwise the count pass runs one lane per tile and the
-// write pass generates the same trials again (skip_count_kernel,
-// skip_write_kernel).  The chunk and tile layout comes from the main path's
+// skip_emit_kernel); otherwise the write pass generates the same trials again
+// (skip_write_kernel), which costs about as much (directed n = 2^25, 536 million
+// edges: 2.75 ms a call, with the rows 2.74) but reads and writes no rows.  The chunk and tile layout comes from the main path's
 // count and offset kernels.
 #pragma once
 #include "kg_tile.hpp"
@@ -18,94 +18,6 @@
 namespace kg {
 
 constexpr uint32_t TAG_SKIP = 7;
-
-// Trials of one tile of St slots; `emit(x)` receives the tile-local keys of
-// the successes in ascending order.  Returns their number.
-template <class Emit>
-__device__ __forceinline__ uint64_t skip_trials(const Stream &st, uint64_t St, double p, Emit emit)
-{
-    if (!(p > 0.0)) return 0;
-    if (p >= 1.0) {
-        for (uint64_t x = 0; x < St; ++x) emit(x);
-        return St;
-    }
-    const bool flip = p > 0.5;
-    const double L = log1p_f64(flip ? -(1.0 - p) : -p);
-    Draws64 d(st);
-    uint64_t pos = 0, k = 0;
-    for (;;) {
-        const double U = unit_of(d.get());
-        const double g = floor(log_f64(U) / L);
-        const uint64_t next = g >= (double)(St - pos) ? St : pos + (uint64_t)g;
-        if (flip) {
-            for (uint64_t x = pos; x < next; ++x) { emit(x); ++k; }
-        } else if (next < St) {
-            emit(next);
-            ++k;
-        }
-        if (next >= St) return k;
-        pos = next + 1;
-    }
-}
-
-// Edge of chunk-local slot l (canonical local order of Sec. 4.1 / 4.2).
-__device__ __forceinline__ uint2 skip_decode(const Inst &I, const Chunk &ch, uint64_t l)
-{
-    if (I.directed) {
-        const uint64_t i = ch.row0 * (I.n - 1) + l;
-        const uint64_t u = i / (I.n - 1), w = i % (I.n - 1);
-        return make_uint2((uint32_t)u, (uint32_t)(w + (w >= u)));
-    }
-    if (!ch.diag) return make_uint2((uint32_t)(ch.a + l / ch.w), (uint32_t)(ch.b + l % ch.w));
-    // triangle: row r starts at r h - r (r + 1) / 2; the last start <= l
-    const uint64_t h = ch.h;
-    uint64_t lo = 0, hi = h - 1;
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (mid * h - mid * (mid + 1) / 2 <= l) lo = mid; else hi = mid;
-    }
-    const uint64_t st = lo * h - lo * (lo + 1) / 2;
-    return make_uint2((uint32_t)(ch.a + lo), (uint32_t)(ch.a + lo + 1 + (l - st)));
-}
-
-// The tile's chunk, geometry, stream and slot count.
-struct SkipTile {
-    Inst I;
-    Chunk ch;
-    Stream st;
-    uint64_t S, lbase;
-};
-
-__device__ __forceinline__ SkipTile skip_tile_at(const Job &job, uint64_t t)
-{
-    SkipTile r;
-    const uint64_t g = last_le(job.tstart, job.G, t);
-    r.I = inst_at(job, inst_of_chunk(job, g));
-    const uint64_t c = chunk_ordinal(r.I, g - r.I.chunk_base);
-    r.ch = chunk_geometry(r.I, c);
-    const uint64_t tl = t - job.tstart[g];
-    r.lbase = tl << r.I.s;
-    const uint64_t full = 1ull << r.I.s;
-    r.S = r.ch.N - r.lbase < full ? r.ch.N - r.lbase : full;
-    r.st = make_stream(r.I.seed, (uint32_t)c, (uint32_t)tl, TAG_SKIP);
-    return r;
-}
-
-// Count pass: one lane per tile; the count goes to tile_off[t] and the wave's
-// sum to queue[wave] (the main path's queue is free in this mode).
-__global__ __launch_bounds__(64) void skip_count_kernel(Job job)
-{
-    const uint64_t t = (uint64_t)blockIdx.x * 64 + threadIdx.x;
-    const uint64_t T = job.status[2];
-    uint64_t k = 0;
-    if (!job.status[1] && t < T) {
-        const SkipTile r = skip_tile_at(job, t);
-        k = skip_trials(r.st, r.S, r.I.p, [](uint64_t) {});
-        job.tile_off[t] = k;
-    }
-    const uint64_t incl = wave_incl_scan64(k);
-    if (threadIdx.x == 63) job.queue[blockIdx.x] = incl;
-}
 
 // Scan of the wave sums (one workgroup of 1024 lanes, rounds of 1024); the
 // total edges and the overflow flag.
@@ -160,7 +72,6 @@ __global__ __launch_bounds__(64) void skip_fix_kernel(Job job)
 // the gaps, scans them across the wave and appends the events below S to
 // LDS; full batches and the tile's last one are decoded and stored with
 // consecutive lanes on consecutive edges (the main sampler's emission).
-// The positions are those of skip_trials: the same draws, gaps and sums.
 constexpr uint32_t kSkipKeys = 1408;   // LDS batch (11 rounds of 128 events)
 
 // One round of a tile's waiting times: the positions x0, x1 of lane L's two
@@ -344,11 +255,11 @@ __global__ __launch_bounds__(64) void skip_write_kernel(Job job)
     }
 }
 
-// Slab variant (when the workspace holds it): a gap pass generates each
-// tile's events once, keeps the positions of up to `cap` of them in the
-// tile's slab row (slab + t cap, ascending) and writes the tile's edge count;
+// Gap pass: generates each tile's events once, and, where the workspace holds
+// a slab of rows (cap > 0), keeps the positions of up to `cap` of them in the
+// tile's row (slab + t cap, ascending) and writes the tile's edge count;
 // after the scan an emission pass only decodes the stored positions, so the
-// FP64 log and division of a gap are paid once instead of twice.  A tile
+// Philox block and logarithm of a gap are paid once instead of twice.  A tile
 // with more events than its row holds is generated again by the write path.
 __global__ __launch_bounds__(64) void skip_gen_kernel(Job job, uint32_t *slab, uint32_t cap)
 {
