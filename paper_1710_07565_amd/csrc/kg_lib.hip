@@ -636,10 +636,14 @@ RggBlocks rgg_blocks(int D, uint64_t n, uint32_t L)
 // Squares of quantised distances: below lo an edge for certain, above
 // lo + band none.  Rounding the positions down moves a distance by less than
 // sqrt(D) units (0.01 covers the rounding of the coordinates and the predicate).
+// The plane's candidate lists are padded with the window's corner, a whole
+// cell away from the block in both directions, so at a square of 2 4^Q or more:
+// `lo` stays below that.  It does by itself while r is at most a cell side; a grid
+// of one cell takes any r, and there no two points are as far apart as that.
 void rgg_block_band(int D, double r, uint32_t L, uint32_t Q, uint32_t &lo, uint32_t &band)
 {
     const double rq = fmin(ldexp(r, (int)(L + Q)), 65536.0), e = sqrt((double)D) + 0.01;
-    const double most = 2147483647.0;
+    const double most = D == 2 ? ldexp(1.0, 2 * (int)Q + 1) - 1.0 : 2147483647.0;
     const double a = rq > e ? floor((rq - e) * (rq - e)) : 0.0, b = ceil((rq + e) * (rq + e));
     lo = (uint32_t)fmin(a, most);
     band = (uint32_t)(fmin(b, most) - (double)lo);

@@ -399,7 +399,8 @@ __global__ __launch_bounds__(64) void rgg_block_count2_kernel(RggBlockJob J)
                 s_id[p] = v;
                 s_xy[p] = J.q[v] + s.pos[c];
             });
-            // padding: the window's corner, further from the block than r
+            // padding: the window's corner, at squares of at least lo, which
+            // are open at most, and open candidates are checked against C
             for (uint32_t p = K.C + lane; p < K.G * K.Cg; p += 64) s_xy[p] = 0;
             __syncthreads();
             const int32_t base = -(int32_t)J.lo;
