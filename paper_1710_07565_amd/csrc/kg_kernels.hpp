@@ -556,9 +556,9 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t v)
 // Triangle: rows counted from the bottom hold 1, 2, 3, ... slots.
 // Because n <= 2^32, rows, columns, section sizes and the divisor fit 32
 // bits.  The dividend c0 + x fits 32 bits unless the tile has close
-// to 2^32 slots ("wide").  Divisions use a binary64 reciprocal estimate
-// corrected by one step (exact for dividends below 2^33), or a shift when
-// the divisor is a power of two.
+// to 2^32 slots ("wide").  Divisions use the reciprocal multiplier, for wide
+// tiles a binary64 reciprocal estimate corrected by one step (exact for
+// dividends below 2^33), or a shift when the divisor is a power of two.
 struct Decoder {
     uint32_t type;      // 0 directed, 1 rectangle, 2 triangle
     uint32_t pow2;      // divisor is 2^sh
@@ -576,11 +576,9 @@ struct Decoder {
         if (!wide) {
             const uint32_t y = c0 + x;
             if (pow2) { rem = y & (dv - 1); return y >> sh; }
-            uint32_t q = (uint32_t)((double)y * rcp);
-            int32_t r = (int32_t)(y - q * dv);
-            if (r < 0) { --q; r += (int32_t)dv; }
-            else if ((uint32_t)r >= dv) { ++q; r -= (int32_t)dv; }
-            rem = (uint32_t)r;
+            // (no signed remainder: one of a divisor above 2^31 needs 32 bits)
+            const uint32_t q = (uint32_t)(((uint64_t)y * mul + add) >> 32) >> sh;
+            rem = y - q * dv;
             return q;
         }
         const uint64_t y = (uint64_t)c0 + x;
