@@ -555,10 +555,11 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t v)
 // Rectangle: local l -> (row r0 + l / width, column b + l % width).
 // Triangle: rows counted from the bottom hold 1, 2, 3, ... slots.
 // Because n <= 2^32, rows, columns, section sizes and the divisor fit 32
-// bits.  The dividend c0 + x fits 32 bits unless the tile has close
-// to 2^32 slots ("wide").  Divisions use the reciprocal multiplier, for wide
-// tiles a binary64 reciprocal estimate corrected by one step (exact for
-// dividends below 2^33), or a shift when the divisor is a power of two.
+// bits.  The dividend c0 + x fits 32 bits unless the tile's start in its row
+// and its slots add up to more than 2^32 ("wide").  Divisions use the
+// reciprocal multiplier, for wide tiles a binary64 reciprocal estimate corrected
+// by one step (exact for dividends below 2^33), or a shift when the divisor is
+// a power of two.
 struct Decoder {
     uint32_t type;      // 0 directed, 1 rectangle, 2 triangle
     uint32_t pow2;      // divisor is 2^sh

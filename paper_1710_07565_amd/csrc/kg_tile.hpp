@@ -814,7 +814,7 @@ __device__ __forceinline__ bool sample_tile(TileCtx &tc, uint32_t *s_key, uint32
         tc.full = uni(tc.S == (1ull << tc.bits));
     }
     tc.mask = (uint32_t)((1ull << tc.bits) - 1);
-    d.wide = s == 32 ? uni((uint64_t)d.c0 + tc.S > (1ull << 32)) : 0u;
+    d.wide = uni((uint64_t)d.c0 + tc.S > (1ull << 32));      // rows of more than 2^32 - 2^s slots
     tc.o0 = o0;
     const uint32_t lim = fast_cap < kFastDraws ? fast_cap : kFastDraws;
     const bool comp = 2 * k > tc.S;
@@ -885,8 +885,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 ++tc.st.b;
                 d.lbase += 1ull << s;
                 if (d.type != 2) {
+                    const uint32_t room = d.dv - w.rs;      // c0 + rs may pass 2^32
                     uint32_t c0 = d.c0 + w.rs, r0 = d.r0 + qs32;
-                    if (c0 >= d.dv) { c0 -= d.dv; ++r0; }
+                    if (d.c0 >= room) { c0 = d.c0 - room; ++r0; }
                     d.c0 = c0;
                     d.r0 = r0;
                 }

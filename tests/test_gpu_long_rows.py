@@ -34,3 +34,18 @@ def check(kgref, n, m, p, P, rank, s):
 def test_long_rows_equal_oracle(kgref, n, m, p, P, rank, s):
     assert 2**31 < n - 1 <= 2**32 - 2**s
     check(kgref, n, m, p, P, rank, s)
+
+
+# rows of more than 2^32 - 2^s slots: a tile that starts near a row's end has
+# slots past 2^32 counted from that row's start, and the next tile starts in the
+# row after
+WIDE = [(4 * 10**9, 6 * 10**12, None, 6 * 10**6, 1234567, 31),
+        (2**32 - 5, 2**43, None, 2**22, 77, 31), (2**32 - 5, 2**43, None, 2**20, 77, 31),
+        (2**32, 2**44, None, 2**22, 2**22 - 1, 30), (3900000007, 2 * 10**13, None, 2**23, 3, 29),
+        (2**32 - 1, 0, 2.7e-7, 2**20, 2**19, 31)]
+
+
+@pytest.mark.parametrize("n,m,p,P,rank,s", WIDE)
+def test_wide_rows_equal_oracle(kgref, n, m, p, P, rank, s):
+    assert n - 1 > 2**32 - 2**s and s < 32
+    check(kgref, n, m, p, P, rank, s)
