@@ -238,7 +238,11 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
  * n < 2^32, r >= 0 (KG_EINVAL for NaN or negative r); KG_ERANGE if
  * n^2 / 8^L > 2^36.  Asynchronous on `stream`; the workspace (or, if
  * d_workspace is NULL, a stream-ordered allocation) holds
- * kg_rgg3d_workspace_bytes. */
+ * kg_rgg3d_workspace_bytes.  The fast edge passes take 74 to 112 bytes of it
+ * per vertex; a smaller workspace (or allocation, if that much cannot be had)
+ * of 25 to 32 bytes per vertex and 8 per cell is accepted too and gets the
+ * passes that need no more, with the same output (about four times slower at
+ * n = 2^26).  KG_ENOSPC below that. */
 kg_status kg_rgg3d_workspace_bytes(uint64_t n, double r, uint64_t *bytes);
 kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32_t *d_edges,
                    uint64_t capacity_edges, uint64_t *d_total, void *d_workspace, uint64_t workspace_bytes,

@@ -312,6 +312,16 @@ def gnp_skip_workspace_bytes(n, p, directed=True, chunks=1):
     return int(b.value)
 
 
+def _rgg_workspace(need, device):
+    """A workspace of `need` bytes, or None where that does not fit: the
+    library then allocates for itself, the smallest one if it has to."""
+    torch = _torch()
+    try:
+        return torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def rgg2d_workspace_bytes(n, r):
     b = ctypes.c_uint64(0)
     _lib.check(_lib.lib().kg_rgg2d_workspace_bytes(int(n), float(r), ctypes.byref(b)), "kg_rgg2d_workspace_bytes")
@@ -342,15 +352,16 @@ def rgg2d(n, r, seed=1, points=None, out=None, total=None, workspace=None, strea
         if points is None:
             points = torch.empty((int(n), 2), dtype=torch.float64, device=dev)
         if workspace is None:
-            workspace = torch.empty(max(rgg2d_workspace_bytes(n, r), 1), dtype=torch.uint8, device=dev)
+            workspace = _rgg_workspace(rgg2d_workspace_bytes(n, r), dev)
         if total is None:
             total = torch.zeros(1, dtype=torch.uint64, device=dev)
+    ws = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.numel())
 
     def call(edges):
         st = _lib.lib().kg_rgg2d(int(n), float(r), int(seed) & (2**64 - 1),
                                  points.data_ptr() if points.numel() else None,
                                  edges.data_ptr() if edges.numel() else None, edges.shape[0], total.data_ptr(),
-                                 workspace.data_ptr(), workspace.numel(), _stream(stream))
+                                 *ws, _stream(stream))
         _lib.check(st, "kg_rgg2d")
 
     if out is not None:
@@ -400,15 +411,16 @@ def rgg3d(n, r, seed=1, points=None, out=None, total=None, workspace=None, strea
         if points is None:
             points = torch.empty((int(n), 3), dtype=torch.float64, device=dev)
         if workspace is None:
-            workspace = torch.empty(max(rgg3d_workspace_bytes(n, r), 1), dtype=torch.uint8, device=dev)
+            workspace = _rgg_workspace(rgg3d_workspace_bytes(n, r), dev)
         if total is None:
             total = torch.zeros(1, dtype=torch.uint64, device=dev)
+    ws = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.numel())
 
     def call(edges):
         st = _lib.lib().kg_rgg3d(int(n), float(r), int(seed) & (2**64 - 1),
                                  points.data_ptr() if points.numel() else None,
                                  edges.data_ptr() if edges.numel() else None, edges.shape[0], total.data_ptr(),
-                                 workspace.data_ptr(), workspace.numel(), _stream(stream))
+                                 *ws, _stream(stream))
         _lib.check(st, "kg_rgg3d")
 
     if out is not None:

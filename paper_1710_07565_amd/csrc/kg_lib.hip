@@ -696,16 +696,44 @@ RggLayout rgg_layout_form(int D, uint64_t n, uint32_t L, const RggBlocks &P)
     return Y;
 }
 
-// At least what the lane-per-vertex passes take (40 bytes per vertex and the
-// cells in two dimensions, 24 in three), so that the size keeps growing with n and L.
-RggLayout rgg_layout_any(int D, uint64_t n, uint32_t L)
-{
-    RggLayout Y = rgg_layout_form(D, n, L, rgg_blocks(D, n, L));
-    Y.total = std::max(Y.total, rgg_layout_form(D, n, L, RggBlocks()).total);
-    return Y;
-}
+// The layouts of a call: the lane-per-vertex passes', which a workspace has to
+// hold at least, and the block passes', which take more in three dimensions
+// (74 to 112 bytes per vertex against 25 to 32).  The first choice is the block
+// passes, except where their workspace with the points and the mean number of edges
+// passes 280 GiB, which no program has room for on a card of 288: n = 2^31 at
+// r = 0.55 (ln n / n)^(1/3), 192 GB + 52 + 129.  A caller's workspace that
+// holds only the lane-per-vertex layout gets that.
+struct RggLayouts {
+    RggLayout lane, first;
+    uint64_t need;           // workspace of the first choice
 
-RggLayout rgg_layout(uint64_t n, double r) { return rgg_layout_any(2, n, rgg_level(n, r)); }
+    RggLayouts(int D, uint64_t n, double r, uint32_t L)
+        : lane(rgg_layout_form(D, n, L, RggBlocks())), first(rgg_layout_form(D, n, L, rgg_blocks(D, n, L)))
+    {
+        const double ball = D == 2 ? 3.1416 * r * r : 4.1888 * r * r * r;
+        const double edges = 0.5 * (double)n * (double)n * fmin(ball, 1.0);
+        if (first.total > lane.total &&
+            (double)first.total + 8.0 * D * (double)n + 8.0 * edges > 280.0 * 1024 * 1024 * 1024)
+            first = lane;
+        // at least the lane-per-vertex size, which keeps growing with n and L
+        need = std::max(first.total, lane.total);
+    }
+};
+
+RggLayouts rgg_layouts(uint64_t n, double r) { return RggLayouts(2, n, r, rgg_level(n, r)); }
+
+// The layout for the caller's workspace, or for one that the library allocates
+// (the lane-per-vertex one if the first choice's cannot be had).
+kg_status rgg_acquire(Workspace &ws, RggLayout &Y, const RggLayouts &Ys, void *d_ws, uint64_t bytes, hipStream_t s)
+{
+    Y = Ys.first;
+    if (Ys.need > Ys.lane.total) {
+        if (!d_ws && acquire(ws, nullptr, 0, Ys.need, s) == KG_OK) return KG_OK;
+        if (!d_ws) (void)hipGetLastError();
+        if (!d_ws || bytes < Ys.need) Y = Ys.lane;
+    }
+    return acquire(ws, d_ws, bytes, std::max(Y.total, Ys.lane.total), s);
+}
 
 RggBlockJob rgg_block_job(int D, double r, const RggLayout &Y, char *ws, const double *pts, uint32_t *edges)
 {
@@ -757,7 +785,7 @@ uint32_t rgg3_level(uint64_t n, double r)
     return L;
 }
 
-RggLayout rgg3_layout(uint64_t n, double r) { return rgg_layout_any(3, n, rgg3_level(n, r)); }
+RggLayouts rgg3_layouts(uint64_t n, double r) { return RggLayouts(3, n, r, rgg3_level(n, r)); }
 
 kg_status rgg3_check(uint64_t n, double r)
 {
@@ -1018,7 +1046,7 @@ kg_status kg_rgg2d_workspace_bytes(uint64_t n, double r, uint64_t *bytes)
     if (!bytes) return KG_EINVAL;
     const kg_status st = rgg_check(n, r);
     if (st) return st;
-    *bytes = rgg_layout(n, r).total;
+    *bytes = rgg_layouts(n, r).need;
     return KG_OK;
 }
 
@@ -1038,9 +1066,9 @@ kg_status kg_rgg2d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     int dev = 0;
     st = ensure_init(&dev);
     if (st) return st;
-    const RggLayout Y = rgg_layout(n, r);
+    RggLayout Y;
     Workspace ws;
-    st = acquire(ws, d_workspace, workspace_bytes, Y.total, s);
+    st = rgg_acquire(ws, Y, rgg_layouts(n, r), d_workspace, workspace_bytes, s);
     if (st) return st;
     RggJob J;
     memset(&J, 0, sizeof(J));
@@ -1100,7 +1128,7 @@ kg_status kg_rgg3d_workspace_bytes(uint64_t n, double r, uint64_t *bytes)
     if (!bytes) return KG_EINVAL;
     const kg_status st = rgg3_check(n, r);
     if (st) return st;
-    *bytes = rgg3_layout(n, r).total;
+    *bytes = rgg3_layouts(n, r).need;
     return KG_OK;
 }
 
@@ -1120,9 +1148,9 @@ kg_status kg_rgg3d(uint64_t n, double r, uint64_t seed, double *d_points, uint32
     int dev = 0;
     st = ensure_init(&dev);
     if (st) return st;
-    const RggLayout Y = rgg3_layout(n, r);
+    RggLayout Y;
     Workspace ws;
-    st = acquire(ws, d_workspace, workspace_bytes, Y.total, s);
+    st = rgg_acquire(ws, Y, rgg3_layouts(n, r), d_workspace, workspace_bytes, s);
     if (st) return st;
     Rgg3Job J;
     memset(&J, 0, sizeof(J));
