@@ -168,8 +168,10 @@ __device__ __forceinline__ SkipRound skip_round(const TileCtx &tc, uint32_t r, u
         o.x1 = o.x0 + a1;
         o.v0 = o.x0 < S;
         o.v1 = o.x1 < S;
-        o.next = pos + (__builtin_amdgcn_readlane((uint32_t)incl, 63) |
-                        ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(incl >> 32), 63) << 32));
+        // (the builtin's result is signed: no sign bit may reach the upper half)
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)incl, 63);
+        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(incl >> 32), 63);
+        o.next = pos + ((uint64_t)hi << 32 | lo);
     }
     o.nv = (uint32_t)(__popcll(__ballot(o.v0)) + __popcll(__ballot(o.v1)));
     return o;
