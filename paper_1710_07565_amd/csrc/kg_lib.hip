@@ -975,6 +975,19 @@ kg_status kg_gnp_skip_workspace_bytes(uint64_t n, double p, int directed, uint32
     return KG_OK;
 }
 
+// The count pass that keeps no positions: a lane per tile where tiles have fewer
+// than 512 events (their gaps come one after the other) and there are either 2048
+// tiles per event of one, so that lanes suffice, or more tiles than the waves'
+// fixed shares hold (waves then queue for ranges, about 1 us per thousand tiles
+// however few their events).  Whole call without edges, lane / wave, us: 2^14
+// tiles of 4 events 19.5 / 26.4, of 64 40 / 26; 2^16 of 16 27 / 43, of 64 45 / 42;
+// 2^18 of 4 31 / 256, of 500 336 / 391; 2^20 of 4 71 / 1007, of 500 1099 / 1441.
+static bool skip_by_lanes(uint64_t n, double p, int directed, uint64_t tiles, uint64_t waves)
+{
+    const double events = fmin(p, 1.0 - p) * (double)n * (double)(n - 1) * (directed ? 1.0 : 0.5) / (double)tiles;
+    return events < 512.0 && ((double)tiles >= 2048.0 * events || tiles >= waves * kStaticTiles);
+}
+
 kg_status kg_gnp_skip(uint64_t n, double p, int directed, uint64_t seed, uint32_t chunks, uint32_t *d_edges,
                       uint64_t capacity_edges, uint64_t *d_total, void *d_workspace, uint64_t workspace_bytes,
                       void *stream)
@@ -1014,7 +1027,10 @@ kg_status kg_gnp_skip(uint64_t n, double p, int directed, uint64_t seed, uint32_
             KernelTimer tm(KG_KERNEL_PLAN, s);
             uint64_t ggrid = (uint64_t)g_num_cu[dev] * (uint64_t)g_gen_blocks_per_cu[dev];
             if (ggrid > P.Tb + 1) ggrid = P.Tb + 1;
-            hipLaunchKernelGGL(skip_gen_kernel, dim3((uint32_t)ggrid), dim3(64), 0, s, job, row0, rows ? cap : 0);
+            if (!rows && skip_by_lanes(n, p, directed, P.Tb, ggrid))
+                hipLaunchKernelGGL(skip_count_kernel, dim3((uint32_t)nw), dim3(64), 0, s, job);
+            else
+                hipLaunchKernelGGL(skip_gen_kernel, dim3((uint32_t)ggrid), dim3(64), 0, s, job, row0, rows ? cap : 0);
             hipLaunchKernelGGL(skip_sums_kernel, dim3((uint32_t)nw), dim3(64), 0, s, job);
         }
         Job jw = job;

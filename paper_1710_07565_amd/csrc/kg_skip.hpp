@@ -311,6 +311,33 @@ __global__ __launch_bounds__(64) void skip_gen_kernel(Job job, uint32_t *slab, u
     }
 }
 
+// Counts without positions, a lane per tile: for many tiles of few events, where
+// most of a wave's 128 gaps would lie past its tile's end (kg_gnp_skip's rule).
+__global__ __launch_bounds__(64) void skip_count_kernel(Job job)
+{
+    const Inst I = job.one;
+    const bool flip = I.p > 0.5;
+    const bool all = I.p >= 1.0;
+    __shared__ double2 s_tab[kGapTab];
+    load_gap_tab(s_tab);
+    const GapLaw gap = gap_law(all ? -1.0 : log1p_f64(flip ? -(1.0 - I.p) : -I.p), I.s, s_tab);
+    const uint64_t t = (uint64_t)blockIdx.x * 64 + threadIdx.x;
+    if (t >= job.status[2]) return;
+    const uint64_t g = last_le(job.tstart, job.G, t), tl = t - job.tstart[g];
+    const uint64_t lo = tl << I.s, end = lo + (1ull << I.s), N = chunk_geometry(I, g).N;
+    const uint64_t S = (end < N ? end : N) - lo;
+    uint64_t nev = 0, pos = 0;
+    if (!all && I.p > 0.0) {
+        Draws64 d(make_stream(I.seed, (uint32_t)g, (uint32_t)tl, TAG_SKIP));
+        for (;; ++nev) {
+            const double w = gap(unit_of(d.get()));
+            if (w >= (double)(S - pos)) break;
+            pos += (uint64_t)w + 1;
+        }
+    }
+    job.tile_off[t] = all ? S : !(I.p > 0.0) ? 0 : flip ? S - nev : nev;
+}
+
 // The gap pass's tile counts summed per wave of 64 tiles (for the scan).
 __global__ __launch_bounds__(64) void skip_sums_kernel(Job job)
 {
