@@ -305,6 +305,7 @@ struct InstList {
 struct Prepared {
     InstList insts;
     uint64_t G = 0, Tb = 0;
+    bool sparse = false;              // some instance has tiles of 2^32 slots
     uint64_t chunks_of[32] = {};      // chunks with 2^l .. 2^(l+1) - 1 tiles, by each instance's mean
     Layout L;
 };
@@ -315,6 +316,7 @@ kg_status prepare(const kg_instance *in, uint32_t count, Prepared &P)
     P.insts.resize(count);
     P.G = 0;
     P.Tb = 0;
+    P.sparse = false;
     memset(P.chunks_of, 0, sizeof(P.chunks_of));
     for (uint32_t i = 0; i < count; ++i) {
         uint64_t tb = 0;
@@ -323,6 +325,7 @@ kg_status prepare(const kg_instance *in, uint32_t count, Prepared &P)
         P.insts[i].chunk_base = P.G;
         P.G += P.insts[i].nchunks;
         P.Tb += tb;
+        P.sparse |= P.insts[i].s == 32;
         const uint64_t mean = tb / P.insts[i].nchunks;      // below 2^31 + 2
         P.chunks_of[mean ? 63 - __builtin_clzll(mean) : 0] += P.insts[i].nchunks;
         // one-dimensional grids of one wave per 64 chunks
@@ -517,7 +520,8 @@ kg_status launch_generate(const Prepared &P, Job &job, int dev, hipStream_t s)
     if (qgrid > P.Tb + 1) qgrid = P.Tb + 1;
     {
         KernelTimer tm(KG_KERNEL_SAMPLE, s);
-        hipLaunchKernelGGL(tile_kernel, dim3((uint32_t)sgrid), dim3(64), 0, s, job);
+        if (P.sparse) hipLaunchKernelGGL(tile_sparse_kernel, dim3((uint32_t)sgrid), dim3(64), 0, s, job);
+        else hipLaunchKernelGGL(tile_kernel, dim3((uint32_t)sgrid), dim3(64), 0, s, job);
     }
     {
         KernelTimer tm(KG_KERNEL_QUEUE, s);

@@ -300,9 +300,9 @@ __device__ __forceinline__ void cx(uint32_t &a, uint32_t &b)
 // is sorted on its own, as a sequence of at most R elements, which R rounds
 // of odd-even transposition sort (Knuth, TAOCP vol. 3, 5.3.4) always sort.
 // Returns whether two adjacent positions are equal (repeats; count_repeats
-// counts them).
-template <int W>
-__device__ __forceinline__ bool oddeven(uint32_t *s, uint32_t R)
+// counts them); with PADS, other than `pads` pairs of equal padding.
+template <int W, bool PADS>
+__device__ __forceinline__ bool oddeven(uint32_t *s, uint32_t R, uint32_t pads)
 {
     const uint32_t lane = lane_here();
     const uint32_t p0 = W * lane;
@@ -321,6 +321,12 @@ __device__ __forceinline__ bool oddeven(uint32_t *s, uint32_t R)
     }
     wstore<W>(s, p0, v);
     const uint32_t nx = from_next_lane(v[0], ~v[W - 1]);       // lane 63: a value unequal to its last key
+    if (PADS) {
+        uint32_t n = (uint32_t)__popcll(__ballot(v[W - 1] == nx));
+#pragma unroll
+        for (int i = 0; i + 1 < W; ++i) n += (uint32_t)__popcll(__ballot(v[i] == v[i + 1]));
+        return n != pads;
+    }
     uint64_t eq = __ballot(v[W - 1] == nx);
 #pragma unroll
     for (int i = 0; i + 1 < W; ++i) eq |= __ballot(v[i] == v[i + 1]);
@@ -375,8 +381,17 @@ __device__ __forceinline__ uint32_t wave_max32(uint32_t v)
 // the sorted set in s[0..ke) and returns true, or returns false once J would
 // exceed lim (or in the rare cases the queue kernel handles); the counters
 // are zero again whenever it returns.
+// Jobs with tiles of 2^32 slots (s = 32, fewer than 1120 keys on average) have
+// copies of their own (SPARSE).  Keys of 32 bits leave no values for a padding
+// without repeats, and to look all keys through for repeats on that account made
+// these tiles slower than a form without insertions; the copies count the equal
+// pairs.  Up to kSparseDraws - 16 keys (room for repeats) a copy of three rounds
+// also saves the steps over the other two.  n = 2^28, 2^23 tiles of 32, 300, 500 and
+// 1000 keys: 7.0, 9.9, 11.4 and 17.7 ms without the copies, 6.2, 8.3, 9.3 and 15.1 with.
 constexpr uint32_t kBucketWords = 512;   // one 32-bit counter per bucket
 constexpr uint32_t kMaxRounds = 32;      // a fuller bucket sends the tile to the queue
+constexpr int kSparseRounds = 3;
+constexpr uint32_t kSparseDraws = 256 * kSparseRounds;
 constexpr uint32_t kMissing = 6;         // values inserted one by one (a pass costs about as much as six)
 
 // Draws J, J + 1, ... of the tile one by one until the sorted keys s[0..V)
@@ -460,6 +475,7 @@ __device__ __forceinline__ uint32_t draws_for(float e, float f)
     return (uint32_t)fmaxf(e, x);
 }
 
+template <int ROUNDS, bool SPARSE>
 __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t *cnt, uint32_t ke, uint32_t lim)
 {
     const uint32_t lane = threadIdx.x;
@@ -489,9 +505,9 @@ __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t
         uint64_t coll = 0;      // a valid key equal to ~0 (2^32-slot tiles only)
         bool hit = false;
         // the draws stay in registers (x[4 e + q] = draw 256 e + 4 lane + q)
-        uint32_t x[4 * kFastRounds], rk[4 * kFastRounds];
+        uint32_t x[4 * ROUNDS], rk[4 * ROUNDS];
 #pragma unroll
-        for (int e = 0; e < (int)kFastRounds; ++e) {
+        for (int e = 0; e < ROUNDS; ++e) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) { x[4 * e + q] = kNone; rk[4 * e + q] = 0; }
             const uint32_t blk = lane + 64u * e;
@@ -558,7 +574,7 @@ __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t
         __syncthreads();
         {
 #pragma unroll
-            for (int e = 0; e < (int)kFastRounds; ++e) {
+            for (int e = 0; e < ROUNDS; ++e) {
                 if ((uint32_t)e < nclean) {
                     // every entry of a clean round is a valid key
                     uint32_t old[4];
@@ -598,19 +614,22 @@ __device__ __forceinline__ bool fast_set(const TileCtx &t, uint32_t *s, uint32_t
             constexpr uint32_t kSpan[6] = {256, 512, 768, 1024, 1152, 1280};
             const uint32_t span = kSpan[mode];
             // ascending above every key, so that no two are equal (in a tile of
-            // 2^32 slots they all are ~0, and the repeats are counted always)
+            // 2^32 slots they all are ~0: the sparse copy counts the equal pairs
+            // among them, the common one the repeats always)
+            const uint32_t pads = t.bits < 32 || V == span ? 0u : span - 1 - V;
             for (uint32_t p = V + lane; p < span; p += 64) s[p] = t.bits < 32 ? 0x80000000u | p : kNone;
             __syncthreads();
             bool rep;
-            if (mode == 0) rep = oddeven<4>(s, R);
-            else if (mode == 1) rep = oddeven<8>(s, R);
-            else if (mode == 2) rep = oddeven<12>(s, R);
-            else if (mode == 3) rep = oddeven<16>(s, R);
-            else if (mode == 4) rep = oddeven<18>(s, R);
-            else rep = oddeven<20>(s, R);
+            if (mode == 0) rep = oddeven<4, SPARSE>(s, R, pads);
+            else if (mode == 1) rep = oddeven<8, SPARSE>(s, R, pads);
+            else if (ROUNDS <= 3 || mode == 2) rep = oddeven<12, SPARSE>(s, R, pads);
+            else if (mode == 3) rep = oddeven<16, SPARSE>(s, R, pads);
+            else if (mode == 4) rep = oddeven<18, SPARSE>(s, R, pads);
+            else rep = oddeven<20, SPARSE>(s, R, pads);
             __syncthreads();
             ndup = rep ? count_repeats(s, V, dup) : 0u;
         }
+        if (SPARSE && __builtin_expect(V == ke && ndup == 0, 1)) return true;
         const uint32_t D = V - ndup;
         if (D > ke) {
             guess = false;
@@ -800,7 +819,9 @@ __device__ __forceinline__ void emit_tile(const TileCtx &t, const uint32_t *s, u
 }
 
 // Slots of the tile whose stream and decoder the context holds, and its edges:
-// `last_S` slots if it is the chunk's `last` tile (0: 2^32), else 2^s.
+// `last_S` slots if it is the chunk's `last` tile (0: 2^32), else 2^s.  SPARSE: with
+// the copy of the base case for s = 32 (few tiles of a wave each do without).
+template <bool SPARSE>
 __device__ __forceinline__ bool sample_tile(TileCtx &tc, uint32_t *s_key, uint32_t *s_cnt, uint64_t o0, uint64_t k,
                                             uint32_t s, bool last, uint32_t last_S, uint32_t fast_cap)
 {
@@ -821,7 +842,10 @@ __device__ __forceinline__ bool sample_tile(TileCtx &tc, uint32_t *s_key, uint32
     const uint64_t ke = comp ? tc.S - k : k;
     if (ke == 0) {
         emit_complement(tc, s_key, 0, 0, tc.S, 0);
-    } else if (ke <= lim && fast_set(tc, s_key, s_cnt, (uint32_t)ke, lim)) {
+    } else if (ke <= lim &&
+               ((SPARSE && s == 32 && ke <= kSparseDraws - 16 &&
+                 fast_set<kSparseRounds, true>(tc, s_key, s_cnt, (uint32_t)ke, lim < kSparseDraws ? lim : kSparseDraws)) ||
+                fast_set<(int)kFastRounds, SPARSE>(tc, s_key, s_cnt, (uint32_t)ke, lim))) {
         if (!comp) emit_tile(tc, s_key, (uint32_t)ke);
         else emit_complement(tc, s_key, (uint32_t)ke, 0, tc.S, 0);
     } else {
@@ -838,12 +862,10 @@ __device__ __forceinline__ void clear_counters(uint32_t *s_cnt)
     __syncthreads();
 }
 
-// 4 waves per SIMD (up to 128 VGPRs, no spills); the LDS of a wave (keys of
-// up to 1280 draws and 512 bucket counters, 7.2 KB) would allow 5
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void tile_kernel(Job job)
+// A workgroup's ranges of tiles.
+template <bool SPARSE>
+__device__ __forceinline__ void sample_ranges(const Job &job, uint32_t *s_key, uint32_t *s_cnt)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
-    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];   // bucket counters, then starts
     if (ld_uni(job.status + 1)) return;
     clear_counters(s_cnt);
     TileWalk w;
@@ -875,7 +897,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 o_pre = ld_uni(job.tile_off + t + i + 2);
                 const uint64_t k = o_next - o0;
                 if (k != 0) {
-                    if (!sample_tile(tc, s_key, s_cnt, o0, k, s, i == full, last_S, job.fast_cap) && threadIdx.x == 0) {
+                    if (!sample_tile<SPARSE>(tc, s_key, s_cnt, o0, k, s, i == full, last_S, job.fast_cap) &&
+                        threadIdx.x == 0) {
                         const uint64_t q = atomicAdd((unsigned long long *)(job.status + 4), 1ull);
                         job.queue[q] = t + i;
                     }
@@ -899,6 +922,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             while (ld_uni(job.tstart + g + 1) <= t) ++g;
         }
     }
+}
+
+// 4 waves per SIMD (up to 128 VGPRs, no spills); the LDS of a wave (keys of
+// up to 1280 draws and 512 bucket counters, 7.2 KB) would allow 5
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void tile_kernel(Job job)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];   // bucket counters, then starts
+    sample_ranges<false>(job, s_key, s_cnt);
+}
+
+// The same for jobs with tiles of 2^32 slots: a kernel of its own, since the second
+// copy of the base case costs the others' tiles about 1 %.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void tile_sparse_kernel(Job job)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[kKeyWords];
+    __shared__ __attribute__((aligned(16))) uint32_t s_cnt[kBucketWords];
+    sample_ranges<true>(job, s_key, s_cnt);
 }
 
 // The sampler of small jobs (at most a tile per workgroup): the wave walks
@@ -982,7 +1023,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8))) void
         else { lo = mid; A = M; o0 += X; k -= X; heap = 2 * heap + 1; }
     }
     if (k == 0) return;
-    if (!sample_tile(tc, s_key, s_cnt, o0, k, w.s, t + 1 == ge, last_S, job.fast_cap)) {
+    if (!sample_tile<false>(tc, s_key, s_cnt, o0, k, w.s, t + 1 == ge, last_S, job.fast_cap)) {
         __syncthreads();
         leaf_sample<kCapMax>(tc, s_key, s_hist, k, job.leaf_cap < kCapMax ? job.leaf_cap : kCapMax);
     }
