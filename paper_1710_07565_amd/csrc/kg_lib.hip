@@ -831,11 +831,12 @@ void rgg_split(int D, uint64_t n, uint64_t seed, uint32_t L, uint64_t *mid, uint
     for (uint32_t i = 0, p = 0; i < launches; ++i) {
         const uint32_t q = (depth - p) / (launches - i);
         uint64_t *out = i + 1 == launches ? coff : mid + (i & 1) * split_words(depth);
-        const dim3 grid((uint32_t)(1ull << p)), block(i == 0 ? 1024 : 256);
+        const dim3 grid((uint32_t)(1ull << p)), block(i == 0 ? 1024 : p < 16 ? 256 : 64);
+        const size_t lds = 2 * sizeof(uint32_t) << q;
         if (D == 2)
-            hipLaunchKernelGGL(rgg_split_kernel<2>, grid, block, 0, s, seed, n, (uint32_t)TAG_RTREE, in, out, p, q);
+            hipLaunchKernelGGL(rgg_split_kernel<2>, grid, block, lds, s, seed, n, (uint32_t)TAG_RTREE, in, out, p, q);
         else
-            hipLaunchKernelGGL(rgg_split_kernel<3>, grid, block, 0, s, seed, n, (uint32_t)TAG_RTREE3, in, out, p, q);
+            hipLaunchKernelGGL(rgg_split_kernel<3>, grid, block, lds, s, seed, n, (uint32_t)TAG_RTREE3, in, out, p, q);
         in = out;
         p += q;
     }

@@ -79,6 +79,11 @@ __device__ __forceinline__ uint32_t gather_bits(uint32_t z)
 // In the launches of few workgroups, while a level has few nodes, its variates'
 // latency is the time, and 8 lanes try proposals of each; elsewhere a node has
 // one lane.
+// A launch of very many workgroups (three launches, 2^16 nodes and more) gives a
+// node one wave: half its levels have fewer nodes than a wave has lanes.  Depth 26,
+// 2^26 points: 3.39 ms with 256 lanes and LDS for kSplitMost levels, 1.45 so, and
+// 1.96 in one launch per level; with 2^12 workgroups 256 lanes are better (depth
+// 24 0.37 ms, one wave 0.71).
 // Measured against one launch per level and a scan (14 launches instead of 2):
 // n = 1,000,003 in two dimensions 110 -> 43 us, n = 2^26 0.31 -> 0.28 ms; three
 // dimensions 0.62 -> 0.57 ms.
@@ -91,15 +96,15 @@ template <int D>
 __global__ __launch_bounds__(1024) void rgg_split_kernel(uint64_t seed, uint64_t n, uint32_t tag, const uint64_t *in,
                                                          uint64_t *out, uint32_t p, uint32_t q)
 {
-    __shared__ uint32_t s_n[2][1u << kSplitMost];
+    extern __shared__ uint32_t s_counts[];       // two buffers of 2^q
     __shared__ uint32_t s_w[16];
     const uint32_t t = threadIdx.x, NT = blockDim.x;
     const uint64_t node = blockIdx.x;
     const uint64_t first = p ? in[node] : 0, last = p ? in[node + 1] : n;
-    if (t == 0) s_n[0][0] = (uint32_t)(last - first);
+    if (t == 0) s_counts[0] = (uint32_t)(last - first);
     __syncthreads();
-    uint32_t cur = 0;
-    for (uint32_t d = 0; d < q; ++d, cur ^= 1) {
+    uint32_t cur = 0, nxt = 1u << q;             // the level's counts, its children's
+    for (uint32_t d = 0; d < q; ++d, cur ^= 1u << q, nxt ^= 1u << q) {
         const uint32_t m = 1u << d, depth = p + d, l = depth / D, r = depth - D * l;
         auto stream = [&](uint32_t i) {
             const uint32_t g = (uint32_t)(node << d) + i;
@@ -107,19 +112,19 @@ __global__ __launch_bounds__(1024) void rgg_split_kernel(uint64_t seed, uint64_t
             return make_stream(seed, g >> r, ((1u << D) - 1) * l + slot, tag);
         };
         auto put = [&](uint32_t i, uint32_t k, uint32_t x) {
-            s_n[cur ^ 1][2 * i] = x;
-            s_n[cur ^ 1][2 * i + 1] = k - x;
+            s_counts[nxt + 2 * i] = x;
+            s_counts[nxt + 2 * i + 1] = k - x;
         };
         if (m * kSplitLanes <= NT && gridDim.x <= kSplitFew) {
             const uint32_t i = t / kSplitLanes;
             if (i < m) {
-                const uint32_t k = s_n[cur][i];
+                const uint32_t k = s_counts[cur + i];
                 const uint32_t x = (uint32_t)binom<kSplitLanes>(stream(i), k, 0.5);
                 if (t % kSplitLanes == 0) put(i, k, x);
             }
         } else {
             for (uint32_t i = t; i < m; i += NT) {
-                const uint32_t k = s_n[cur][i];
+                const uint32_t k = s_counts[cur + i];
                 put(i, k, (uint32_t)binom(stream(i), k, 0.5));
             }
         }
@@ -129,19 +134,19 @@ __global__ __launch_bounds__(1024) void rgg_split_kernel(uint64_t seed, uint64_t
     const uint32_t m = 1u << q, per = (m + NT - 1) / NT, lane = t & 63, w = t >> 6;
     const uint32_t i0 = min(t * per, m), i1 = min(i0 + per, m);
     uint32_t sum = 0;
-    for (uint32_t i = i0; i < i1; ++i) sum += s_n[cur][i];
+    for (uint32_t i = i0; i < i1; ++i) sum += s_counts[cur + i];
     const uint32_t incl = wave_incl_scan32(sum);
     if (lane == 63) s_w[w] = incl;
     __syncthreads();
     uint32_t run = incl - sum;
     for (uint32_t j = 0; j < w; ++j) run += s_w[j];
     for (uint32_t i = i0; i < i1; ++i) {
-        const uint32_t c = s_n[cur][i];
-        s_n[cur][i] = run;
+        const uint32_t c = s_counts[cur + i];
+        s_counts[cur + i] = run;
         run += c;
     }
     __syncthreads();
-    for (uint32_t i = t; i < m; i += NT) out[node * m + i] = first + s_n[cur][i];
+    for (uint32_t i = t; i < m; i += NT) out[node * m + i] = first + s_counts[cur + i];
     if (t == 0 && node + 1 == gridDim.x) out[(uint64_t)gridDim.x * m] = n;
 }
 
