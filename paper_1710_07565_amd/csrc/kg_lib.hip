@@ -607,28 +607,37 @@ uint32_t rgg_level(uint64_t n, double r)
 
 // The block kernels (kg_rgg_block.hpp) take grids with few points per cell,
 // which the level rule gives unless the radius (or the level limit) keeps the
-// cells large: in two dimensions up to 32 points per cell, in three up to 22,
-// so that a block's result words hold its candidates (at most 6, of 18, cells'
-// points) with four standard deviations to spare; denser grids keep a lane per
-// vertex, whose waves share the work of one cell.  A block is one cell, or
-// 2^D where a cell's points would leave too little to share the window's
-// set-up: in two dimensions below 10 (n = 8.9 million, 8.5 points per cell: one cell
-// 801 us, four 654; 11 points 900 and 979); in three, where 16 points share a matrix
-// product, below 7.5 (n = 10.9 and 14.7 million, 5.2 and 7 points per cell: one
-// cell 2.15 and 2.40 ms, eight 1.22 and 2.27; at 8 points 2.55 and 2.98).  From
-// 5 points per cell in three dimensions on (10 with one cell), the candidates
-// need 16 words per vertex.
+// cells large: in two dimensions up to 32 points per cell, in three up to 22;
+// denser grids keep a lane per vertex, whose waves share the work of one cell.
+// A block is one cell, or 2^D where a cell's points would leave too little to
+// share the window's set-up: in two dimensions below 10 (n = 8.9 million, 8.5
+// points per cell: one cell 801 us, four 654; 11 points 900 and 979); in three,
+// where 16 points share a matrix product, below 7.5 (n = 10.9 and 14.7 million,
+// 5.2 and 7 points per cell: one cell 2.15 and 2.40 ms, eight 1.22 and 2.27; at 8
+// points 2.55 and 2.98).  Below 2.1 points per cell, 1.5 with a radius under an
+// eighth of a cell, the plane keeps a lane per vertex too: a block of 16 cells then
+// has fewer points than lanes (4^12 cells, both edge passes, lane / block us:
+// 1 point at a cell's radius 993 / 2009, 2 points 2195 / 2280, 2.5 points 2824 /
+// 2427; at 10^-4 of a cell 1 point 932 / 1383, 1.6 points 1553 / 1463).
+// A block's candidates are its own points and those of the window's cells after
+// it: up to 6 cells' (one cell) or 11 (four) in two dimensions, 20 or 45 in three.
+// Beyond the result words' bits it is tested in binary64, which keeps the passes
+// right and costs time only: with one cell per block at 32 (256 bits), 10 (256) and
+// 22 points (512) that takes 4.6, 4.0 and 3.4 standard deviations, with eight cells at 5
+// points (256) 2.1, so that 2 in 100 of the fullest windows are tested so; from
+// 5 points on (10 with one cell) the words are 16.
 struct RggBlocks {
     int B = -1;                // block level (cells of side 2^B); -1: not taken
     uint32_t words = 8, Q = 13, list = 0;      // result words per vertex, position bits, kept list words per block
     uint64_t nb = 0;
 };
 
-RggBlocks rgg_blocks(int D, uint64_t n, uint32_t L)
+RggBlocks rgg_blocks(int D, uint64_t n, double r, uint32_t L)
 {
     RggBlocks P;
     const double a = ldexp((double)n, -(int)(D * L));     // points per cell
     if (n == 0 || a > (D == 2 ? 32.0 : 22.0)) return P;
+    if (D == 2 && L >= 1 && a < (ldexp(r, (int)L) < 0.125 ? 1.5 : 2.1)) return P;
     P.B = L >= 1 && a < (D == 2 ? 10.0 : 7.5) ? 1 : 0;
     if (D == 3 && (P.B == 1 ? a >= 5.0 : a >= 10.0)) P.words = 16;
     if (D == 2 && P.B == 0) P.Q = 14;
@@ -712,7 +721,7 @@ struct RggLayouts {
     uint64_t need;           // workspace of the first choice
 
     RggLayouts(int D, uint64_t n, double r, uint32_t L)
-        : lane(rgg_layout_form(D, n, L, RggBlocks())), first(rgg_layout_form(D, n, L, rgg_blocks(D, n, L)))
+        : lane(rgg_layout_form(D, n, L, RggBlocks())), first(rgg_layout_form(D, n, L, rgg_blocks(D, n, r, L)))
     {
         const double ball = D == 2 ? 3.1416 * r * r : 4.1888 * r * r * r;
         const double edges = 0.5 * (double)n * (double)n * fmin(ball, 1.0);
