@@ -725,9 +725,10 @@ __device__ __forceinline__ uint2 dec_narrow(const DecV &d, uint32_t x)
 // Triangle slots (rows of a section counted down by one slot each) relative
 // to the tile's first row: slot y of rows of L, L - 1, ... slots lies in row
 // r = floor(B - sqrt(B^2 - 2 y)), B = L + 1/2, as r = 2 y / (B + sqrt(...))
-// without the cancellation.  The hardware's square root and reciprocal are
-// good to 2^-28 and r below 2^26, so the estimate is off by one at most and
-// the row's integer bounds correct it.  32-bit products suffice while
+// without the cancellation.  y < 2^32 keeps r below 92,682 (rows that all hold
+// at least one slot, the r-th from the end r of them), so with the hardware's
+// square root and reciprocal (2^29 ulp, 2^-23, each at worst) the estimate is off by
+// one at most, and the row's integer bounds correct it.  32-bit products suffice while
 // y + L < 2^32 and L < 2^26 (larger tiles and sections: emit_sorted).  About
 // 20 vector instructions per slot against 150 for the 64-bit formula:
 // undirected n = 4,194,381, m = 67,108,867 in one section 409 -> 252 us, in
@@ -846,7 +847,9 @@ __device__ __forceinline__ bool sample_tile(TileCtx &tc, uint32_t *s_key, uint32
                ((SPARSE && s == 32 && ke <= kSparseDraws - 16 &&
                  fast_set<kSparseRounds, true>(tc, s_key, s_cnt, (uint32_t)ke, lim < kSparseDraws ? lim : kSparseDraws)) ||
                 fast_set<(int)kFastRounds, SPARSE>(tc, s_key, s_cnt, (uint32_t)ke, lim))) {
-        if (!comp) emit_tile(tc, s_key, (uint32_t)ke);
+        // (a triangle's tiles of 2^32 slots are too large for dec_tri)
+        if (!comp && SPARSE && d.type == 2 && s == 32) emit_sorted(tc, s_key, (uint32_t)ke);
+        else if (!comp) emit_tile(tc, s_key, (uint32_t)ke);
         else emit_complement(tc, s_key, (uint32_t)ke, 0, tc.S, 0);
     } else {
         return false;
