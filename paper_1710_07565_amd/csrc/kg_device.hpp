@@ -283,13 +283,13 @@ __device__ __forceinline__ double lnf_diff(uint64_t x, uint64_t y)
 }
 
 // floor(a * b / d) for a*b < 2^117, d >= 1 and a quotient below 2^53,
-// exactly: an estimate `est` (off by a few), corrected by the remainder.
-// Below d = 2^60 the remainder of the estimate fits a signed 64-bit word, so
-// the products are needed modulo 2^64 only.
+// exactly: an estimate `est` (off by 2^-45 of itself and one), corrected by the
+// remainder.  Below d = 2^60 and a quotient of 2^45 the remainder of the estimate
+// fits a signed 64-bit word, so the products are needed modulo 2^64 only.
 __device__ __forceinline__ uint64_t muldiv_floor(uint64_t a, uint64_t b, uint64_t d, double est)
 {
     uint64_t q = est <= 0.0 ? 0ull : (uint64_t)est;
-    if (d < (1ull << 60)) {
+    if (d < (1ull << 60) && q < (1ull << 45)) {
         int64_t r = (int64_t)(a * b - q * d);
         while (r < 0) { --q; r += (int64_t)d; }
         while (r >= (int64_t)d) { ++q; r -= (int64_t)d; }
@@ -532,7 +532,8 @@ __device__ __forceinline__ RouQuick<2> quick_of(const BinRatio &r, double Nd, do
 // The mode floor((k + 1)(K + 1) / (N + 2)).
 __device__ __forceinline__ uint64_t hyp_mode(uint64_t N, uint64_t K, uint64_t k, double Nd, double Kd, double kd)
 {
-    // the quotient to about 2^-50: the hardware's reciprocal (2^-26), one step
+    // the quotient to 2^-45 of itself at worst: the hardware's reciprocal (2^29 ulp,
+    // 2^-23), one step
     const double d = Nd + 2.0;
     double r = __builtin_amdgcn_rcp(d);
     r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
