@@ -231,9 +231,9 @@ kg_status plan_instance(const kg_instance &in, Inst &out, uint64_t &tile_bound)
                                             : (ldexp(in.p, (int)t) >= (double)kLambda);
         if (ok) { s = t; break; }
     }
-    {
+    if (((u128)in.n * in.n) >> s >= ((u128)1 << 31)) {
         // every chunk has fewer than 2^31 tiles (the tile index is a 32-bit
-        // stream word): bounded through the largest section
+        // stream word): bounded through the largest section, unless all slots are few enough
         const uint64_t rows = (in.n + in.chunks - 1) / in.chunks;
         const u128 Nc = in.directed ? (u128)rows * (in.n - 1) : (u128)rows * rows;
         if ((Nc >> s) >= ((u128)1 << 31)) return KG_ERANGE;
@@ -302,11 +302,16 @@ struct InstList {
     const Inst &operator[](size_t i) const { return data()[i]; }
 };
 
+// Tiles (their logarithm) of the smallest chunks whose tree plan_top_kernel could
+// shorten: two per planner unit at least, 2^kTopLog units per subtree.
+constexpr uint32_t kDeepLog = kTopLog + 2;
+
 struct Prepared {
     InstList insts;
     uint64_t G = 0, Tb = 0;
     bool sparse = false;              // some instance has tiles of 2^32 slots
-    uint64_t chunks_of[32] = {};      // chunks with 2^l .. 2^(l+1) - 1 tiles, by each instance's mean
+    // chunks with 2^l .. 2^(l+1) - 1 tiles, by each instance's mean, from kDeepLog on
+    uint64_t chunks_of[32] = {};
     Layout L;
 };
 
@@ -314,23 +319,27 @@ kg_status prepare(const kg_instance *in, uint32_t count, Prepared &P)
 {
     if (!in || count == 0) return KG_EINVAL;
     P.insts.resize(count);
-    P.G = 0;
-    P.Tb = 0;
-    P.sparse = false;
     memset(P.chunks_of, 0, sizeof(P.chunks_of));
-    for (uint32_t i = 0; i < count; ++i) {
+    Inst *out = P.insts.data();
+    uint64_t G = 0, Tb = 0;
+    bool sparse = false;
+    for (uint32_t i = 0; i < count; ++i, ++out) {
         uint64_t tb = 0;
-        const kg_status st = plan_instance(in[i], P.insts[i], tb);
+        const kg_status st = plan_instance(in[i], *out, tb);
         if (st) return st;
-        P.insts[i].chunk_base = P.G;
-        P.G += P.insts[i].nchunks;
-        P.Tb += tb;
-        P.sparse |= P.insts[i].s == 32;
-        const uint64_t mean = tb / P.insts[i].nchunks;      // below 2^31 + 2
-        P.chunks_of[mean ? 63 - __builtin_clzll(mean) : 0] += P.insts[i].nchunks;
+        const uint64_t chunks = out->nchunks;
+        out->chunk_base = G;
+        G += chunks;
+        Tb += tb;
+        sparse |= out->s == 32;
+        // (no division for the small instances, of which a batch can have very many)
+        if (tb >> kDeepLog >= chunks) P.chunks_of[63 - __builtin_clzll(tb / chunks)] += chunks;   // below 2^31 + 2
         // one-dimensional grids of one wave per 64 chunks
-        if (P.G > kMaxChunks) return KG_ERANGE;
+        if (G > kMaxChunks) return KG_ERANGE;
     }
+    P.G = G;
+    P.Tb = Tb;
+    P.sparse = sparse;
     P.L = layout_for(count, P.G, P.Tb);
     return KG_OK;
 }
