@@ -289,7 +289,7 @@ __device__ __forceinline__ double lnf_diff(uint64_t x, uint64_t y)
 __device__ __forceinline__ uint64_t muldiv_floor(uint64_t a, uint64_t b, uint64_t d, double est)
 {
     uint64_t q = est <= 0.0 ? 0ull : (uint64_t)est;
-    if (d < (1ull << 60) && q < (1ull << 45)) {
+    if (((uint32_t)(d >> 60) | (uint32_t)(q >> 45)) == 0) {
         int64_t r = (int64_t)(a * b - q * d);
         while (r < 0) { --q; r += (int64_t)d; }
         while (r >= (int64_t)d) { ++q; r -= (int64_t)d; }
