@@ -627,7 +627,9 @@ uint32_t rgg_level(uint64_t n, double r)
 // eighth of a cell, the plane keeps a lane per vertex too: a block of 16 cells then
 // has fewer points than lanes (4^12 cells, both edge passes, lane / block us:
 // 1 point at a cell's radius 993 / 2009, 2 points 2195 / 2280, 2.5 points 2824 /
-// 2427; at 10^-4 of a cell 1 point 932 / 1383, 1.6 points 1553 / 1463).
+// 2427; at 10^-4 of a cell 1 point 932 / 1383, 1.6 points 1553 / 1463) -- from 4^9
+// cells on: fewer do not fill the chip, and there the blocks' shorter passes win
+// (whole call, 1 point at a cell's radius: 4^9 cells 93 / 107, 4^8 64 / 66, 4^6 65 / 62).
 // A block's candidates are its own points and those of the window's cells after
 // it: up to 6 cells' (one cell) or 11 (four) in two dimensions, 20 or 45 in three.
 // Beyond the result words' bits it is tested in binary64, which keeps the passes
@@ -646,7 +648,7 @@ RggBlocks rgg_blocks(int D, uint64_t n, double r, uint32_t L)
     RggBlocks P;
     const double a = ldexp((double)n, -(int)(D * L));     // points per cell
     if (n == 0 || a > (D == 2 ? 32.0 : 22.0)) return P;
-    if (D == 2 && L >= 1 && a < (ldexp(r, (int)L) < 0.125 ? 1.5 : 2.1)) return P;
+    if (D == 2 && L >= 9 && a < (ldexp(r, (int)L) < 0.125 ? 1.5 : 2.1)) return P;
     P.B = L >= 1 && a < (D == 2 ? 10.0 : 7.5) ? 1 : 0;
     if (D == 3 && (P.B == 1 ? a >= 5.0 : a >= 10.0)) P.words = 16;
     if (D == 2 && P.B == 0) P.Q = 14;

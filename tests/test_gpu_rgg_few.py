@@ -1,7 +1,7 @@
 """Plane geometric graphs of about one to three points per cell, on both sides of
 the lines below which a lane per vertex takes the edges instead of a block of
-cells (2.1 points, 1.5 for a radius under an eighth of a cell).  Byte for byte
-against the oracle."""
+cells (2.1 points, 1.5 for a radius under an eighth of a cell; 4^9 cells and
+more).  Byte for byte against the oracle."""
 import numpy as np
 import pytest
 
@@ -10,7 +10,7 @@ from gpu_util import require_gpu, to_np_u32
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("L", [1, 6])
+@pytest.mark.parametrize("L", [1, 8, 9])
 @pytest.mark.parametrize("a", [1.0, 1.49, 1.51, 2.09, 2.11, 3.0])
 @pytest.mark.parametrize("f", [1.0, 0.5, 0.126, 0.124, 1e-3, 0.0])
 def test_few_points_equal_oracle(kgref, L, a, f):
