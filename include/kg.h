@@ -313,7 +313,7 @@ int kg_last_hip_error(void);
  * them.  Host only; synchronises with the recorded events. */
 enum {
     KG_KERNEL_COUNT = 0,   /* per-chunk counts (kg_rgg2d: the quadrant recursion) */
-    KG_KERNEL_SCAN = 1,    /* offsets (the scan of the wave sums and the fix-up; kg_rgg2d: both scans) */
+    KG_KERNEL_SCAN = 1,    /* offsets (the scans of the chunks' sums; kg_rgg2d, kg_rgg3d: of the edge counts) */
     KG_KERNEL_PLAN = 2,    /* tile plan (kg_gnp_skip: count pass; kg_rgg2d: edge count pass) */
     KG_KERNEL_SAMPLE = 3,  /* common-case tile sampler (kg_gnp_skip, kg_rgg2d: write pass) */
     KG_KERNEL_QUEUE = 4    /* general base case for the tiles the sampler queued (kg_rgg2d: points) */

@@ -28,8 +28,8 @@
 // Count pass: the result words and the block's edge count.  Write pass: the
 // words' set bits are the edges, in output order; they are gathered in LDS and
 // stored with consecutive lanes on consecutive edges.  A block with more
-// candidates than its words hold (hardly ever at the densities this path is
-// chosen for) is tested in binary64 in both passes.
+// candidates than its words hold (the path's rule has how often) is tested in
+// binary64 in both passes.
 //
 // What bounds it: vector instructions (in two dimensions 3.5 per test of about
 // 80 per vertex, and more than that again for the window, the lists and the
@@ -181,9 +181,9 @@ struct RggWindow {
     uint64_t full;             // lanes whose cell holds points
     LaneSort order;
 
-    // The parts of a block's candidates (k, C the same in each 8 lanes): the G
-    // of 1 .. 8 with the fewest vector instructions, about 4 (6 in three
-    // dimensions) per candidate and 60 per pass.  Returns G and, above bit
+    // The parts of a block's candidates (k, C the same in each 8 lanes): in two
+    // dimensions the G of 1 .. 8 with the fewest vector instructions, about 4
+    // per candidate and 60 per pass.  Returns G and, above bit
     // 4, the candidates of a part (a multiple of 4); 0 if the result words or
     // the lists are too small.
     static __device__ __forceinline__ uint32_t parts(uint32_t k, uint32_t C)
@@ -197,7 +197,7 @@ struct RggWindow {
         }
         const uint32_t g = (threadIdx.x & 7) + 1;
         const uint32_t c = 4 * (uint32_t)((float)(C + 4 * g - 1) * __builtin_amdgcn_rcpf((float)(4 * g)) + 0.0001f);
-        uint32_t cost = ((k * g + 63) >> 6) * ((D == 2 ? 4 : 6) * c + 60);
+        uint32_t cost = ((k * g + 63) >> 6) * (4 * c + 60);
         if (C > 32 * WORDS || g * ((c + 31) >> 5) > WORDS || g * c > CAND) cost = 0xFFFF;
         // c <= CAND < 2^10, cost < 2^16: the least cost, its c and g
         uint32_t v = cost << 14 | c << 4 | g;
