@@ -36,7 +36,7 @@
 // masks), in the write pass also latency.  n = 2^26 at
 // r = 0.55 (ln n / n)^(1/d), lane per vertex before: two dimensions count 4.4 ->
 // 1.9 ms, write 2.6 -> 2.2 ms (call 7.8 -> 4.4 ms); three dimensions count
-// 10.7 -> 3.2 ms, write 8.3 -> 1.6 ms (20.8 -> 5.6 ms).
+// 10.7 -> 2.9 ms, write 8.3 -> 1.6 ms (20.8 -> 5.6 ms).
 #pragma once
 #include "kg_rgg.hpp"
 #include "kg_rgg3.hpp"
@@ -469,8 +469,8 @@ __global__ __launch_bounds__(64) void rgg_block_count2_kernel(RggBlockJob J)
 // squares are taken 2^(2Q - 14) further to both sides.  A product and 6 vector
 // instructions per 256 tests, where the packed form of two dimensions takes
 // 30: 594 vector instructions per block instead of 1056.  n = 2^26,
-// r = 0.55 (ln n / n)^(1/3): 3.9 -> 3.2 ms (products and vector instructions of a
-// SIMD hardly overlap: together they fill 85 % of the time).
+// r = 0.55 (ln n / n)^(1/3): 3.9 -> 2.9 ms (products and vector instructions of a
+// SIMD hardly overlap: 23 and 70 % of the time).
 template <int B, int WORDS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void rgg_block_count3_kernel(RggBlockJob J)
 {

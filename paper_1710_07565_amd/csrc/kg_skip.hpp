@@ -9,9 +9,10 @@
 // the workspace holds a row of positions per tile, the count pass keeps the
 // events' positions and the write pass only decodes them (skip_gen_kernel,
 // skip_emit_kernel); otherwise the write pass generates the same trials again
-// (skip_write_kernel), which costs about as much (directed n = 2^25, 536 million
-// edges: 2.75 ms a call, with the rows 2.74) but reads and writes no rows.  The chunk and tile layout comes from the main path's
-// count and offset kernels.
+// (skip_write_kernel), which costs no more (directed n = 2^25, 536 million
+// edges: 2.65 ms a call, with the rows 2.73) and reads and writes no rows; there
+// many tiles of few events are counted by a lane each (skip_count_kernel).  The
+// chunk and tile layout comes from the main path's count and offset kernels.
 #pragma once
 #include "kg_tile.hpp"
 
@@ -106,7 +107,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan_sat(uint32_t v)
 // 18 binary64 operations and a 16-byte LDS read instead of about 60.  The gap
 // pass is bound by vector instructions; with this form, the sums below and
 // one 8-byte store a pair, directed n = 2^25, 536 million edges: 2204 ->
-// 1330 us (0.40 million gaps a microsecond), the call 3570 -> 2700 us.
+// 1280 us (0.42 million gaps a microsecond), the call 3570 -> 2700 us.
 struct GapLaw {
     double L, iL, open;
     const double2 *tab;      // LDS copy of g_gap_tab, or null (full form only)
